@@ -48,7 +48,7 @@ UNIT = "segment-pair evals/s"
 # refinement steps; selects, compares and sign changes = 0).  The b_j term's
 # scalar is summed per target point and its vector added once, which the
 # per-evaluation counts leave out.
-FLOP_F64_EVAL = 126          # FP64 path (pair_acc_f64)
+FLOP_F64_EVAL = 115          # FP64 path (pair_run_acc_f64: sources in runs of one Burgers vector)
 FLOP_MIX_EVERY_F32 = {0: 23, 1: 15, 2: 23}   # mixed, every pair: offset to the source midpoint
                              # (9), its axial part (5) and square (1); variants 0 and 2 also its
                              # squared length (5) and the band/collinearity test (3)

@@ -169,7 +169,8 @@ __host__ __device__ inline void fcc(int alpha, double n[3], double m[3])
 
 // FP64 segment records, structure of arrays with stride n_segs:
 //  0..2 x1/a, 3..5 t, 6 L/a, 7..9 b/a, 10..12 c = (b/a) x t, 13 length of the
-//  run of segments that each start where the one before ends (as a double);
+//  run of segments that each start where the one before ends and share its
+//  Burgers vector (as a double);
 // followed in the same buffer by one RECA-double record per segment (array of
 // structures, read with wavefront-uniform scalar loads by the FP64 kernel):
 //  0..12 as above, 13 the run length as int64 bits, 14..15 zero.

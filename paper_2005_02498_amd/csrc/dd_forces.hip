@@ -176,8 +176,12 @@ __global__ __launch_bounds__(PREP_BLOCK) void k_seg_prep(PrepArgs A)
     sh_g2[tid] = g2;
     sh_inst[tid] = inst;
     __syncthreads();
-    // does the next segment of this workgroup start at the node where this one ends?
-    sh_chain[tid] = live && tid + 1 < PREP_BLOCK && sh_inst[tid + 1] == inst && sh_g1[tid + 1] == g2;
+    // does the next segment of this workgroup start at the node where this one
+    // ends, with the same Burgers vector?
+    bool chain = live && tid + 1 < PREP_BLOCK && sh_inst[tid + 1] == inst && sh_g1[tid + 1] == g2;
+    if (chain)
+        for (int k = 0; k < 3; ++k) chain = chain && A.burgers[k * ns + s + 1] == A.burgers[k * ns + s];
+    sh_chain[tid] = chain;
     __syncthreads();
     if (!live) return;
     double rr[13];
@@ -195,9 +199,10 @@ __global__ __launch_bounds__(PREP_BLOCK) void k_seg_prep(PrepArgs A)
     r[7 * ns + s] = b[0];  r[8 * ns + s] = b[1];  r[9 * ns + s] = b[2];
     r[10 * ns + s] = c[0]; r[11 * ns + s] = c[1]; r[12 * ns + s] = c[2];
     // length of the run of segments starting here in which each next segment
-    // starts at the node where the one before it ends (loops stored in order),
-    // within this workgroup's segments: the all-pairs kernel computes the
-    // inverse distance to a shared node once per run
+    // starts at the node where the one before it ends and has the same Burgers
+    // vector (loops stored in order), within this workgroup's segments: the
+    // all-pairs kernel computes the inverse distance to a shared node, and the
+    // products with the Burgers vector, once per run
     int run = 1;
     while (tid + run < PREP_BLOCK && sh_chain[tid + run - 1]) ++run;
     r[13 * ns + s] = (double)run;

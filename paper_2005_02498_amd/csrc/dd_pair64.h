@@ -102,6 +102,57 @@ __device__ __forceinline__ void pair_acc_f64(
     a2 = fma(Ph, h2, fma(Pt, t2, fma(Pc, c2, fma(Pr, rb2, a2))));
 }
 
+// One source of a run of sources with the same Burgers vector b.  With
+// c = b x t every term with a cross product by b can wait for the end of the
+// run: with g = kr b_j x b (kr = k1/k2), c.b_j = t.g / kr and (rho x b).b_j =
+// -rho.g / kr, so that over the run
+//   sum sigma b_j / k2 = U - kr W x b + ak b_j,
+//   U = sum Pt t + Ph rho,   W = sum Pr rho + Pc t,
+//   Pt = q (P tb - D51 hb) + e1 tg + g0 hg,   Ph = q (E50 hb - D51 tb) - I30 tg / kr,
+//   Pr = g0 tb,   Pc = e1 tb - I30 hb / kr,   e1 = (nu / kr) I31 - D51,
+// with tb = t.b_j, hb = rho.b_j, tg = t.g, hg = rho.g and the line integrals of
+// pair_acc_f64: rho x b (6 operations a source) is never formed.  ikr = 1/kr,
+// nukr = nu/kr; r1, r1c, r2, r2c as in pair_acc_f64.
+__device__ __forceinline__ void pair_run_acc_f64(
+    double x0, double x1, double x2, double bj0, double bj1, double bj2, double g0x, double g1x, double g2x,
+    double p0, double p1, double p2, double t0, double t1, double t2, double L, double c0, double c1, double c2,
+    double ikr, double nukr, double r1, double r1c, double &r2, double &r2c, double &U0, double &U1, double &U2,
+    double &W0, double &W1, double &W2, double &ak)
+{
+    const double R0 = x0 - p0, R1 = x1 - p1, R2 = x2 - p2;
+    const double y = fma(R2, t2, fma(R1, t1, R0 * t0));
+    const double h0 = fma(-y, t0, R0), h1 = fma(-y, t1, R1), h2 = fma(-y, t2, R2);   // rho
+    const double d2 = fma(h2, h2, fma(h1, h1, fma(h0, h0, 1.0)));
+    const double u2 = L - y;
+    r2 = rsqrt64(fma(u2, u2, d2));
+    r2c = r2 * r2 * r2;
+    const double id2 = rcp64(d2);
+    const double s1 = -y * r1, s2 = u2 * r2;
+    const double I30 = (s2 - s1) * id2;
+    const double P = I30 * fma(s1, s1 + s2, s2 * s2);
+    const double E50 = fma(3.0, I30, -P) * id2;
+    const double I30k = I30 * ikr;
+    const double D51 = r1c - r2c;
+    const double e1 = fma(nukr, r1 - r2, -D51);
+    const double F = I30 + E50, g0 = I30 + F;
+    const double q = fma(c2, h2, fma(c1, h1, c0 * h0));
+    ak = fma(q, F, ak);   // kd
+    const double tb = fma(t2, bj2, fma(t1, bj1, t0 * bj0));
+    const double hb = fma(h2, bj2, fma(h1, bj1, h0 * bj0));
+    const double tg = fma(t2, g2x, fma(t1, g1x, t0 * g0x));
+    const double hg = fma(h2, g2x, fma(h1, g1x, h0 * g0x));
+    const double Pt = fma(q, fma(P, tb, -D51 * hb), fma(g0, hg, e1 * tg));
+    const double Ph = fma(q, fma(E50, hb, -D51 * tb), -I30k * tg);
+    const double Pc = fma(e1, tb, -I30k * hb);
+    const double Pr = g0 * tb;
+    U0 = fma(Ph, h0, fma(Pt, t0, U0));
+    U1 = fma(Ph, h1, fma(Pt, t1, U1));
+    U2 = fma(Ph, h2, fma(Pt, t2, U2));
+    W0 = fma(Pr, h0, fma(Pc, t0, W0));
+    W1 = fma(Pr, h1, fma(Pc, t1, W1));
+    W2 = fma(Pr, h2, fma(Pc, t2, W2));
+}
+
 // One isolated pair (the near-field branch of the mixed path): adds
 // sigma^i b_j / k2 of the source whose FP64 record is d (x1, t, L, b, c in
 // entries 0..12) to (a0, a1, a2).

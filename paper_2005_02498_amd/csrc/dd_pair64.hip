@@ -13,15 +13,29 @@ namespace dd {
 // (3 values) over the range; the item's sums, scaled by k2, go to their own
 // slot, reduced in a fixed order later.
 //
-// Sources come in runs that share nodes (loops stored in order): the inverse
-// distance to a run's first node is computed once, then each source reuses
-// the previous source's far-end value.  Only the part of the range that holds
-// the tile's own segments tests for the excluded self pair.
+// Sources come in runs that share nodes and the Burgers vector (loops stored
+// in order): the inverse distance to a run's first node is computed once, then
+// each source reuses the previous source's far-end value, and the cross
+// products by the Burgers vector are taken once per run (pair_run_acc_f64).
+// Only the part of the range that holds the tile's own segments tests for the
+// excluded self pair.
+//
+// Bound by FP64 issue: 82 VALU instructions per evaluation in the inner loop
+// (89 when every source forms rho x b), at about 4.75 cycles each at the 2.25 GHz
+// this load runs at.  A step of 16,384 segments at 2 points, start to end:
+// 1.535 -> 1.444 ms.  Measured and left out: two Gauss points of a segment per
+// lane (t.b_j and t.g shared, 79 instructions, 120 VGPRs): 1.449 ms; six
+// wavefronts per SIMD forced by launch bounds (80 VGPRs for 96): 1.473 ms.
+//
+// Runs of fewer than RUN_MIN sources take the form that needs no set-up: the
+// run form costs 15 instructions per run and saves 7 per source.
+constexpr int RUN_MIN = 4;
+
 template <bool SELF>
 __device__ __forceinline__ void pair64_range(const double *__restrict__ ra, int64_t b, int64_t e,
                                              int64_t j, double xq0, double xq1, double xq2, double bj0,
-                                             double bj1, double bj2, double kr, double nu, double &a0,
-                                             double &a1, double &a2, double &ak)
+                                             double bj1, double bj2, double kr, double nu, double ikr,
+                                             double nukr, double &a0, double &a1, double &a2, double &ak)
 {
     for (int64_t m = b; m < e;) {
         const double *c = ra + m * RECA;
@@ -32,20 +46,27 @@ __device__ __forceinline__ void pair64_range(const double *__restrict__ ra, int6
         double r1 = rsqrt64(fma(R2, R2, fma(R1, R1, fma(R0, R0, 1.0))));
         double r1c = r1 * r1 * r1;
         int k = 0;
-        if (!SELF) {
+        if (!SELF && n >= RUN_MIN) {
+            const double b0 = c[7], b1 = c[8], b2 = c[9];
+            const double g0 = kr * fma(bj1, b2, -bj2 * b1), g1 = kr * fma(bj2, b0, -bj0 * b2),
+                         g2 = kr * fma(bj0, b1, -bj1 * b0);
+            double w0 = 0.0, w1 = 0.0, w2 = 0.0;
             // two sources per iteration: the second takes the first's far-end
             // values and leaves its own where the first's near-end values were,
             // so no register copy is made per source
             for (; k + 2 <= n; k += 2, c += 2 * RECA) {
                 double r2, r2c;
-                pair_acc_f64(xq0, xq1, xq2, bj0, bj1, bj2, c[0], c[1], c[2], c[3], c[4], c[5], c[6],
-                             c[7], c[8], c[9], c[10], c[11], c[12], kr, nu, r1, r1c, r2, r2c, a0, a1,
-                             a2, ak);
+                pair_run_acc_f64(xq0, xq1, xq2, bj0, bj1, bj2, g0, g1, g2, c[0], c[1], c[2], c[3], c[4], c[5],
+                                 c[6], c[10], c[11], c[12], ikr, nukr, r1, r1c, r2, r2c, a0, a1, a2, w0, w1, w2,
+                                 ak);
                 const double *d = c + RECA;
-                pair_acc_f64(xq0, xq1, xq2, bj0, bj1, bj2, d[0], d[1], d[2], d[3], d[4], d[5], d[6],
-                             d[7], d[8], d[9], d[10], d[11], d[12], kr, nu, r2, r2c, r1, r1c, a0, a1,
-                             a2, ak);
+                pair_run_acc_f64(xq0, xq1, xq2, bj0, bj1, bj2, g0, g1, g2, d[0], d[1], d[2], d[3], d[4], d[5],
+                                 d[6], d[10], d[11], d[12], ikr, nukr, r2, r2c, r1, r1c, a0, a1, a2, w0, w1, w2,
+                                 ak);
             }
+            a0 = fma(-kr, fma(w1, b2, -w2 * b1), a0);
+            a1 = fma(-kr, fma(w2, b0, -w0 * b2), a1);
+            a2 = fma(-kr, fma(w0, b1, -w1 * b0), a2);
         }
         for (; k < n; ++k, c += RECA) {
             double r2, r2c;
@@ -75,7 +96,8 @@ __global__ __launch_bounds__(TILE) void k_pair64(const Item *__restrict__ items,
                                                  const Tile *__restrict__ tiles,
                                                  const double *__restrict__ rec,
                                                  const double *__restrict__ ra, int64_t ns,
-                                                 GaussRule g, double kr, double nu, double k2,
+                                                 GaussRule g, double kr, double nu, double ikr, double nukr,
+                                                 double k2,
                                                  double *__restrict__ partial)
 {
     const Item it = items[blockIdx.x];
@@ -100,9 +122,9 @@ __global__ __launch_bounds__(TILE) void k_pair64(const Item *__restrict__ items,
     const int64_t jlo = tl.point_begin / Q, jhi = (tl.point_begin + tl.n_points - 1) / Q;
     const int64_t b = it.src_begin, e = it.src_end;
     const int64_t s0 = min(max(b, jlo), e), s1 = min(max(b, jhi + 1), e);
-    pair64_range<false>(ra, b, s0, j, xq0, xq1, xq2, bj0, bj1, bj2, kr, nu, a0, a1, a2, ak);
-    pair64_range<true>(ra, s0, s1, j, xq0, xq1, xq2, bj0, bj1, bj2, kr, nu, a0, a1, a2, ak);
-    pair64_range<false>(ra, s1, e, j, xq0, xq1, xq2, bj0, bj1, bj2, kr, nu, a0, a1, a2, ak);
+    pair64_range<false>(ra, b, s0, j, xq0, xq1, xq2, bj0, bj1, bj2, kr, nu, ikr, nukr, a0, a1, a2, ak);
+    pair64_range<true>(ra, s0, s1, j, xq0, xq1, xq2, bj0, bj1, bj2, kr, nu, ikr, nukr, a0, a1, a2, ak);
+    pair64_range<false>(ra, s1, e, j, xq0, xq1, xq2, bj0, bj1, bj2, kr, nu, ikr, nukr, a0, a1, a2, ak);
     a0 = fma(ak, bj0, a0);   // the b_j terms of every source at once
     a1 = fma(ak, bj1, a1);
     a2 = fma(ak, bj2, a2);
@@ -119,7 +141,7 @@ void launch_pair64(const Item *items, const Tile *tiles, const double *rec, int6
 {
     const double kr = k1 / k2, nu = 1.0 - 2.0 * kr;
     hipLaunchKernelGGL(k_pair64, dim3((unsigned)n_items), dim3(TILE), 0, st, items, tiles, rec,
-                       rec + (int64_t)REC64 * ns, ns, g, kr, nu, k2, partial);
+                       rec + (int64_t)REC64 * ns, ns, g, kr, nu, 1.0 / kr, nu / kr, k2, partial);
 }
 
 }  // namespace dd
