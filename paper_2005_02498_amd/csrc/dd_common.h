@@ -187,13 +187,13 @@ inline size_t rec64_bytes(int64_t ns)
 // the midpoint xm/a rounded to FP32 and its rounding remainder xm/a - [XH],
 // t, and for the source quadrature of the kernel variant in use (points
 // xm +- hq t with weight Wo each, plus xm with weight Wc for 3 points) hq,
-// Wo b/a, Wo c, the squared band outside which it is used, 1 + hq^2, 2 hq and
-// Wc/Wo; then L/a and 1/Wo (read only outside the quadrature) and two zeros.
+// Wo b/a, Wo c, 1 + hq^2, 2 hq, Wc/Wo and the squared band outside which it is
+// used; then L/a and 1/Wo (read only outside the quadrature) and two zeros.
 // Without a quadrature Wo = 1.  The field is linear in b (c = b x t), so a
 // rule on the scaled b and c needs no weight; the closed form unscales them
 // with 1/Wo.  The quadrature reads the first R32_QUAD_VECS groups of four.
-constexpr int R32_XH = 0, R32_XL = 3, R32_T = 6, R32_HQ = 9, R32_B = 10, R32_C = 13, R32_BAND = 16,
-              R32_RA0 = 17, R32_TW = 18, R32_WC = 19, R32_L = 20, R32_IW = 21;
+constexpr int R32_XH = 0, R32_XL = 3, R32_T = 6, R32_HQ = 9, R32_B = 10, R32_C = 13, R32_RA0 = 16, R32_TW = 17,
+              R32_WC = 18, R32_BAND = 19, R32_L = 20, R32_IW = 21;
 constexpr int R32_QUAD_VECS = 5;
 constexpr int REC32A = 24;
 // Mixed kernel variants: 0 = 2-point source quadrature beyond max(30 L,
@@ -271,11 +271,12 @@ int burst_batch_init(BurstBatch &B, hipStream_t st);
 int burst_batch_run(const BurstBatch &B, const std::vector<uint8_t> &active, const double *sigma_dev,
                     int n_steps, double *sums_dev, hipStream_t st);
 
-// All-pairs launchers (one workgroup per work item, TILE threads).
+// All-pairs launchers (one workgroup per work item, TILE threads); range = the
+// longest source range of an item.
 void launch_pair64(const Item *items, const Tile *tiles, const double *rec, int64_t ns, const GaussRule &g,
                    double k1, double k2, double *partial, int64_t n_items, hipStream_t st);
 void launch_pair_mixed(const Item *items, const Tile *tiles, const double *rec, const float *rec32, int64_t ns,
                        const GaussRule &g, double k1, double k2, float cut, double *partial,
-                       unsigned long long *counters, int64_t n_items, int variant, hipStream_t st);
+                       unsigned long long *counters, int64_t n_items, int64_t range, int variant, hipStream_t st);
 
 }  // namespace dd

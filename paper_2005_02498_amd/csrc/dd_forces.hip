@@ -1549,7 +1549,7 @@ struct ForceCtx {
     int32_t *scan_tmp = nullptr;   // scratch of the node-list scan (after csr_cnt)
     Tile *tiles = nullptr;
     Item *items = nullptr;
-    int64_t n_items = 0;
+    int64_t n_items = 0, range = 0;   // work items and their longest source range
     GaussRule g{};
     double k1 = 0, k2 = 0, inv_a = 0, inv_mu = 0, fscale = 0, a = 0;
     int precision = DD_FP64;
@@ -1643,6 +1643,7 @@ int setup(Workspace *ws, hipStream_t st, const std::vector<int64_t> &seg_off_h, 
     C.items = (Item *)ws->ptr[WS_ITEMS];
     C.L.tile_begin = n_inst > 1 || active ? (const int64_t *)ws->ptr[WS_OFFS] : nullptr;
     C.n_items = g_plan_items;
+    C.range = g_plan_chunk;
     if ((rc = ensure(ws, WS_PARTIAL, sizeof(double) * 3 * TILE * std::max<int64_t>(C.n_items, 1), &p)))
         return rc;
     C.partial = (double *)p;
@@ -1821,7 +1822,7 @@ int launch_forces(ForceCtx &C, Workspace *ws, const double *x, const int32_t *se
             timing_begin(st, ws->capturing);
             if (C.precision == DD_MIXED)
                 launch_pair_mixed(C.items, C.tiles, C.rec64, C.rec32, ns, C.g, C.k1, C.k2, C.cut, C.partial,
-                                  ws->near_count, C.n_items, C.variant, st);
+                                  ws->near_count, C.n_items, C.range, C.variant, st);
             else
                 launch_pair64(C.items, C.tiles, C.rec64, ns, C.g, C.k1, C.k2, C.partial, C.n_items, st);
             timing_end(st, ws->capturing);
@@ -1986,7 +1987,7 @@ int tuned_chunk(Workspace *ws, hipStream_t st, const std::vector<int64_t> &so, i
             (void)hipEventRecord(e0, st);
             if (prec == DD_MIXED)
                 launch_pair_mixed(C.items, C.tiles, C.rec64, C.rec32, ns, C.g, C.k1, C.k2, C.cut, C.partial,
-                                  ws->near_count, C.n_items, C.variant, st);
+                                  ws->near_count, C.n_items, C.range, C.variant, st);
             else
                 launch_pair64(C.items, C.tiles, C.rec64, ns, C.g, C.k1, C.k2, C.partial, C.n_items, st);
             // the reduction of the partial sums grows with the number of work
@@ -2943,6 +2944,7 @@ extern "C" int dd_nodal_forces_noalloc(int64_t n_nodes, const double *x, int64_t
     C.items = cv.take<Item>((size_t)std::max<int64_t>(n_items, 1));
     C.partial = cv.take<double>(3 * (size_t)TILE * (size_t)std::max<int64_t>(n_items, 1));
     C.n_items = n_items;
+    C.range = chunk_len;
     if (n_items > 0)
         hipLaunchKernelGGL(k_plan_flat, dim3(grid_for(n_items, 256, INT32_MAX)), dim3(256), 0, st, C.tiles,
                            C.items, n_segs, n_gauss, chunk_len, n_tiles, n_chunks);

@@ -119,8 +119,9 @@ __device__ __forceinline__ void pair_acc_f32(
 // a vector register by the caller: an FP32 instruction with a literal or
 // scalar-register operand issues at half the rate of one whose operands are
 // all vector registers.
+// tb = t.b_j and cb = c.b_j come from the caller.
 __device__ __forceinline__ void quad_moments_acc_f32(float e0, float e1, float e2, float ym, const float *s,
-                                                     float S3, float S5, float S3v, float S5v, float S5vv,
+                                                     float tb, float cb, float S3, float S5, float S3v, float S5v, float S5vv,
                                                      float bj0, float bj1, float bj2, float kr, float nu, float three,
                                                      float &f0, float &f1, float &f2, float &fk)
 {
@@ -129,9 +130,7 @@ __device__ __forceinline__ void quad_moments_acc_f32(float e0, float e1, float e
     const float c0 = s[R32_C], c1 = s[R32_C + 1], c2 = s[R32_C + 2];
     const float h0 = fmaf(-ym, t0, e0), h1 = fmaf(-ym, t1, e1), h2 = fmaf(-ym, t2, e2);
     const float rb0 = fmaf(h1, b2, -h2 * b1), rb1 = fmaf(h2, b0, -h0 * b2), rb2 = fmaf(h0, b1, -h1 * b0);
-    const float tb = fmaf(t2, bj2, fmaf(t1, bj1, t0 * bj0));
     const float hb = fmaf(h2, bj2, fmaf(h1, bj1, h0 * bj0));
-    const float cb = fmaf(c2, bj2, fmaf(c1, bj1, c0 * bj0));
     const float rbb = fmaf(rb2, bj2, fmaf(rb1, bj1, rb0 * bj0));
     const float q = fmaf(c2, h2, fmaf(c1, h1, c0 * h0));
     const float q3 = three * q;
@@ -147,15 +146,25 @@ __device__ __forceinline__ void quad_moments_acc_f32(float e0, float e1, float e
     f2 = fmaf(Ch, h2, fmaf(Ct, t2, fmaf(Cc, c2, fmaf(Cr, rb2, f2))));
 }
 
+// t.b_j and c.b_j of the source whose FP32 record is s.
+__device__ __forceinline__ float record_tb(const float *s, float bj0, float bj1, float bj2)
+{
+    return fmaf(s[R32_T + 2], bj2, fmaf(s[R32_T + 1], bj1, s[R32_T] * bj0));
+}
+__device__ __forceinline__ float record_cb(const float *s, float bj0, float bj1, float bj2)
+{
+    return fmaf(s[R32_C + 2], bj2, fmaf(s[R32_C + 1], bj1, s[R32_C] * bj0));
+}
+
 // e = target - source midpoint, ee = |e|^2, ym = e.t; s = the source's FP32 record (see
-// REC32A), whose b and c carry the weight Wo; adds K b_j / k2 to (f0, f1, f2)
+// REC32A), whose b and c carry the weight Wo (ra0, tw2: its 1 + hq^2 and 2 hq); adds K b_j / k2 to (f0, f1, f2)
 // + fk b_j.  2-point rule: points at v = ym -+ hq, weight Wo each (in b, c).
 __device__ __forceinline__ void quad2_acc_f32(float e0, float e1, float e2, float ee, float ym, const float *s,
-                                              float bj0, float bj1, float bj2, float kr, float nu, float three,
+                                              float ra0, float tw2, float tb, float cb, float bj0, float bj1, float bj2, float kr, float nu, float three,
                                               float &f0, float &f1, float &f2, float &fk)
 {
     const float hq = s[R32_HQ];
-    const float base = ee + s[R32_RA0], tw = s[R32_TW] * ym;
+    const float base = ee + ra0, tw = tw2 * ym;
     const float vA = ym + hq, vB = ym - hq;
     const float iA = __builtin_amdgcn_rsqf(base + tw), iB = __builtin_amdgcn_rsqf(base - tw);
     const float iA2 = iA * iA, iB2 = iB * iB;
@@ -165,7 +174,7 @@ __device__ __forceinline__ void quad2_acc_f32(float e0, float e1, float e2, floa
     const float S3 = iA3 + iB3, S5 = iA5 + iB5;
     const float S3v = fmaf(iA3, vA, iB3 * vB), S5v = pA + pB;
     const float S5vv = fmaf(pA, vA, pB * vB);
-    quad_moments_acc_f32(e0, e1, e2, ym, s, S3, S5, S3v, S5v, S5vv, bj0, bj1, bj2, kr, nu, three, f0, f1, f2, fk);
+    quad_moments_acc_f32(e0, e1, e2, ym, s, tb, cb, S3, S5, S3v, S5v, S5vv, bj0, bj1, bj2, kr, nu, three, f0, f1, f2, fk);
 }
 
 // 3-point rule: points at v = ym -+ hq with weight Wo (in b, c) and at v = ym
@@ -173,11 +182,11 @@ __device__ __forceinline__ void quad2_acc_f32(float e0, float e1, float e2, floa
 // sqrt(3/5), Wo = 5L/18, Wc = 8L/18).
 // Its error is below 2e-7 relative beyond 6 source lengths from the midpoint.
 __device__ __forceinline__ void quad3_acc_f32(float e0, float e1, float e2, float ee, float ym, const float *s,
-                                              float bj0, float bj1, float bj2, float kr, float nu, float three,
+                                              float ra0, float tw2, float tb, float cb, float bj0, float bj1, float bj2, float kr, float nu, float three,
                                               float &f0, float &f1, float &f2, float &fk)
 {
-    const float hq = s[R32_HQ], Wc = s[R32_WC];
-    const float base = ee + s[R32_RA0], tw = s[R32_TW] * ym;
+    const float hq = s[R32_HQ], Wc = 1.6f;   // the record's Wc/Wo
+    const float base = ee + ra0, tw = tw2 * ym;
     const float vA = ym + hq, vB = ym - hq;
     const float iA = __builtin_amdgcn_rsqf(base + tw), iB = __builtin_amdgcn_rsqf(base - tw);
     const float iC = __builtin_amdgcn_rsqf(ee + 1.0f);
@@ -189,7 +198,7 @@ __device__ __forceinline__ void quad3_acc_f32(float e0, float e1, float e2, floa
     const float S3v = fmaf(Wc, iC3 * ym, fmaf(iA3, vA, iB3 * vB));
     const float S5v = fmaf(Wc, pC, pA + pB);
     const float S5vv = fmaf(Wc, pC * ym, fmaf(pA, vA, pB * vB));
-    quad_moments_acc_f32(e0, e1, e2, ym, s, S3, S5, S3v, S5v, S5vv, bj0, bj1, bj2, kr, nu, three, f0, f1, f2, fk);
+    quad_moments_acc_f32(e0, e1, e2, ym, s, tb, cb, S3, S5, S3v, S5v, S5vv, bj0, bj1, bj2, kr, nu, three, f0, f1, f2, fk);
 }
 
 }  // namespace dd

@@ -67,3 +67,30 @@ def test_short_runs_vs_oracle(Q, chunk, variant):
             assert e < tol
     finally:
         dd.dd_set_plan(-1)
+
+
+@pytest.mark.parametrize("nseg", [27, 32])
+@pytest.mark.parametrize("Q,variant", [(2, 0), (2, 2), (4, 2), (3, 0)])
+def test_mixed_safe_sources_vs_oracle(nseg, Q, variant):
+    """The mixed kernel's loop without tests: loops of 32 segments (each
+    wavefront's target points share a Burgers vector at 2 and 4 points) and of
+    27 (they do not), a source range that is no multiple of 64; every pair it
+    takes by quadrature is counted as such."""
+    rng = np.random.default_rng(3)
+    x, seg, bur, nrm, _ = W._loops(rng, 19, 9000.0, 100.0, 500.0, nseg=nseg)
+    sig = W.uniaxial_001(50e6)
+    ref = O.nodal_forces(x, seg, bur, sig, W.MU, W.NU, W.CORE_A, Q)
+    dev = torch.device("cuda:0")
+    args = [torch.tensor(a, device=dev) for a in (x, seg, bur, nrm)]
+    dd.dd_set_plan(200, variant)
+    try:
+        dd.dd_timing_read(reset=True)
+        F = dd.dd_nodal_forces(*args, sig, MAT, Q, dd.DD_MIXED, 20.0).cpu().numpy()
+        quad = dd.dd_timing_read(reset=True)[3]
+    finally:
+        dd.dd_set_plan(-1)
+    e = normwise(F, ref)
+    share = quad / (Q * (19.0 * nseg) ** 2)
+    print(f"mixed {nseg} segments a loop Q={Q} variant={variant}: err {e:.2e}, quadrature share {share:.2f}")
+    assert e < 1e-4
+    assert share > 0.5
