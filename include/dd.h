@@ -123,15 +123,16 @@ int dd_set_autotune(int on);
 /* How dd_burst_batch runs its steps.  0 (default): batches of small FP64
  * bursts (every instance at most 512 segments and 512 nodes; no exact band)
  * run all their steps in one persistent launch, several co-resident
- * workgroups per instance meeting at one barrier per step (about 2 nodes per
- * workgroup, at most 128 per instance), when all of them fit on the device at
- * once; other bursts replay a cached graph of per-step kernels.  1: always the step graph.  2: the persistent launch with one
- * workgroup per instance (a reference point for the split).  The persistent
- * launch's results do not depend on the split; they differ from the step
- * graph's only in the order of floating-point sums.  Returns the previous
- * mode, or DD_EINVAL for a mode other than 0, 1 and 2.  A persistent burst
- * whose workgroups wait too long at a step barrier raises DD_EHIP (reported
- * as the device-side checks are). */
+ * workgroups per instance that exchange the node positions through memory once
+ * per step (as few nodes per workgroup as the device has room for, at most 32),
+ * unless the instances are so many that the step graph is the faster; other
+ * bursts replay a cached graph of per-step kernels.  1: always the step graph.
+ * 2: the persistent launch with one workgroup per instance (a reference point
+ * for the split).  The positions do not depend on the split; the slip rates, and
+ * the results of the step graph, differ only in the order of floating-point
+ * sums.  Returns the previous mode, or DD_EINVAL for a mode other than 0, 1 and
+ * 2.  A persistent burst whose workgroups wait too long for a position raises
+ * DD_EHIP (reported as the device-side checks are). */
 int dd_set_burst_mode(int mode);
 
 /* Report, and clear, the conditions the device-side checks raised since the
@@ -155,7 +156,8 @@ int dd_set_plan(int64_t chunk_len, int variant);
 
 /* The work split of the most recent force evaluation on this device: the
  * source-range length of a work item, the number of work items, and the
- * mixed kernel's variant.  Variants: 0 = each source is first tested in FP32
+ * mixed kernel's variant (a single FP64 volume of at most 512 segments and
+ * nodes, without the exact band, is one item of all sources per node).  Variants: 0 = each source is first tested in FP32
  * against a band of max(30 L, cutoff + L/2) around its midpoint, and sources
  * outside it for every target point of a wavefront are evaluated by 2-point
  * Gauss-Legendre quadrature along the source; 1 = no such test, every pair

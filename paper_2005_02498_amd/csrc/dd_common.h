@@ -46,7 +46,7 @@ enum : unsigned {
     FLAG_NONFINITE = 8u,
     FLAG_NEAR_FULL = 16u,     // a near-pair list or the pair store ran out of room
     FLAG_NEAR_PANELS = 32u,   // an exact-band integral needed more panels than allowed
-    FLAG_BARRIER = 64u,       // a persistent burst's barrier wait ran out of polls
+    FLAG_BARRIER = 64u,       // a persistent burst waited too long for a position
 };
 
 // -------------------------------------------------------------- workspace --
@@ -92,9 +92,8 @@ enum Slot {
     WS_SES_X,          //   their end points and bounding spheres
     WS_JN_CAND,        // junction nodes: per-segment candidates and parameters
     WS_T0,             // junction bursts: the call's start time (one double)
-    WS_PB,             // persistent bursts: second position buffer, velocities, per-workgroup sums
+    WS_PB,             // persistent bursts: published and final positions, per-workgroup sums
     WS_PB_INT,         //   workgroup tables
-    WS_PB_BAR,         //   barrier arrival words
     WS_NSLOTS
 };
 

@@ -1205,277 +1205,565 @@ __global__ void k_scale_rates(double *acc, int64_t n, double inv_steps)
     if (i < n) acc[i] *= inv_steps;
 }
 
-// ------------------------------------------------ persistent small bursts --
-// Every step of a batch of small bursts (FP64, no junctions, no exact band)
-// in one launch: G_i co-resident workgroups per instance i (a cooperative
-// launch) that meet at one barrier per step.  Each workgroup rebuilds its
-// instance's segment records in LDS from the positions of the step; it owns
-// a contiguous range of the instance's nodes and evaluates, for every
-// segment incident to them (a segment whose nodes lie in two ranges is
-// evaluated by both owners), the stress at its Gauss points from every other
-// segment, summed over fixed chunks of PB_CHUNK sources in chunk order, then
-// the end forces, the nodal forces in node-list order and the glide step of
-// its nodes.  No sum depends on G_i, so the results do not depend on how the
-// instances are split.  Positions and velocities alternate between two
-// buffers from step to step.  The slip-rate sums of a step are formed after
-// the next barrier (every velocity is then written; the step's records are
-// still in LDS), per workgroup over the segments that start at its nodes, in
-// index order, and summed over the workgroups in order at the end.
+// -------------------------------------------------- small FP64 volumes --
+// Volumes of at most PB_MAX_SEGS segments and nodes (FP64, no junctions, no
+// exact band).  G_i workgroups share instance i; each owns a contiguous range of
+// its nodes and evaluates, for every segment incident to them (a segment whose
+// nodes lie in two ranges is evaluated by both owners), the stress at its Gauss
+// points from every other segment, then the end forces, the nodal forces in
+// node-list order and the glide velocities of its nodes.  A thread holds one
+// source segment in registers, rebuilt every step from the positions in LDS, and
+// takes PB_POINTS target points at a time; with fewer sources than threads the
+// workgroup splits the points over several copies of the sources.  The stresses
+// of a target point are summed over the sources in a fixed order, so no result
+// depends on G_i.
+//
+// BURST: every step of a batch of bursts in one launch (cooperative: all
+// workgroups are resident).  A node's new position is published component by
+// component in one of three buffers, whose unwritten words hold PB_EMPTY, a
+// signaling NaN that no arithmetic produces: a workgroup that needs the
+// positions of step k polls buffer k mod 3 until every word of its instance is
+// there, so the data is its own barrier and no fence is needed.  Once it has
+// read all of step k, every workgroup has published step k and so has read all
+// of step k - 1: the owner then empties its words of buffer (k - 1) mod 3, the
+// one that step k + 2 uses.  That store has left before the owner publishes step
+// k + 1, and a reader polls step k + 2 only after it has read step k + 1.  The
+// slip rates are collected per segment and owned node after the publication, and
+// summed over the workgroups by k_pb_finish, which also copies the final
+// positions.
+// Otherwise (one volume, one force evaluation): the nodal forces, and the glide
+// velocities if asked for.
+//
+// Bound by latency.  256 segments at 2 points, 256 workgroups of one node: 5.2 us a
+// step (21.5 before, with a barrier of fences and arrival words, records of every
+// segment in LDS rows whose reads all met one bank, and serial sums), of which
+// 0.3 us records, 1.2 us stresses (1,024 evaluations a workgroup, 0.8 us of FP64
+// issue on its CU), 0.6 us sums and point forces, and the rest the node's glide and
+// the way of its position through memory to the other workgroups (about 2 us).
+// Left out: two nodes a workgroup (8.5 us: fewer CUs), several copies of the
+// published positions (5.6), target points precomputed in LDS (no gain).
 constexpr int PB_THREADS = 512;
 constexpr int PB_MAX_SEGS = 512;    // segments and nodes per instance
-constexpr int PB_CHUNK = 8;         // sources per partial sum
-constexpr int PB_ITEMS = 1024;      // (target point, chunk) partial sums held at once
-constexpr int PB_NODES_PER_WG = 2;  // nodes per workgroup aimed at
-constexpr int PB_MAX_G = 128;       // workgroups per instance at most
-constexpr uint64_t PB_WAIT_TICKS = 200000000ull;   // longest barrier wait: 2 s of the 100 MHz wall clock
+constexpr int PB_POINTS = 2;        // target points a thread takes at a time
+constexpr uint64_t PB_WAIT_TICKS = 200000000ull;   // longest wait for a position: 2 s of the 100 MHz wall clock
+constexpr unsigned long long PB_EMPTY = 0x7ff4dd5e9a3c7b11ull;
 
 struct PBArgs {
     Layout L;
     const int32_t *seg_nodes;
     const double *burgers, *normal;
     const uint8_t *pinned;
-    const double *sigma_app;   // [n_inst][6]
+    const double *sigma_dev;   // [n_inst][6], or null: sigma
+    Sig6 sigma;
     const double *volume;      // [n_inst]
-    const int32_t *csr_ptr, *csr_list;
-    const int32_t *wg;         // [4][n_wg]: instance, rank in it, the instance's G, its first workgroup
+    const int32_t *wg;         // [4][n_wg]: instance, rank in it, the instance's G, its first workgroup (BURST)
     int n_wg;
-    double *xa, *xb;           // positions: the caller's array and the second buffer [3][nn]
-    double *vel;               // [2][3][nn]
-    double *wpart;             // [n_wg][12]
-    unsigned *arrive;          // [n_wg][16] barrier arrival words (one per 64 bytes), zero at launch
+    const double *x;           // positions at the start
+    double *xbuf;              // [3][3][nn] published positions (BURST)
+    double *xend;              // [3][nn] final positions (BURST)
+    double *wpart;             // [n_wg][12] (BURST)
+    double *force, *vel;       // [3][nn], vel null: no glide (one evaluation)
     unsigned *flags;
-    double *rate_out;          // [n_inst][12], added to
     GaussRule g;
     double kr, nu, k2, inv_a, a, inv_mu, fscale, invB, dt;
     int n_steps;
 };
 
-// Barrier of the G workgroups of one instance (workgroups first ..
-// first + G - 1), the step-th since the launch: each workgroup publishes step
-// in its own arrival word (one per 64-byte line, after a release fence) and
-// waits, one thread per workgroup, until every word of the instance holds at
-// least step; then one acquire fence for the workgroup.  A wait longer than
-// PB_WAIT_TICKS raises FLAG_BARRIER and returns false (the caller then
-// leaves the kernel, and so, after their own wait, do the other workgroups).
-__device__ __forceinline__ bool pb_barrier(unsigned *arrive, int wg, int first, int G, unsigned step,
-                                           unsigned *flags)
+__device__ __forceinline__ double pb_load(const double *p)
 {
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        __threadfence();
-        __hip_atomic_store(arrive + 16 * wg, step, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
-    int ok = 1;
-    if ((int)threadIdx.x < G) {
-        const unsigned *f = arrive + 16 * (first + (int)threadIdx.x);
-        const uint64_t t0 = wall_clock64();
-        while (__hip_atomic_load(f, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < step) {
-            if (wall_clock64() - t0 > PB_WAIT_TICKS) {
-                atomicOr(flags, FLAG_BARRIER);
-                ok = 0;
-                break;
-            }
-            __builtin_amdgcn_s_sleep(1);
-        }
-    }
-    ok = __syncthreads_and(ok);
-    if (threadIdx.x == 0) __threadfence();
-    __syncthreads();
-    return ok != 0;
+    return __longlong_as_double((long long)__hip_atomic_load((const unsigned long long *)p, __ATOMIC_RELAXED,
+                                                             __HIP_MEMORY_SCOPE_AGENT));
+}
+__device__ __forceinline__ void pb_store(double *p, double v)
+{
+    __hip_atomic_store((unsigned long long *)p, (unsigned long long)__double_as_longlong(v), __ATOMIC_RELAXED,
+                       __HIP_MEMORY_SCOPE_AGENT);
 }
 
-__global__ __launch_bounds__(PB_THREADS) void k_burst_persistent(PBArgs A)
+// v plus the value of the lane that the DPP control pairs with this one.
+template <int CTRL>
+__device__ __forceinline__ double dpp_pair_sum(double v)
 {
-    __shared__ double s_rec[PB_MAX_SEGS][16];   // x1, t, L, b, c (units of a)
-    __shared__ double s_part[PB_ITEMS][3];
-    __shared__ double s_segF[PB_MAX_SEGS][6];   // end forces of the listed segments
-    __shared__ double s_wacc[12];
-    __shared__ int32_t s_list[PB_MAX_SEGS];     // the workgroup's segments (instance-local), index order
-    __shared__ int16_t s_loc[PB_MAX_SEGS];      // segment -> list position, -1: not listed
-    __shared__ int8_t s_sys[PB_MAX_SEGS];
-    __shared__ uint8_t s_own[PB_MAX_SEGS];      // listed segment starts at an owned node
-    __shared__ int s_nl;
-    const int tid = threadIdx.x, wg = blockIdx.x;
-    const int inst = A.wg[wg], w = A.wg[A.n_wg + wg], G = A.wg[2 * A.n_wg + wg], first = A.wg[3 * A.n_wg + wg];
-    const Layout &L = A.L;
-    const int64_t nn = L.nn, ns = L.ns;
-    const int64_t n0 = L.node_off[inst], nn_i = L.node_off[inst + 1] - n0;
-    const int64_t s0 = L.seg_off[inst], ns_i = L.seg_off[inst + 1] - s0;
-    const int64_t o_lo = n0 + nn_i * w / G, o_hi = n0 + nn_i * (w + 1) / G;   // owned nodes
-    const double invV = 1.0 / A.volume[inst];
-    unsigned step_no = 0;   // barriers passed
+    const long long u = __double_as_longlong(v);
+    const unsigned lo = (unsigned)__builtin_amdgcn_update_dpp(0, (int)(u & 0xffffffffll), CTRL, 0xf, 0xf, true);
+    const unsigned hi = (unsigned)__builtin_amdgcn_update_dpp(0, (int)(u >> 32), CTRL, 0xf, 0xf, true);
+    return v + __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
+}
 
-    // the list of segments incident to owned nodes, their slip systems
-    if (tid == 0) {
-        int nl = 0;
-        for (int64_t sl = 0; sl < ns_i; ++sl) {
-            int64_t g1, g2;
-            seg_ends(L, A.seg_nodes, s0 + sl, g1, g2);
-            const bool own1 = g1 >= o_lo && g1 < o_hi, own2 = g2 >= o_lo && g2 < o_hi;
-            s_loc[sl] = -1;
-            if (own1 || own2) {
-                s_loc[sl] = (int16_t)nl;
-                s_list[nl] = (int32_t)sl;
-                s_own[nl] = own1;
-                ++nl;
-            }
-        }
-        s_nl = nl;
-        for (int k = 0; k < 12; ++k) s_wacc[k] = 0.0;
-    }
-    for (int64_t sl = tid; sl < ns_i; sl += PB_THREADS) {
+// Sum over 32 consecutive lanes, in every one of them.
+__device__ __forceinline__ double sum32(double v)
+{
+    v = dpp_pair_sum<0xB1>(v);    // lanes 1 apart
+    v = dpp_pair_sum<0x4E>(v);    // 2 apart
+    v = dpp_pair_sum<0x141>(v);   // the other four of eight
+    v = dpp_pair_sum<0x140>(v);   // the other eight of sixteen
+    return v + __shfl_xor(v, 16);
+}
+
+template <bool BURST>
+__global__ __launch_bounds__(PB_THREADS) void k_small(PBArgs A)
+{
+    __shared__ double s_x[3][PB_MAX_SEGS];                     // node positions of the step
+    __shared__ double s_rec[10][PB_MAX_SEGS];                  // x1, t, L, b of every segment (units of a)
+    __shared__ double s_part[PB_THREADS * PB_POINTS * 3];      // per point and component, by source
+    __shared__ double s_con[PB_THREADS / 64 * PB_POINTS][2][3];   // force of a point at its segment's two nodes
+    __shared__ double s_segF[PB_MAX_SEGS][6];                  // end forces of the listed segments (several rounds)
+    __shared__ double s_app[PB_MAX_SEGS][3];                   // sigma_app b of the listed segments
+    __shared__ double s_nrm[PB_MAX_SEGS][6];                   // up to two distinct normals of an owned node
+    __shared__ double s_gs[DD_MAX_GAUSS], s_gw[DD_MAX_GAUSS];
+    __shared__ int16_t s_list[PB_MAX_SEGS];                    // the workgroup's segments (instance-local), index order
+    __shared__ int16_t s_n1[PB_MAX_SEGS], s_n2[PB_MAX_SEGS];   // nodes of every segment (instance-local)
+    __shared__ int s_ent[2 * PB_MAX_SEGS];                     // by owned node: segment << 16 | list position << 1 | end
+    __shared__ int16_t s_eptr[PB_MAX_SEGS + 1];
+    __shared__ int8_t s_cnt[PB_MAX_SEGS];                      // distinct normals of an owned node (1 or 2), 0: fixed
+    __shared__ uint8_t s_bad[PB_MAX_SEGS];
+    __shared__ int s_nl;
+    // velocities of the owned nodes, in s_part between the sums of one step and the stresses of the next
+    double(*s_v)[PB_MAX_SEGS] = reinterpret_cast<double(*)[PB_MAX_SEGS]>(s_part);
+    const int tid = threadIdx.x, wg = blockIdx.x;
+    const Layout &L = A.L;
+    const int inst = BURST ? A.wg[wg] : 0, w = BURST ? A.wg[A.n_wg + wg] : wg, G = BURST ? A.wg[2 * A.n_wg + wg] : A.n_wg;
+    const int64_t nn = L.nn, ns = L.ns;
+    const int64_t n0 = node_begin(L, inst), s0 = seg_begin(L, inst);
+    const int nn_i = (int)node_count(L, inst), ns_i = (int)(L.seg_off ? L.seg_off[inst + 1] - s0 : ns);
+    const int o_lo = (int)((int64_t)nn_i * w / G), o_hi = (int)((int64_t)nn_i * (w + 1) / G), n_own = o_hi - o_lo;
+    const int Q = A.g.n;
+
+    // the segments' nodes and Burgers vectors
+    for (int sl = tid; sl < ns_i; sl += PB_THREADS) {
         const int64_t sg = s0 + sl;
         int64_t g1, g2;
-        unsigned fl = seg_ends(L, A.seg_nodes, sg, g1, g2) ? 0u : FLAG_BAD_INDEX;
-        const double b[3] = {A.burgers[sg], A.burgers[ns + sg], A.burgers[2 * ns + sg]};
+        const bool ok = seg_ends(L, A.seg_nodes, sg, g1, g2);
+        unsigned fl = ok ? 0u : FLAG_BAD_INDEX;
         const double nv[3] = {A.normal[sg], A.normal[ns + sg], A.normal[2 * ns + sg]};
         if (!(fabs(nv[0] * nv[0] + nv[1] * nv[1] + nv[2] * nv[2] - 1.0) <= 2e-6)) fl |= FLAG_BAD_NORMAL;
-        s_sys[sl] = (int8_t)seg_system(b, nv);
+        s_n1[sl] = (int16_t)(g1 - n0);
+        s_n2[sl] = (int16_t)(g2 - n0);
+        s_bad[sl] = !ok;
+        for (int c = 0; c < 3; ++c) s_rec[7 + c][sl] = A.burgers[c * ns + sg] * A.inv_a;
         if (fl) atomicOr(A.flags, fl);
+    }
+    if (tid < DD_MAX_GAUSS) {
+        s_gs[tid] = A.g.s[tid];
+        s_gw[tid] = A.g.w[tid];
+    }
+    __syncthreads();
+    // the list of segments incident to owned nodes, by the first wavefront
+    if (tid < 64) {
+        int nl = 0;
+        for (int b = 0; b < ns_i; b += 64) {
+            const int sl = b + tid;
+            const bool mine = sl < ns_i && !s_bad[sl] &&
+                              ((s_n1[sl] >= o_lo && s_n1[sl] < o_hi) || (s_n2[sl] >= o_lo && s_n2[sl] < o_hi));
+            const uint64_t m = __builtin_amdgcn_ballot_w64(mine);
+            if (mine) s_list[nl + __builtin_popcountll(m & ((1ull << tid) - 1))] = (int16_t)sl;
+            nl += __builtin_popcountll(m);
+        }
+        if (tid == 0) s_nl = nl;
     }
     __syncthreads();
     const int nl = s_nl;
-    const int Q = A.g.n;
-    const int nch = (int)((ns_i + PB_CHUNK - 1) / PB_CHUNK);
-    const int per_batch = nch > 0 ? (PB_ITEMS / (Q * nch) > 0 ? PB_ITEMS / (Q * nch) : 1) : 1;
-    double S6[6];
-    for (int k = 0; k < 6; ++k) S6[k] = A.sigma_app[6 * inst + k] * A.inv_mu;
-
-    for (int k = 0; k <= A.n_steps; ++k) {
-        const double *xc = (k & 1) ? A.xb : A.xa;   // positions at the start of step k
-        if (k > 0) {
-            if (!pb_barrier(A.arrive, wg, first, G, ++step_no, A.flags)) return;
-            // slip-rate sums of step k - 1 (its records are still in LDS)
-            const double *vk = A.vel + (int64_t)((k - 1) & 1) * 3 * nn;
-            for (int l = tid; l < nl; l += PB_THREADS) {
-                s_part[l][0] = 0.0;
-                const int sl = s_list[l], al = s_sys[sl];
-                if (!s_own[l] || al < 0) continue;
-                int64_t g1, g2;
-                seg_ends(L, A.seg_nodes, s0 + sl, g1, g2);
+    // per owned node its (segment, end) entries in index order, and its distinct normals
+    for (int o = tid; o < n_own; o += PB_THREADS) {
+        int c = 0;
+        for (int l = 0; l < nl; ++l) c += (s_n1[s_list[l]] == o_lo + o) + (s_n2[s_list[l]] == o_lo + o);
+        s_eptr[o + 1] = (int16_t)c;
+    }
+    // per listed segment (thread = list position) sigma_app b, and its part of the slip rates
+    int al = -1;
+    double rn0 = 0, rn1 = 0, rn2 = 0, rbm = 0, rate = 0;
+    if (tid < nl) {
+        const int sl = s_list[tid];
+        const double b[3] = {s_rec[7][sl], s_rec[8][sl], s_rec[9][sl]};
+        double S[6];
+        for (int c = 0; c < 6; ++c) S[c] = (A.sigma_dev ? A.sigma_dev[6 * inst + c] : A.sigma.v[c]) * A.inv_mu;
+        s_app[tid][0] = S[0] * b[0] + S[5] * b[1] + S[4] * b[2];
+        s_app[tid][1] = S[5] * b[0] + S[1] * b[1] + S[3] * b[2];
+        s_app[tid][2] = S[4] * b[0] + S[3] * b[1] + S[2] * b[2];
+        if (BURST) {
+            const int64_t sg = s0 + sl;
+            const double bc[3] = {A.burgers[sg], A.burgers[ns + sg], A.burgers[2 * ns + sg]};
+            const double nv[3] = {A.normal[sg], A.normal[ns + sg], A.normal[2 * ns + sg]};
+            al = seg_system(bc, nv);
+            if (al >= 0) {
                 double n[3], m[3];
                 fcc(al, n, m);
-                const double *r = s_rec[sl];
-                s_part[l][0] = seg_rate(r + 3, r + 7, r[6] * A.a, vk, nn, g1, g2, n, m, A.a, invV);
+                rn0 = n[0];
+                rn1 = n[1];
+                rn2 = n[2];
+                rbm = (b[0] * m[0] + b[1] * m[1] + b[2] * m[2]) * A.a * A.a / A.volume[inst];
             }
-            __syncthreads();
-            if (tid == 0)
-                for (int l = 0; l < nl; ++l) {
-                    const int al = s_sys[s_list[l]];
-                    if (s_own[l] && al >= 0) s_wacc[al] += s_part[l][0];
-                }
-            __syncthreads();
-        }
-        if (k == A.n_steps) break;
-        // records of step k
-        for (int64_t sl = tid; sl < ns_i; sl += PB_THREADS) {
-            int64_t g1, g2;
-            seg_ends(L, A.seg_nodes, s0 + sl, g1, g2);
-            const double Ls = seg_record(xc, nn, g1, g2, A.burgers, ns, s0 + sl, A.inv_a, s_rec[sl]);
-            if (!(Ls > 0.0) || !isfinite(Ls)) atomicOr(A.flags, FLAG_ZERO_LENGTH);
-        }
-        __syncthreads();
-        // Gauss-point stresses of the listed segments, in batches of whole segments
-        for (int l0 = 0; l0 < nl; l0 += per_batch) {
-            const int l1 = l0 + per_batch < nl ? l0 + per_batch : nl;
-            const int items = (l1 - l0) * Q * nch;
-            for (int it = tid; it < items; it += PB_THREADS) {
-                const int c = it % nch, tq = it / nch;
-                const int sj = s_list[l0 + tq / Q], q = tq % Q;
-                const double *rj = s_rec[sj];
-                double sq = A.g.s[0];
-                for (int i = 1; i < DD_MAX_GAUSS; ++i)
-                    if (i == q) sq = A.g.s[i];
-                const double xq0 = rj[0] + sq * rj[6] * rj[3];
-                const double xq1 = rj[1] + sq * rj[6] * rj[4];
-                const double xq2 = rj[2] + sq * rj[6] * rj[5];
-                double a0 = 0.0, a1 = 0.0, a2 = 0.0, ak = 0.0;
-                const int c1 = (c + 1) * PB_CHUNK < ns_i ? (c + 1) * PB_CHUNK : (int)ns_i;
-                for (int src = c * PB_CHUNK; src < c1; ++src) {
-                    if (src == sj) continue;
-                    const double *d = s_rec[src];
-                    const double R0 = xq0 - d[0], R1 = xq1 - d[1], R2 = xq2 - d[2];
-                    const double r1 = rsqrt64(fma(R2, R2, fma(R1, R1, fma(R0, R0, 1.0))));
-                    double r2, r2c;
-                    pair_acc_f64(xq0, xq1, xq2, rj[7], rj[8], rj[9], d[0], d[1], d[2], d[3], d[4], d[5], d[6],
-                                 d[7], d[8], d[9], d[10], d[11], d[12], A.kr, A.nu, r1, r1 * r1 * r1, r2, r2c, a0,
-                                 a1, a2, ak);
-                }
-                s_part[it][0] = A.k2 * fma(ak, rj[7], a0);
-                s_part[it][1] = A.k2 * fma(ak, rj[8], a1);
-                s_part[it][2] = A.k2 * fma(ak, rj[9], a2);
-            }
-            __syncthreads();
-            // end forces: per listed segment, Gauss points in order, chunks in order
-            for (int l = l0 + tid; l < l1; l += PB_THREADS) {
-                const double *rj = s_rec[s_list[l]];
-                const double t0 = rj[3], t1 = rj[4], t2 = rj[5], Ls = rj[6];
-                const double b0 = rj[7], b1 = rj[8], b2 = rj[9];
-                const double ab0 = S6[0] * b0 + S6[5] * b1 + S6[4] * b2;
-                const double ab1 = S6[5] * b0 + S6[1] * b1 + S6[3] * b2;
-                const double ab2 = S6[4] * b0 + S6[3] * b1 + S6[2] * b2;
-                double F1[3] = {0, 0, 0}, F2[3] = {0, 0, 0};
-                for (int q = 0; q < Q; ++q) {
-                    const int base = ((l - l0) * Q + q) * nch;
-                    double sa = 0, sb = 0, sc = 0;
-                    for (int c = 0; c < nch; ++c) {
-                        sa += s_part[base + c][0];
-                        sb += s_part[base + c][1];
-                        sc += s_part[base + c][2];
-                    }
-                    sa += ab0;
-                    sb += ab1;
-                    sc += ab2;
-                    const double f0 = sb * t2 - sc * t1, f1 = sc * t0 - sa * t2, f2 = sa * t1 - sb * t0;
-                    const double w1 = Ls * A.g.w[q] * (1.0 - A.g.s[q]), w2 = Ls * A.g.w[q] * A.g.s[q];
-                    F1[0] += w1 * f0; F1[1] += w1 * f1; F1[2] += w1 * f2;
-                    F2[0] += w2 * f0; F2[1] += w2 * f1; F2[2] += w2 * f2;
-                }
-                for (int c = 0; c < 3; ++c) {
-                    s_segF[l][c] = F1[c] * A.fscale;
-                    s_segF[l][3 + c] = F2[c] * A.fscale;
-                }
-            }
-            __syncthreads();
-        }
-        // owned nodes: nodal force in node-list order, glide step into the other buffers
-        double *xn = (k & 1) ? A.xa : A.xb;
-        double *vn = A.vel + (int64_t)(k & 1) * 3 * nn;
-        for (int64_t n = o_lo + tid; n < o_hi; n += PB_THREADS) {
-            double F0 = 0, F1 = 0, F2 = 0, ell = 0.0, nrm[3][3];
-            int cnt = 0;
-            for (int32_t e = A.csr_ptr[n]; e < A.csr_ptr[n + 1]; ++e) {
-                const int32_t v = A.csr_list[e];
-                const int64_t sg = v >> 1;
-                const int end = v & 1, l = s_loc[sg - s0];
-                F0 += s_segF[l][3 * end];
-                F1 += s_segF[l][3 * end + 1];
-                F2 += s_segF[l][3 * end + 2];
-                ell += 0.5 * (s_rec[sg - s0][6] * A.a);
-                add_normal(A.normal[sg], A.normal[ns + sg], A.normal[2 * ns + sg], nrm, cnt);
-            }
-            double v0 = 0, v1 = 0, v2 = 0;
-            const bool fixed = (A.pinned && A.pinned[n]) || !(ell > 0.0) || cnt == 0 || cnt >= 3;
-            if (!fixed) glide_velocity(F0, F1, F2, ell, A.invB, nrm, cnt, v0, v1, v2);
-            vn[n] = v0;
-            vn[nn + n] = v1;
-            vn[2 * nn + n] = v2;
-            xn[n] = xc[n] + v0 * A.dt;
-            xn[nn + n] = xc[nn + n] + v1 * A.dt;
-            xn[2 * nn + n] = xc[2 * nn + n] + v2 * A.dt;
         }
     }
-    // an odd number of steps leaves the positions in the second buffer: owned
-    // nodes back to the caller's array (every read of it ended at the last barrier)
-    if (A.n_steps & 1)
-        for (int64_t n = o_lo + tid; n < o_hi; n += PB_THREADS)
-            for (int c = 0; c < 3; ++c) A.xa[c * nn + n] = A.xb[c * nn + n];
-    if (tid < 12) A.wpart[12 * (int64_t)wg + tid] = s_wacc[tid];
-    if (!pb_barrier(A.arrive, wg, first, G, ++step_no, A.flags)) return;
-    if (w == 0 && tid < 12) {
+    __syncthreads();
+    if (tid == 0) {
+        s_eptr[0] = 0;
+        for (int o = 0; o < n_own; ++o) s_eptr[o + 1] += s_eptr[o];
+    }
+    __syncthreads();
+    for (int o = tid; o < n_own; o += PB_THREADS) {
+        int e = s_eptr[o], cnt = 0;
+        double nrm[3][3];
+        for (int l = 0; l < nl; ++l) {
+            const int sl = s_list[l];
+            for (int end = 0; end < 2; ++end)
+                if ((end ? s_n2 : s_n1)[sl] == o_lo + o) {
+                    s_ent[e++] = sl << 16 | l << 1 | end;
+                    add_normal(A.normal[s0 + sl], A.normal[ns + s0 + sl], A.normal[2 * ns + s0 + sl], nrm, cnt);
+                }
+        }
+        const bool fixed = cnt == 0 || cnt >= 3 || (A.pinned && A.pinned[n0 + o_lo + o]);
+        s_cnt[o] = fixed ? 0 : (int8_t)cnt;
+        for (int c = 0; c < 6; ++c) s_nrm[o][c] = c < 3 * cnt && cnt < 3 ? nrm[c / 3][c % 3] : 0.0;
+    }
+    __syncthreads();
+
+    // a thread's source, and which of the copies of the sources it belongs to
+    const int P = ns_i > 0 ? (ns_i + 63) & ~63 : 64;
+    const int copies = PB_THREADS / P, copy = tid / P, src = tid - copy * P;
+    const bool has_src = copy < copies && src < ns_i;
+    const int per_round = copies * PB_POINTS, n_points = nl * Q;
+    const bool single = n_points <= per_round;   // one round: a node's forces come straight from the sums
+    const double b0 = has_src ? s_rec[7][src] : 0.0, b1 = has_src ? s_rec[8][src] : 0.0, b2 = has_src ? s_rec[9][src] : 0.0;
+    const int i1 = has_src ? s_n1[src] : 0, i2 = has_src ? s_n2[src] : 0;
+    // its target points of a round (the last point again where there are fewer)
+    int tj[PB_POINTS];
+    double ts[PB_POINTS], tb[PB_POINTS][3];
+    auto target = [&](int r0) {
+#pragma unroll
+        for (int i = 0; i < PB_POINTS; ++i) {
+            const int pt = min(r0 + copy * PB_POINTS + i, n_points - 1), l = pt / Q;
+            tj[i] = s_list[l];
+            ts[i] = s_gs[pt - l * Q];
+            for (int c = 0; c < 3; ++c) tb[i][c] = s_rec[7 + c][tj[i]];
+        }
+    };
+    if (has_src && n_points > 0) target(0);
+    // the thread's node: its force and glide are in the last wavefront's hands, idle
+    // while the sums are formed, when it owns few
+    const int own = tid - (n_own <= 64 ? PB_THREADS - 64 : 0);
+    const bool has_node = own >= 0 && own < n_own;
+    const int ne = has_node ? s_eptr[own + 1] - s_eptr[own] : 0, e0 = has_node ? s_eptr[own] : 0;
+    const int en0 = ne > 0 ? s_ent[e0] : 0, en1 = ne > 1 ? s_ent[e0 + 1] : en0;
+    const int n_normals = has_node ? s_cnt[own] : 0;
+    double nr[6] = {0, 0, 0, 0, 0, 0}, sc = 0.0;
+    if (has_node)
+        for (int c = 0; c < 6; ++c) nr[c] = s_nrm[own][c];
+    // the point whose sums this thread shares: its segment, sigma_app b, Gauss point and weight
+    int ps = 0;
+    double papp[3] = {0, 0, 0}, pg = 0, pw = 0;
+    auto point_of = [&](int pt) {
+        const int l = pt / Q;
+        ps = s_list[l];
+        for (int c = 0; c < 3; ++c) papp[c] = s_app[l][c];
+        pg = s_gs[pt - l * Q];
+        pw = s_gw[pt - l * Q];
+    };
+    if (tid / 32 < n_points) point_of(tid / 32);
+    // a listed segment's owned nodes (-1: not owned) and its direction and length in the step (slip rates)
+    int ro1 = -1, ro2 = -1;
+    double ru0 = 0, ru1 = 0, ru2 = 0, rL = 0;
+    if (al >= 0) {
+        const int sl = s_list[tid], a1 = s_n1[sl] - o_lo, a2 = s_n2[sl] - o_lo;
+        ro1 = a1 >= 0 && a1 < n_own ? a1 : -1;
+        ro2 = a2 >= 0 && a2 < n_own ? a2 : -1;
+    }
+
+    const double kr = A.kr, nu = A.nu, k2 = A.k2, inv_a = A.inv_a, fscale = A.fscale, dt = A.dt;
+    // slip rates: a listed segment's owned nodes carry half of its mean velocity
+    auto add_rate = [&]() {
+        if (al < 0) return;
+        double vb0 = 0, vb1 = 0, vb2 = 0;
+        if (ro1 >= 0) {
+            vb0 += 0.5 * s_v[0][ro1];
+            vb1 += 0.5 * s_v[1][ro1];
+            vb2 += 0.5 * s_v[2][ro1];
+        }
+        if (ro2 >= 0) {
+            vb0 += 0.5 * s_v[0][ro2];
+            vb1 += 0.5 * s_v[1][ro2];
+            vb2 += 0.5 * s_v[2][ro2];
+        }
+        const double q0 = ru1 * vb2 - ru2 * vb1, q1 = ru2 * vb0 - ru0 * vb2, q2 = ru0 * vb1 - ru1 * vb0;
+        rate += rbm * rL * (q0 * rn0 + q1 * rn1 + q2 * rn2);
+    };
+
+    for (int k = 0; k < (BURST ? A.n_steps : 1); ++k) {
+        // positions of the step; the first look at the published ones is under way
+        // while the slip rates of the step before are added
+        int ok = 1;
+        double v[3] = {0, 0, 0};
+        const double *xk = A.x + n0 + tid;
+        if (tid < nn_i) {
+            if (BURST && k > 0) xk = A.xbuf + (int64_t)(k % 3) * 3 * nn + n0 + tid;
+            // (a look at once would come too early, and the many looks slow the
+            // stores down: 6.7 us a step without the pause, 5.6 with it)
+            if (BURST && k > 0) __builtin_amdgcn_s_sleep(8);
+            for (int c = 0; c < 3; ++c) v[c] = BURST && k > 0 ? pb_load(xk + c * nn) : xk[c * nn];
+        }
+        if (BURST && k > 0) add_rate();
+        if (tid < nn_i) {
+            if (BURST && k > 0) {
+                const uint64_t t0 = wall_clock64();
+                for (;;) {
+                    bool all = true;
+                    for (int c = 0; c < 3; ++c) all = all && (unsigned long long)__double_as_longlong(v[c]) != PB_EMPTY;
+                    if (all) break;
+                    if (wall_clock64() - t0 > PB_WAIT_TICKS) {
+                        atomicOr(A.flags, FLAG_BARRIER);
+                        ok = 0;
+                        break;
+                    }
+                    for (int c = 0; c < 3; ++c) v[c] = pb_load(xk + c * nn);
+                }
+            }
+            for (int c = 0; c < 3; ++c) s_x[c][tid] = v[c];
+        }
+        if (BURST) {
+            if (!__syncthreads_and(ok)) return;
+            if (k > 0 && has_node) {
+                double *q = A.xbuf + (int64_t)((k + 2) % 3) * 3 * nn + n0 + o_lo + own;
+                for (int c = 0; c < 3; ++c) pb_store(q + c * nn, __longlong_as_double((long long)PB_EMPTY));
+            }
+        } else {
+            __syncthreads();
+        }
+        // records
+        double p0 = 0, p1 = 0, p2 = 0, t0 = 0, t1 = 0, t2 = 0, Ls = 0, c0 = 0, c1 = 0, c2 = 0;
+        if (has_src) {
+            p0 = s_x[0][i1] * inv_a;
+            p1 = s_x[1][i1] * inv_a;
+            p2 = s_x[2][i1] * inv_a;
+            const double d0 = s_x[0][i2] * inv_a - p0, d1 = s_x[1][i2] * inv_a - p1, d2 = s_x[2][i2] * inv_a - p2;
+            const double LL = d0 * d0 + d1 * d1 + d2 * d2, iL = rsqrt64(LL);
+            Ls = LL * iL;
+            t0 = d0 * iL;
+            t1 = d1 * iL;
+            t2 = d2 * iL;
+            c0 = b1 * t2 - b2 * t1;
+            c1 = b2 * t0 - b0 * t2;
+            c2 = b0 * t1 - b1 * t0;
+            if (copy == 0) {
+                s_rec[0][src] = p0; s_rec[1][src] = p1; s_rec[2][src] = p2;
+                s_rec[3][src] = t0; s_rec[4][src] = t1; s_rec[5][src] = t2;
+                s_rec[6][src] = Ls;
+                if (!(Ls > 0.0) || !isfinite(Ls)) atomicOr(A.flags, FLAG_ZERO_LENGTH);
+            }
+        }
+        __syncthreads();
+        if (BURST && al >= 0) {
+            const int sl = s_list[tid];
+            ru0 = s_rec[3][sl];
+            ru1 = s_rec[4][sl];
+            ru2 = s_rec[5][sl];
+            rL = s_rec[6][sl];
+        }
+        for (int r0 = 0; r0 < n_points; r0 += per_round) {
+            const int np = min(per_round, n_points - r0);
+            if (copy < copies) {
+                double v[PB_POINTS][3] = {};   // (0 for the threads that pad the sources to P)
+                if (has_src && !single) target(r0);
+                if (has_src)
+#pragma unroll
+                for (int i = 0; i < PB_POINTS; ++i) {
+                    const int sj = tj[i];
+                    const double lj = ts[i] * s_rec[6][sj];
+                    const double x0 = fma(lj, s_rec[3][sj], s_rec[0][sj]), x1 = fma(lj, s_rec[4][sj], s_rec[1][sj]),
+                                 x2 = fma(lj, s_rec[5][sj], s_rec[2][sj]);
+                    const double bj0 = tb[i][0], bj1 = tb[i][1], bj2 = tb[i][2];
+                    const double R0 = x0 - p0, R1 = x1 - p1, R2 = x2 - p2;
+                    const double r1 = rsqrt64(fma(R2, R2, fma(R1, R1, fma(R0, R0, 1.0))));
+                    double r2, r2c, a0 = 0.0, a1 = 0.0, a2 = 0.0, ak = 0.0;
+                    pair_acc_f64(x0, x1, x2, bj0, bj1, bj2, p0, p1, p2, t0, t1, t2, Ls, b0, b1, b2, c0, c1, c2, kr, nu, r1, r1 * r1 * r1, r2, r2c, a0, a1, a2, ak);
+                    const bool self = src == sj;
+                    v[i][0] = self ? 0.0 : fma(ak, bj0, a0);
+                    v[i][1] = self ? 0.0 : fma(ak, bj1, a1);
+                    v[i][2] = self ? 0.0 : fma(ak, bj2, a2);
+                }
+#pragma unroll
+                for (int i = 0; i < PB_POINTS; ++i)
+                    if (copy * PB_POINTS + i < np)
+#pragma unroll
+                        for (int c = 0; c < 3; ++c) s_part[(3 * (copy * PB_POINTS + i) + c) * P + src] = v[i][c];
+            }
+            __syncthreads();
+            // a point per 32 lanes: its three sums over the sources, eight loads in
+            // flight each, then its force at its segment's nodes
+            {
+                const int pt = tid / 32;
+                if (pt < np) {
+                    if (!single) point_of(r0 + pt);
+                    const double *q = s_part + 3 * pt * P;
+                    double v[3] = {0.0, 0.0, 0.0};
+                    int m0 = tid & 31;
+                    for (; m0 + 256 <= P + 31; m0 += 256) {
+                        double u[3][8];
+#pragma unroll
+                        for (int c = 0; c < 3; ++c)
+#pragma unroll
+                            for (int i = 0; i < 8; ++i) u[c][i] = q[c * P + m0 + 32 * i];
+#pragma unroll
+                        for (int i = 0; i < 8; ++i)
+#pragma unroll
+                            for (int c = 0; c < 3; ++c) v[c] += u[c][i];
+                    }
+                    for (; m0 < P; m0 += 64) {
+                        double u[3][2];
+#pragma unroll
+                        for (int c = 0; c < 3; ++c)
+#pragma unroll
+                            for (int i = 0; i < 2; ++i) u[c][i] = q[c * P + m0 + 32 * i];
+#pragma unroll
+                        for (int i = 0; i < 2; ++i)
+#pragma unroll
+                            for (int c = 0; c < 3; ++c) v[c] += u[c][i];
+                    }
+                    const double u0 = s_rec[3][ps], u1 = s_rec[4][ps], u2 = s_rec[5][ps], Lp = s_rec[6][ps];
+                    for (int c = 0; c < 3; ++c) v[c] = fma(k2, sum32(v[c]), papp[c]);
+                    const double f0 = v[1] * u2 - v[2] * u1, f1 = v[2] * u0 - v[0] * u2, f2 = v[0] * u1 - v[1] * u0;
+                    if ((tid & 31) < 2) {
+                        const int end = tid & 31;
+                        const double wt = Lp * pw * (end ? pg : 1.0 - pg);
+                        s_con[pt][end][0] = wt * f0;
+                        s_con[pt][end][1] = wt * f1;
+                        s_con[pt][end][2] = wt * f2;
+                    }
+                }
+            }
+            // meanwhile: 1 / (B ell) of the owned nodes
+            if (r0 == 0 && n_normals && (BURST || A.vel)) {
+                double ell = 0.5 * (s_rec[6][en0 >> 16] * A.a);
+                if (ne > 1) ell += 0.5 * (s_rec[6][en1 >> 16] * A.a);
+                for (int e = 2; e < ne; ++e) ell += 0.5 * (s_rec[6][s_ent[e0 + e] >> 16] * A.a);
+                sc = ell > 0.0 ? A.invB / ell : 0.0;
+            }
+            __syncthreads();
+            if (single) break;
+            // end forces of the segments whose points these are
+            const int l = r0 / Q + tid;
+            if (l < nl && l * Q < r0 + np) {
+                const int q0 = max(0, r0 - l * Q), q1 = min(Q, r0 + np - l * Q);
+                for (int c = 0; c < 6; ++c) {
+                    double F = q0 ? s_segF[l][c] : 0.0;
+                    for (int q = q0; q < q1; ++q) F += s_con[l * Q + q - r0][c / 3][c % 3];
+                    s_segF[l][c] = F;
+                }
+            }
+        }
+        if (!single) __syncthreads();
+        // owned nodes: nodal force in node-list order, glide velocity, new position
+        if (has_node) {
+            const int n = o_lo + own;
+            double F0 = 0, F1 = 0, F2 = 0, v0 = 0, v1 = 0, v2 = 0;
+            const double xo[3] = {s_x[0][n], s_x[1][n], s_x[2][n]};
+            for (int e = 0; e < ne; ++e) {
+                const int en = e == 0 ? en0 : (e == 1 ? en1 : s_ent[e0 + e]), l = (en >> 1) & (PB_MAX_SEGS - 1),
+                          end = en & 1;
+                double F[3] = {0.0, 0.0, 0.0};
+                if (single) {
+                    // (the clamped point of an odd Q is read, not added)
+                    for (int q = 0; q < Q; q += 2) {
+                        const double *u = s_con[l * Q + q][end], *w = s_con[l * Q + min(q + 1, Q - 1)][end];
+                        const double ua = u[0], ub = u[1], uc = u[2], wa = w[0], wb = w[1], wc = w[2];
+                        F[0] += ua;
+                        F[1] += ub;
+                        F[2] += uc;
+                        F[0] = q + 1 < Q ? F[0] + wa : F[0];
+                        F[1] = q + 1 < Q ? F[1] + wb : F[1];
+                        F[2] = q + 1 < Q ? F[2] + wc : F[2];
+                    }
+                } else {
+                    for (int c = 0; c < 3; ++c) F[c] = s_segF[l][3 * end + c];
+                }
+                F0 += F[0];
+                F1 += F[1];
+                F2 += F[2];
+            }
+            F0 *= fscale;
+            F1 *= fscale;
+            F2 *= fscale;
+            if (!BURST) {
+                A.force[n] = F0;
+                A.force[nn + n] = F1;
+                A.force[2 * nn + n] = F2;
+            }
+            if (sc != 0.0) {
+                v0 = F0 * sc;
+                v1 = F1 * sc;
+                v2 = F2 * sc;
+                if (n_normals == 1) {
+                    const double vn = v0 * nr[0] + v1 * nr[1] + v2 * nr[2];
+                    v0 -= vn * nr[0];
+                    v1 -= vn * nr[1];
+                    v2 -= vn * nr[2];
+                } else {
+                    const double nrm[3][3] = {{nr[0], nr[1], nr[2]}, {nr[3], nr[4], nr[5]}, {0, 0, 0}};
+                    glide_velocity(F0, F1, F2, 1.0, sc, nrm, 2, v0, v1, v2);
+                }
+            }
+            if (BURST) {
+                const double x0 = xo[0] + v0 * dt, x1 = xo[1] + v1 * dt, x2 = xo[2] + v2 * dt;
+                if (k + 1 < A.n_steps) {
+                    // the emptied words of this step have left (see above)
+                    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+                    double *q = A.xbuf + (int64_t)((k + 1) % 3) * 3 * nn + n0 + n;
+                    pb_store(q, x0);
+                    pb_store(q + nn, x1);
+                    pb_store(q + 2 * nn, x2);
+                } else {
+                    double *q = A.xend + n0 + n;
+                    q[0] = x0;
+                    q[nn] = x1;
+                    q[2 * nn] = x2;
+                }
+                s_v[0][own] = v0;
+                s_v[1][own] = v1;
+                s_v[2][own] = v2;
+            } else if (A.vel) {
+                A.vel[n] = v0;
+                A.vel[nn + n] = v1;
+                A.vel[2 * nn + n] = v2;
+            }
+        }
+        if (BURST) __syncthreads();
+    }
+    if (BURST) {
+        add_rate();   // of the last step
+        // per slip system in list order
+        __syncthreads();
+        if (tid < nl) {
+            s_part[tid] = rate;
+            s_ent[tid] = al;
+        }
+        __syncthreads();
+        if (tid < 12) {
+            double sum = 0.0;
+            for (int l = 0; l < nl; ++l)
+                if (s_ent[l] == tid) sum += s_part[l];
+            A.wpart[12 * (int64_t)wg + tid] = sum;
+        }
+    }
+}
+
+// Buffers of unpublished positions before a burst.
+__global__ void k_pb_empty(double *p, int64_t n)
+{
+    const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+    if (i < n) p[i] = __longlong_as_double((long long)PB_EMPTY);
+}
+
+// After the last step: positions to the caller's array, and per instance the
+// slip-rate sums of its workgroups, in order, over the number of steps.
+__global__ void k_pb_finish(const int32_t *wg, int n_wg, int n_inst, const double *wpart, double inv_steps,
+                            double *rate_out, int64_t n3, const double *xend, double *x)
+{
+    const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+    if (i < n3) x[i] = xend[i];
+    if (i < 12 * (int64_t)n_wg && wg[n_wg + i / 12] == 0) {
+        const int64_t first = i / 12, al = i % 12;
         double sum = 0.0;
-        for (int v = 0; v < G; ++v) sum += A.wpart[12 * (int64_t)(first + v) + tid];
-        A.rate_out[12 * (int64_t)inst + tid] += sum;
+        for (int v = 0; v < wg[2 * n_wg + first]; ++v) sum += wpart[12 * (first + v) + al];
+        rate_out[12 * (int64_t)wg[first] + al] = sum * inv_steps;
     }
 }
 
@@ -1574,6 +1862,8 @@ PlanKey g_plan_key;   // guarded by the single-caller-per-device rule
 int g_plan_dev = -1;
 int64_t g_plan_items = 0;
 int64_t g_plan_chunk = 0;
+// what dd_last_plan reports
+int64_t g_last_chunk = 0, g_last_items = 0;
 int g_last_variant = 0;
 
 int setup(Workspace *ws, hipStream_t st, const std::vector<int64_t> &seg_off_h, int64_t nn,
@@ -1644,6 +1934,8 @@ int setup(Workspace *ws, hipStream_t st, const std::vector<int64_t> &seg_off_h, 
     C.L.tile_begin = n_inst > 1 || active ? (const int64_t *)ws->ptr[WS_OFFS] : nullptr;
     C.n_items = g_plan_items;
     C.range = g_plan_chunk;
+    g_last_chunk = g_plan_chunk;
+    g_last_items = g_plan_items;
     if ((rc = ensure(ws, WS_PARTIAL, sizeof(double) * 3 * TILE * std::max<int64_t>(C.n_items, 1), &p)))
         return rc;
     C.partial = (double *)p;
@@ -2144,6 +2436,62 @@ int presize_near(ForceCtx &C, Workspace *ws, const double *x, const int32_t *seg
     return size_near_pairs(C, ws, x, seg_nodes, 2.0, 8, st);
 }
 
+// ---------------------------------------------------------- small volumes --
+// Whether one FP64 force evaluation of a volume goes to k_small: a volume that
+// fits, and neither a fixed work split nor event timing of the all-pairs kernel
+// asked for (those are about the general path's kernels).  At 256 segments and
+// 2 points dd_step takes two launches instead of ten.
+bool small_volume(int64_t nn, int64_t ns, int precision, double eta)
+{
+    return ns > 0 && ns <= PB_MAX_SEGS && nn <= PB_MAX_SEGS && precision == DD_FP64 && eta == 0.0 &&
+           g_forced_choice.load() < 0 && !timing_on();
+}
+
+void small_args(PBArgs &A, const dd_material *m, int n_gauss)
+{
+    const double k1 = 1.0 / (8.0 * M_PI);
+    A.k2 = 1.0 / (4.0 * M_PI * (1.0 - m->nu));
+    A.g = gauss_rule(n_gauss);
+    A.kr = k1 / A.k2;
+    A.nu = 1.0 - 2.0 * A.kr;
+    A.inv_a = 1.0 / m->a;
+    A.a = m->a;
+    A.inv_mu = 1.0 / m->mu;
+    A.fscale = m->mu * m->a * m->a;
+}
+
+// One force evaluation (force [3][nn]), with the glide velocities if vel is not
+// null, by workgroups of one node each.
+void launch_small(Workspace *ws, int64_t nn, int64_t ns, const double *x, const int32_t *seg_nodes, const double *burgers,
+                  const double *normal, const uint8_t *pinned, const Sig6 &sigma, const dd_material *m, int n_gauss,
+                  double invB, double *force, double *vel, hipStream_t st)
+{
+    PBArgs A{};
+    small_args(A, m, n_gauss);
+    A.L.nn = nn;
+    A.L.ns = ns;
+    A.seg_nodes = seg_nodes;
+    A.burgers = burgers;
+    A.normal = normal;
+    A.pinned = pinned;
+    A.sigma = sigma;
+    A.n_wg = (int)nn;
+    A.x = x;
+    A.force = force;
+    A.vel = vel;
+    A.flags = ws->flags_dev;
+    A.invB = invB;
+    hipLaunchKernelGGL(k_small<false>, dim3((unsigned)nn), dim3(PB_THREADS), 0, st, A);
+}
+
+// (for dd_last_plan: every workgroup takes all sources)
+void note_small_plan(int64_t nn, int64_t ns)
+{
+    g_last_chunk = ns;
+    g_last_items = nn;
+    g_last_variant = 0;
+}
+
 }  // namespace
 
 // ------------------------------------------------ bursts of an active subset --
@@ -2283,8 +2631,8 @@ extern "C" int dd_set_plan(int64_t chunk_len, int variant)
 
 extern "C" int dd_last_plan(int64_t *chunk_len, int64_t *n_items, int *variant)
 {
-    if (chunk_len) *chunk_len = g_plan_chunk;
-    if (n_items) *n_items = g_plan_items;
+    if (chunk_len) *chunk_len = g_last_chunk;
+    if (n_items) *n_items = g_last_items;
     if (variant) *variant = g_last_variant;
     return DD_OK;
 }
@@ -2309,22 +2657,28 @@ extern "C" int dd_nodal_forces(int64_t n_nodes, const double *x, int64_t n_segs,
     hipStream_t st = (hipStream_t)stream;
     Workspace *ws;
     if ((rc = workspace(&ws))) return rc;
-    ForceCtx C;
-    std::vector<int64_t> so = {0, n_segs};
-    int64_t choice = 0;
-    Layout flat{};
-    if ((rc = tuned_chunk(ws, st, so, n_nodes, flat, seg_nodes, x, burgers, normal, m, n_gauss, precision,
-                          near_cutoff_a, false, &choice)))
-        return rc;
-    if ((rc = setup(ws, st, so, n_nodes, seg_nodes, m, n_gauss, precision, near_cutoff_a, exact_eta,
-                    choice / MIXED_VARIANTS, false, C)))
-        return rc;
-    C.variant = (int)(choice % MIXED_VARIANTS);
-    g_last_variant = C.variant;
-    launch_csr(C, seg_nodes, st);
     Sig6 sv;
     for (int k = 0; k < 6; ++k) sv.v[k] = sigma_app[k];
-    if ((rc = launch_forces(C, ws, x, seg_nodes, burgers, normal, nullptr, sv, force_out, st, true))) return rc;
+    if (small_volume(n_nodes, n_segs, precision, exact_eta)) {
+        launch_small(ws, n_nodes, n_segs, x, seg_nodes, burgers, normal, nullptr, sv, m, n_gauss, 0.0, force_out, nullptr,
+                     st);
+        note_small_plan(n_nodes, n_segs);
+    } else {
+        ForceCtx C;
+        std::vector<int64_t> so = {0, n_segs};
+        int64_t choice = 0;
+        Layout flat{};
+        if ((rc = tuned_chunk(ws, st, so, n_nodes, flat, seg_nodes, x, burgers, normal, m, n_gauss, precision,
+                              near_cutoff_a, false, &choice)))
+            return rc;
+        if ((rc = setup(ws, st, so, n_nodes, seg_nodes, m, n_gauss, precision, near_cutoff_a, exact_eta,
+                        choice / MIXED_VARIANTS, false, C)))
+            return rc;
+        C.variant = (int)(choice % MIXED_VARIANTS);
+        g_last_variant = C.variant;
+        launch_csr(C, seg_nodes, st);
+        if ((rc = launch_forces(C, ws, x, seg_nodes, burgers, normal, nullptr, sv, force_out, st, true))) return rc;
+    }
     DD_HIP(hipGetLastError());
     if (validation_on()) {
         hipLaunchKernelGGL(k_check_finite, dim3(grid_for(3 * n_nodes)), dim3(256), 0, st, force_out,
@@ -2418,18 +2772,6 @@ extern "C" int dd_step(int64_t n_nodes, double *x, int64_t n_segs, const int32_t
     hipStream_t st = (hipStream_t)stream;
     Workspace *ws;
     if ((rc = workspace(&ws))) return rc;
-    ForceCtx C;
-    std::vector<int64_t> so = {0, n_segs};
-    int64_t choice = 0;
-    Layout flat{};
-    if ((rc = tuned_chunk(ws, st, so, n_nodes, flat, seg_nodes, x, burgers, normal, m, n_gauss, precision,
-                          near_cutoff_a, false, &choice)))
-        return rc;
-    if ((rc = setup(ws, st, so, n_nodes, seg_nodes, m, n_gauss, precision, near_cutoff_a, exact_eta,
-                    choice / MIXED_VARIANTS, false, C)))
-        return rc;
-    C.variant = (int)(choice % MIXED_VARIANTS);
-    g_last_variant = C.variant;
     void *p;
     double *F = force_out, *vel = vel_out;
     if (!F) {
@@ -2440,14 +2782,33 @@ extern "C" int dd_step(int64_t n_nodes, double *x, int64_t n_segs, const int32_t
         if ((rc = ensure(ws, WS_VEL, sizeof(double) * 3 * n_nodes, &p))) return rc;
         vel = (double *)p;
     }
-    launch_csr(C, seg_nodes, st);
     Sig6 sv;
     for (int k = 0; k < 6; ++k) sv.v[k] = sigma_app[k];
-    if ((rc = launch_forces(C, ws, x, seg_nodes, burgers, normal, nullptr, sv, F, st, true))) return rc;
-    // lengths from the segment records of this force pass: x can move in the same kernel
-    hipLaunchKernelGGL(k_glide<true>, dim3(grid_for(n_nodes, 256, INT32_MAX)), dim3(256), 0, st, C.L, C.csr_ptr,
-                       C.csr_list, seg_nodes, normal, (const double *)C.rec64, C.a, x, (const double *)F, pinned,
-                       (const uint8_t *)nullptr, (const uint8_t *)nullptr, 1.0 / m->B, dt, vel);
+    if (small_volume(n_nodes, n_segs, precision, exact_eta)) {
+        launch_small(ws, n_nodes, n_segs, x, seg_nodes, burgers, normal, pinned, sv, m, n_gauss, 1.0 / m->B, F, vel, st);
+        note_small_plan(n_nodes, n_segs);
+        hipLaunchKernelGGL(k_euler, dim3(grid_for(3 * n_nodes, 256, INT32_MAX)), dim3(256), 0, st, n_nodes, x,
+                           (const double *)vel, dt);
+    } else {
+        ForceCtx C;
+        std::vector<int64_t> so = {0, n_segs};
+        int64_t choice = 0;
+        Layout flat{};
+        if ((rc = tuned_chunk(ws, st, so, n_nodes, flat, seg_nodes, x, burgers, normal, m, n_gauss, precision,
+                              near_cutoff_a, false, &choice)))
+            return rc;
+        if ((rc = setup(ws, st, so, n_nodes, seg_nodes, m, n_gauss, precision, near_cutoff_a, exact_eta,
+                        choice / MIXED_VARIANTS, false, C)))
+            return rc;
+        C.variant = (int)(choice % MIXED_VARIANTS);
+        g_last_variant = C.variant;
+        launch_csr(C, seg_nodes, st);
+        if ((rc = launch_forces(C, ws, x, seg_nodes, burgers, normal, nullptr, sv, F, st, true))) return rc;
+        // lengths from the segment records of this force pass: x can move in the same kernel
+        hipLaunchKernelGGL(k_glide<true>, dim3(grid_for(n_nodes, 256, INT32_MAX)), dim3(256), 0, st, C.L, C.csr_ptr,
+                           C.csr_list, seg_nodes, normal, (const double *)C.rec64, C.a, x, (const double *)F, pinned,
+                           (const uint8_t *)nullptr, (const uint8_t *)nullptr, 1.0 / m->B, dt, vel);
+    }
     DD_HIP(hipGetLastError());
     if (validation_on()) {
         hipLaunchKernelGGL(k_check_finite, dim3(grid_for(3 * n_nodes)), dim3(256), 0, st, (const double *)F,
@@ -2461,40 +2822,65 @@ extern "C" int dd_step(int64_t n_nodes, double *x, int64_t n_segs, const int32_t
 
 namespace dd {
 namespace {
-// The persistent kernel for a batch of small FP64 bursts, when every
-// instance fits (at most PB_MAX_SEGS segments and nodes) and all the
-// workgroups fit on the device at once; *used = false leaves the call to the
-// step graph.  G_i: about PB_NODES_PER_WG nodes per workgroup, at most
-// PB_MAX_G; one workgroup per instance in burst mode 2.  The node lists must
-// be built.
-int launch_persistent(const ForceCtx &C, Workspace *ws, const std::vector<int64_t> &no,
-                      const std::vector<int64_t> &so, double *x, const int32_t *seg_nodes, const double *burgers,
-                      const double *normal, const uint8_t *pinned, const double *sigma_app, const double *volume,
-                      const dd_material *m, int n_steps, double dt, double *rate_avg_out, hipStream_t st,
-                      bool *used)
+// All steps of a batch of small FP64 bursts in one launch, when every instance
+// fits (at most PB_MAX_SEGS segments and nodes), the workgroups can all be
+// resident with at most PB_MAX_NODES_PER_WG nodes each, and none takes more than
+// PB_MAX_ROUNDS rounds of target points: the workgroups per instance into G,
+// empty when the call is left to the step graph.  One workgroup per instance in
+// burst mode 2.
+//
+// A round is about 1.9 us, the step graph 40-75 us a step.  Measured, us a step
+// (launch, graph): one volume of 256 segments at 2 points, 1 round: 5.2, 41; 16 of
+// them, 9 rounds: 24, 47; 32 of them, 17 rounds: 40, 67; one of 512 at 4 points, 6
+// rounds: 20, 63; 16 of 512 at 2 points, 33 rounds: 81, 73.
+constexpr int PB_MAX_NODES_PER_WG = 32, PB_MAX_ROUNDS = 24;
+
+int plan_persistent(Workspace *ws, const std::vector<int64_t> &no, const std::vector<int64_t> &so, int Q,
+                    std::vector<int> &G)
 {
-    *used = false;
+    G.clear();
     const int mode = g_burst_mode.load();
     if (mode == 1) return DD_OK;
     const int n_inst = (int)no.size() - 1;
     for (int i = 0; i < n_inst; ++i)
         if (no[i + 1] - no[i] > PB_MAX_SEGS || so[i + 1] - so[i] > PB_MAX_SEGS) return DD_OK;
     int per_cu = 0, cus = 0;
-    DD_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_burst_persistent, PB_THREADS, 0));
+    DD_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_small<true>, PB_THREADS, 0));
     DD_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, ws->device));
     const int64_t cap = (int64_t)per_cu * cus;
     if (n_inst > cap) return DD_OK;
-    std::vector<int> G(n_inst);
+    // nodes per workgroup: the fewest with which all workgroups fit
+    G.assign(n_inst, 1);
     int64_t total = 0;
-    for (int i = 0; i < n_inst; ++i) {
-        const int64_t want = (no[i + 1] - no[i] + PB_NODES_PER_WG - 1) / PB_NODES_PER_WG;
-        G[i] = mode == 2 ? 1 : (int)std::max<int64_t>(1, std::min<int64_t>(want, PB_MAX_G));
-        total += G[i];
+    int npw = 1;
+    for (; npw <= PB_MAX_NODES_PER_WG; ++npw) {
+        total = 0;
+        for (int i = 0; i < n_inst; ++i) {
+            G[i] = mode == 2 ? 1 : (int)std::max<int64_t>(1, (no[i + 1] - no[i] + npw - 1) / npw);
+            total += G[i];
+        }
+        if (total <= cap) break;
     }
-    // with fewer workgroups each would carry more nodes, and the step graph is
-    // then the faster of the two (measured): only a batch that fits as split
-    if (total > cap) return DD_OK;
-    const int n_wg = (int)total;
+    bool fits = total <= cap;
+    if (mode != 2)
+        for (int i = 0; i < n_inst; ++i) {
+            const int64_t P = std::max<int64_t>(64, (so[i + 1] - so[i] + 63) / 64 * 64);
+            const int64_t per_round = PB_THREADS / P * PB_POINTS;
+            fits = fits && ((npw + 1) * Q + per_round - 1) / per_round <= PB_MAX_ROUNDS;
+        }
+    if (!fits) G.clear();
+    return DD_OK;
+}
+
+int launch_persistent(Workspace *ws, const Layout &L, const std::vector<int64_t> &no, const std::vector<int> &G, double *x,
+                      const int32_t *seg_nodes, const double *burgers, const double *normal, const uint8_t *pinned,
+                      const double *sigma_app, const double *volume, const dd_material *m, int n_gauss, int n_steps,
+                      double dt, double *rate_avg_out, hipStream_t st, bool *used)
+{
+    *used = false;
+    const int n_inst = (int)no.size() - 1;
+    int n_wg = 0;
+    for (int i = 0; i < n_inst; ++i) n_wg += G[i];
     std::vector<int32_t> tab(4 * (size_t)n_wg);
     for (int i = 0, k = 0; i < n_inst; ++i) {
         const int first = k;
@@ -2505,60 +2891,167 @@ int launch_persistent(const ForceCtx &C, Workspace *ws, const std::vector<int64_
             tab[3 * n_wg + k] = first;
         }
     }
-    const int64_t nn = no.back();
+    const int64_t nn = no.back(), n3 = 3 * std::max<int64_t>(nn, 1);
     void *p;
     int rc;
-    if ((rc = ensure(ws, WS_PB, sizeof(double) * (9 * (size_t)std::max<int64_t>(nn, 1) + 12 * (size_t)n_wg), &p)))
-        return rc;
-    double *xb = (double *)p, *vel2 = xb + 3 * std::max<int64_t>(nn, 1), *wpart = vel2 + 6 * std::max<int64_t>(nn, 1);
+    if ((rc = ensure(ws, WS_PB, sizeof(double) * (4 * (size_t)n3 + 12 * (size_t)n_wg), &p))) return rc;
+    double *xbuf = (double *)p;
     int32_t *wgtab = (int32_t *)ws->ptr[WS_PB_INT];
     if (tab != ws->pb_tab || !wgtab) {   // uploaded (one synchronisation) only when the table changes
         if ((rc = upload(ws, WS_PB_INT, tab, &wgtab, st))) return rc;
         ws->pb_tab = tab;
     }
-    // barrier arrival words, zeroed on the stream
-    void *pb;
-    if ((rc = ensure(ws, WS_PB_BAR, sizeof(unsigned) * 16 * (size_t)n_wg, &pb))) return rc;
-    hipLaunchKernelGGL(k_fill_u32, dim3(grid_for(16 * (int64_t)n_wg)), dim3(256), 0, st, (unsigned *)pb,
-                       16 * (int64_t)n_wg, 0u);
+    hipLaunchKernelGGL(k_pb_empty, dim3(grid_for(3 * n3, 256, INT32_MAX)), dim3(256), 0, st, xbuf, 3 * n3);
     PBArgs A{};
-    A.L = C.L;
+    small_args(A, m, n_gauss);
+    A.L = L;
     A.seg_nodes = seg_nodes;
     A.burgers = burgers;
     A.normal = normal;
     A.pinned = pinned;
-    A.sigma_app = sigma_app;
+    A.sigma_dev = sigma_app;
     A.volume = volume;
-    A.csr_ptr = C.csr_ptr;
-    A.csr_list = C.csr_list;
     A.wg = wgtab;
     A.n_wg = n_wg;
-    A.xa = x;
-    A.xb = xb;
-    A.vel = vel2;
-    A.wpart = wpart;
-    A.arrive = (unsigned *)pb;
+    A.x = x;
+    A.xbuf = xbuf;
+    A.xend = xbuf + 3 * n3;
+    A.wpart = A.xend + n3;
     A.flags = ws->flags_dev;
-    A.rate_out = rate_avg_out;
-    A.g = C.g;
-    A.kr = C.k1 / C.k2;
-    A.nu = 1.0 - 2.0 * A.kr;
-    A.k2 = C.k2;
-    A.inv_a = C.inv_a;
-    A.a = C.a;
-    A.inv_mu = C.inv_mu;
-    A.fscale = C.fscale;
     A.invB = 1.0 / m->B;
     A.dt = dt;
     A.n_steps = n_steps;
     void *args[] = {&A};
-    const hipError_t e = hipLaunchCooperativeKernel((const void *)k_burst_persistent, dim3((unsigned)n_wg),
-                                                    dim3(PB_THREADS), args, 0, st);
+    const hipError_t e = hipLaunchCooperativeKernel((const void *)k_small<true>, dim3((unsigned)n_wg), dim3(PB_THREADS),
+                                                    args, 0, st);
     if (e != hipSuccess) {
         (void)hipGetLastError();   // not launched: the step graph runs instead
         return DD_OK;
     }
+    hipLaunchKernelGGL(k_pb_finish, dim3(grid_for(std::max<int64_t>(3 * nn, 12 * (int64_t)n_wg), 256, INT32_MAX)), dim3(256),
+                       0, st, (const int32_t *)wgtab, n_wg, n_inst, (const double *)A.wpart, 1.0 / n_steps, rate_avg_out,
+                       3 * nn, (const double *)A.xend, x);
     *used = true;
+    return DD_OK;
+}
+
+// A batch of bursts as a cached graph of per-step kernels (arguments checked).
+int burst_graph(Workspace *ws, const Layout &inst, int32_t n_inst, const std::vector<int64_t> &no,
+                const std::vector<int64_t> &so, double *x, const int32_t *seg_nodes, const double *burgers,
+                const double *normal, const uint8_t *pinned, const double *sigma_app, const double *volume,
+                const dd_material *m, int n_gauss, int precision, double near_cutoff_a, double exact_eta, int n_steps,
+                double dt, const dd_junctions *jn, const dd_junction_nodes *jnodes, double *rate_avg_out,
+                double *features_out, hipStream_t st)
+{
+    int rc;
+    const int64_t nn = no[n_inst], ns = so[n_inst];
+    void *p;
+    ForceCtx C;
+    int64_t choice = 0;
+    if ((rc = tuned_chunk(ws, st, so, nn, inst, seg_nodes, x, burgers, normal, m, n_gauss, precision,
+                          near_cutoff_a, true, &choice)))
+        return rc;
+    if ((rc = setup(ws, st, so, nn, seg_nodes, m, n_gauss, precision, near_cutoff_a, exact_eta,
+                    choice / MIXED_VARIANTS, true, C)))
+        return rc;
+    C.variant = (int)(choice % MIXED_VARIANTS);
+    g_last_variant = C.variant;
+    C.L.seg_inst = inst.seg_inst;
+    C.L.node_off = inst.node_off;
+    C.L.seg_off = inst.seg_off;
+    C.L.tile_begin = (const int64_t *)ws->ptr[WS_OFFS];
+    if ((rc = ensure(ws, WS_VEL, sizeof(double) * 3 * std::max<int64_t>(nn, 1), &p))) return rc;
+    double *vel = (double *)p;
+    if ((rc = ensure(ws, WS_FORCE, sizeof(double) * 3 * std::max<int64_t>(nn, 1), &p))) return rc;
+    double *F = (double *)p;
+    uint8_t *held = nullptr;
+    if ((rc = ensure(ws, WS_T0, sizeof(double), &p))) return rc;
+    double *t0_dev = (double *)p;
+    JunctionArgs J{};
+    if (jn && (rc = junction_prepare(ws, C.L, seg_nodes, x, pinned, jn, J, &held, st))) return rc;
+    J.t0 = t0_dev;
+    JNodeArgs JN{};
+    if (jnodes && (rc = jnode_prepare(ws, C.L, seg_nodes, x, pinned, jnodes, JN, st))) return rc;
+    JN.t0 = t0_dev;
+
+    launch_csr(C, seg_nodes, st);
+    hipLaunchKernelGGL(k_fill_f64, dim3(grid_for(12 * (int64_t)n_inst)), dim3(256), 0, st, rate_avg_out,
+                       12 * (int64_t)n_inst, 0.0);
+    Sig6 sv{};
+    // features of the initial state
+    if (features_out && ns > 0) {
+        PrepArgs A;
+        A.L = C.L;
+        A.x = x;
+        A.seg_nodes = seg_nodes;
+        A.burgers = burgers;
+        A.normal = normal;
+        A.inv_a = C.inv_a;
+        A.rec64 = C.rec64;
+        A.rec32 = C.rec32;
+        A.cut = C.cut;
+        A.quadn = C.precision == DD_MIXED ? quad_points(C.variant) : 0;
+        A.sys = C.sys;
+        A.flags = ws->flags_dev;
+        hipLaunchKernelGGL(k_seg_prep, dim3(grid_for(ns, PREP_BLOCK, INT32_MAX)), dim3(PREP_BLOCK), 0, st, A);
+        hipLaunchKernelGGL(k_instance_sums, dim3(n_inst), dim3(256), 0, st, C.L, 1, seg_nodes, C.rec64, C.sys,
+                           (const double *)nullptr, pinned, volume, sigma_app, C.a, features_out);
+    } else if (features_out) {
+        hipLaunchKernelGGL(k_fill_f64, dim3(grid_for(36 * (int64_t)n_inst)), dim3(256), 0, st, features_out,
+                           36 * (int64_t)n_inst, 0.0);
+    }
+    DD_HIP(hipGetLastError());
+
+    if (n_steps > 0 && ns > 0) {
+        if ((rc = presize_near(C, ws, x, seg_nodes, st))) return rc;
+        // the whole step loop as one graph, cached for calls with the same key
+        KeyBuf key;
+        key.add('b').add(n_inst).add_vec(no).add_vec(so).add(x).add(seg_nodes).add(burgers).add(normal);
+        key.add(pinned).add(sigma_app).add(volume).add(*m).add(n_gauss).add(precision).add(near_cutoff_a);
+        key.add(exact_eta).add(n_steps).add(dt).add(choice).add(rate_avg_out).add(jn != nullptr);
+        key.add(C.near.pair_cap).add_workspace(ws);
+        // the start time is not part of the key: the step kernels read it from
+        // the device, where it is stored on the caller's stream before the
+        // graph is launched, so that consecutive calls share one graph
+        if (jn) {
+            dd_junctions kj = *jn;
+            kj.t0 = 0.0;
+            key.add(kj);
+        }
+        key.add(jnodes != nullptr);
+        if (jnodes) {
+            dd_junction_nodes kj = *jnodes;
+            kj.t0 = 0.0;
+            key.add(kj);
+        }
+        if (jn || jnodes)
+            hipLaunchKernelGGL(k_fill_f64, dim3(1), dim3(64), 0, st, t0_dev, (int64_t)1, jn ? jn->t0 : jnodes->t0);
+        rc = launch_cached_graph(ws, key, [&](hipStream_t cs) -> int {
+            for (int k = 0; k < n_steps; ++k) {
+                if (jnodes)   // (the public call passes these arrays as writable)
+                    launch_jnode_step(C, JN, k * dt, k, n_inst, const_cast<int32_t *>(seg_nodes), x,
+                                      const_cast<double *>(burgers), const_cast<double *>(normal), ws->flags_dev,
+                                      nullptr, cs);
+                if (jn) {
+                    J.tk = k * dt;
+                    hipLaunchKernelGGL(k_junctions, dim3(grid_for(nn, 256, INT32_MAX)), dim3(256), 0, cs, C.L,
+                                       seg_nodes, (const double *)x, pinned, J, n_inst, (const uint8_t *)nullptr,
+                                       (const int64_t *)nullptr, dt, k, held);
+                }
+                const int r = launch_forces(C, ws, x, seg_nodes, burgers, normal, sigma_app, sv, F, cs, false);
+                if (r) return r;
+                hipLaunchKernelGGL(k_glide<true>, dim3(grid_for(nn, 256, INT32_MAX)), dim3(256), 0, cs, C.L,
+                                   C.csr_ptr, C.csr_list, seg_nodes, normal, C.rec64, C.a, x, F, pinned,
+                                   (const uint8_t *)held, (const uint8_t *)nullptr, 1.0 / m->B, dt, vel);
+                hipLaunchKernelGGL(k_instance_sums, dim3(n_inst), dim3(256), 0, cs, C.L, 0, seg_nodes, C.rec64,
+                                   C.sys, vel, pinned, volume, sigma_app, C.a, rate_avg_out);
+            }
+            return DD_OK;
+        }, st);
+        if (rc) return rc;
+        hipLaunchKernelGGL(k_scale_rates, dim3(grid_for(12 * (int64_t)n_inst, 256, INT32_MAX)), dim3(256), 0,
+                           st, rate_avg_out, 12 * (int64_t)n_inst, 1.0 / n_steps);
+    }
     return DD_OK;
 }
 
@@ -2620,122 +3113,43 @@ int burst_batch_impl(int32_t n_inst, const int64_t *node_off, const int64_t *seg
     std::vector<int64_t> so(seg_off, seg_off + n_inst + 1), no(node_off, node_off + n_inst + 1);
     Layout inst{};
     if ((rc = instance_tables(ws, no, so, inst, st))) return rc;
-    ForceCtx C;
-    int64_t choice = 0;
-    if ((rc = tuned_chunk(ws, st, so, nn, inst, seg_nodes, x, burgers, normal, m, n_gauss, precision,
-                          near_cutoff_a, true, &choice)))
-        return rc;
-    if ((rc = setup(ws, st, so, nn, seg_nodes, m, n_gauss, precision, near_cutoff_a, exact_eta,
-                    choice / MIXED_VARIANTS, true, C)))
-        return rc;
-    C.variant = (int)(choice % MIXED_VARIANTS);
-    g_last_variant = C.variant;
-    C.L.seg_inst = inst.seg_inst;
-    C.L.node_off = inst.node_off;
-    C.L.seg_off = inst.seg_off;
-    C.L.tile_begin = (const int64_t *)ws->ptr[WS_OFFS];
     void *p;
-    if ((rc = ensure(ws, WS_VEL, sizeof(double) * 3 * std::max<int64_t>(nn, 1), &p))) return rc;
-    double *vel = (double *)p;
-    if ((rc = ensure(ws, WS_FORCE, sizeof(double) * 3 * std::max<int64_t>(nn, 1), &p))) return rc;
-    double *F = (double *)p;
-    uint8_t *held = nullptr;
-    if ((rc = ensure(ws, WS_T0, sizeof(double), &p))) return rc;
-    double *t0_dev = (double *)p;
-    JunctionArgs J{};
-    if (jn && (rc = junction_prepare(ws, C.L, seg_nodes, x, pinned, jn, J, &held, st))) return rc;
-    J.t0 = t0_dev;
-    JNodeArgs JN{};
-    if (jnodes && (rc = jnode_prepare(ws, C.L, seg_nodes, x, pinned, jnodes, JN, st))) return rc;
-    JN.t0 = t0_dev;
-
-    launch_csr(C, seg_nodes, st);
-    hipLaunchKernelGGL(k_fill_f64, dim3(grid_for(12 * (int64_t)n_inst)), dim3(256), 0, st, rate_avg_out,
-                       12 * (int64_t)n_inst, 0.0);
-    Sig6 sv{};
-    // features of the initial state
-    if (features_out && ns > 0) {
-        PrepArgs A;
-        A.L = C.L;
-        A.x = x;
-        A.seg_nodes = seg_nodes;
-        A.burgers = burgers;
-        A.normal = normal;
-        A.inv_a = C.inv_a;
-        A.rec64 = C.rec64;
-        A.rec32 = C.rec32;
-        A.cut = C.cut;
-        A.quadn = C.precision == DD_MIXED ? quad_points(C.variant) : 0;
-        A.sys = C.sys;
-        A.flags = ws->flags_dev;
-        hipLaunchKernelGGL(k_seg_prep, dim3(grid_for(ns, PREP_BLOCK, INT32_MAX)), dim3(PREP_BLOCK), 0, st, A);
-        hipLaunchKernelGGL(k_instance_sums, dim3(n_inst), dim3(256), 0, st, C.L, 1, seg_nodes, C.rec64, C.sys,
-                           (const double *)nullptr, pinned, volume, sigma_app, C.a, features_out);
-    } else if (features_out) {
-        hipLaunchKernelGGL(k_fill_f64, dim3(grid_for(36 * (int64_t)n_inst)), dim3(256), 0, st, features_out,
-                           36 * (int64_t)n_inst, 0.0);
-    }
-    DD_HIP(hipGetLastError());
 
     // small FP64 bursts: every step in one persistent launch, when it fits
     bool persistent = false;
-    if (n_steps > 0 && ns > 0 && !jn && !jnodes && exact_eta == 0.0 && precision == DD_FP64 &&
-        (rc = launch_persistent(C, ws, no, so, x, seg_nodes, burgers, normal, pinned, sigma_app, volume, m, n_steps,
-                                dt, rate_avg_out, st, &persistent)))
-        return rc;
-    if (persistent) {
-        hipLaunchKernelGGL(k_scale_rates, dim3(grid_for(12 * (int64_t)n_inst, 256, INT32_MAX)), dim3(256), 0,
-                           st, rate_avg_out, 12 * (int64_t)n_inst, 1.0 / n_steps);
-    } else if (n_steps > 0 && ns > 0) {
-        if ((rc = presize_near(C, ws, x, seg_nodes, st))) return rc;
-        // the whole step loop as one graph, cached for calls with the same key
-        KeyBuf key;
-        key.add('b').add(n_inst).add_vec(no).add_vec(so).add(x).add(seg_nodes).add(burgers).add(normal);
-        key.add(pinned).add(sigma_app).add(volume).add(*m).add(n_gauss).add(precision).add(near_cutoff_a);
-        key.add(exact_eta).add(n_steps).add(dt).add(choice).add(rate_avg_out).add(jn != nullptr);
-        key.add(C.near.pair_cap).add_workspace(ws);
-        // the start time is not part of the key: the step kernels read it from
-        // the device, where it is stored on the caller's stream before the
-        // graph is launched, so that consecutive calls share one graph
-        if (jn) {
-            dd_junctions kj = *jn;
-            kj.t0 = 0.0;
-            key.add(kj);
-        }
-        key.add(jnodes != nullptr);
-        if (jnodes) {
-            dd_junction_nodes kj = *jnodes;
-            kj.t0 = 0.0;
-            key.add(kj);
-        }
-        if (jn || jnodes)
-            hipLaunchKernelGGL(k_fill_f64, dim3(1), dim3(64), 0, st, t0_dev, (int64_t)1, jn ? jn->t0 : jnodes->t0);
-        rc = launch_cached_graph(ws, key, [&](hipStream_t cs) -> int {
-            for (int k = 0; k < n_steps; ++k) {
-                if (jnodes)   // (the public call passes these arrays as writable)
-                    launch_jnode_step(C, JN, k * dt, k, n_inst, const_cast<int32_t *>(seg_nodes), x,
-                                      const_cast<double *>(burgers), const_cast<double *>(normal), ws->flags_dev,
-                                      nullptr, cs);
-                if (jn) {
-                    J.tk = k * dt;
-                    hipLaunchKernelGGL(k_junctions, dim3(grid_for(nn, 256, INT32_MAX)), dim3(256), 0, cs, C.L,
-                                       seg_nodes, (const double *)x, pinned, J, n_inst, (const uint8_t *)nullptr,
-                                       (const int64_t *)nullptr, dt, k, held);
-                }
-                const int r = launch_forces(C, ws, x, seg_nodes, burgers, normal, sigma_app, sv, F, cs, false);
-                if (r) return r;
-                hipLaunchKernelGGL(k_glide<true>, dim3(grid_for(nn, 256, INT32_MAX)), dim3(256), 0, cs, C.L,
-                                   C.csr_ptr, C.csr_list, seg_nodes, normal, C.rec64, C.a, x, F, pinned,
-                                   (const uint8_t *)held, (const uint8_t *)nullptr, 1.0 / m->B, dt, vel);
-                hipLaunchKernelGGL(k_instance_sums, dim3(n_inst), dim3(256), 0, cs, C.L, 0, seg_nodes, C.rec64,
-                                   C.sys, vel, pinned, volume, sigma_app, C.a, rate_avg_out);
+    if (n_steps > 0 && ns > 0 && !jn && !jnodes && exact_eta == 0.0 && precision == DD_FP64) {
+        std::vector<int> G;
+        if ((rc = plan_persistent(ws, no, so, n_gauss, G))) return rc;
+        if (!G.empty()) {
+            Layout L = inst;
+            L.nn = nn;
+            L.ns = ns;
+            if (features_out) {
+                PrepArgs A{};
+                A.L = L;
+                A.x = x;
+                A.seg_nodes = seg_nodes;
+                A.burgers = burgers;
+                A.normal = normal;
+                A.inv_a = 1.0 / m->a;
+                if ((rc = ensure(ws, WS_SEG64, rec64_bytes(ns), &p))) return rc;
+                A.rec64 = (double *)p;
+                if ((rc = ensure(ws, WS_MISC, sizeof(int32_t) * (size_t)ns, &p))) return rc;
+                A.sys = (int32_t *)p;
+                A.flags = ws->flags_dev;
+                hipLaunchKernelGGL(k_seg_prep, dim3(grid_for(ns, PREP_BLOCK, INT32_MAX)), dim3(PREP_BLOCK), 0, st, A);
+                hipLaunchKernelGGL(k_instance_sums, dim3(n_inst), dim3(256), 0, st, L, 1, seg_nodes, A.rec64, A.sys,
+                                   (const double *)nullptr, pinned, volume, sigma_app, m->a, features_out);
             }
-            return DD_OK;
-        }, st);
-        if (rc) return rc;
-        hipLaunchKernelGGL(k_scale_rates, dim3(grid_for(12 * (int64_t)n_inst, 256, INT32_MAX)), dim3(256), 0,
-                           st, rate_avg_out, 12 * (int64_t)n_inst, 1.0 / n_steps);
+            if ((rc = launch_persistent(ws, L, no, G, x, seg_nodes, burgers, normal, pinned, sigma_app, volume, m, n_gauss,
+                                        n_steps, dt, rate_avg_out, st, &persistent)))
+                return rc;
+        }
     }
+    if (!persistent &&
+        (rc = burst_graph(ws, inst, n_inst, no, so, x, seg_nodes, burgers, normal, pinned, sigma_app, volume, m, n_gauss,
+                          precision, near_cutoff_a, exact_eta, n_steps, dt, jn, jnodes, rate_avg_out, features_out, st)))
+        return rc;
     DD_HIP(hipGetLastError());
     if (validation_on()) {
         hipLaunchKernelGGL(k_check_finite, dim3(grid_for(12 * (int64_t)n_inst)), dim3(256), 0, st,
@@ -2920,6 +3334,14 @@ extern "C" int dd_nodal_forces_noalloc(int64_t n_nodes, const double *x, int64_t
     ws.flags_dev = cv.take<unsigned>(64);
     ws.near_count = (unsigned long long *)(ws.flags_dev + 32);
     ws.capturing = true;   // no event timing (events would be created on first use)
+    if (small_volume(n_nodes, n_segs, precision, 0.0)) {   // as dd_nodal_forces; needs no scratch
+        Sig6 sv;
+        for (int k = 0; k < 6; ++k) sv.v[k] = sigma_app[k];
+        launch_small(&ws, n_nodes, n_segs, x, seg_nodes, burgers, normal, nullptr, sv, m, n_gauss, 0.0, force_out, nullptr,
+                     st);
+        DD_HIP(hipGetLastError());
+        return DD_OK;
+    }
     ForceCtx C;
     C.g = gauss_rule(n_gauss);
     C.k1 = 1.0 / (8.0 * M_PI);
