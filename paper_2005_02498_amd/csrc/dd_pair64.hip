@@ -26,10 +26,33 @@ namespace dd {
 // 1.535 -> 1.444 ms.  Measured and left out: two Gauss points of a segment per
 // lane (t.b_j and t.g shared, 79 instructions, 120 VGPRs): 1.449 ms; six
 // wavefronts per SIMD forced by launch bounds (80 VGPRs for 96): 1.473 ms.
+// With few wavefronts per SIMD (up to a few thousand segments) the wait for a
+// record's scalar load shows: the next record is therefore asked for before a
+// source is evaluated.  A step of 1,024 segments 60.0 -> 54.2 us, 16 volumes of
+// 512 segments 73.0 -> 68.6 us per step, 16,384 segments unchanged.
 //
 // Runs of fewer than RUN_MIN sources take the form that needs no set-up: the
 // run form costs 15 instructions per run and saves 7 per source.
 constexpr int RUN_MIN = 4;
+
+// What a run reads of a source's record (x1, t, L, c), in scalar registers.
+struct RunRec {
+    double v[10];
+    __device__ __forceinline__ explicit RunRec(const double *r)
+    {
+#pragma unroll
+        for (int i = 0; i < 7; ++i) v[i] = r[i];
+#pragma unroll
+        for (int i = 7; i < 10; ++i) v[i] = r[i + 3];
+    }
+    // Loads after this one in the program are issued once these values are here
+    // (scalar loads return in no order, so a wait for one waits for all).
+    __device__ __forceinline__ void arrived()
+    {
+        asm volatile("" : "+s"(v[0]), "+s"(v[1]), "+s"(v[2]), "+s"(v[3]), "+s"(v[4]), "+s"(v[5]), "+s"(v[6]), "+s"(v[7]),
+                          "+s"(v[8]), "+s"(v[9]) : : "memory");
+    }
+};
 
 template <bool SELF>
 __device__ __forceinline__ void pair64_range(const double *__restrict__ ra, int64_t b, int64_t e,
@@ -39,10 +62,12 @@ __device__ __forceinline__ void pair64_range(const double *__restrict__ ra, int6
 {
     for (int64_t m = b; m < e;) {
         const double *c = ra + m * RECA;
+        RunRec A(c);
         // uniform run length (>= 1), counted in 32 bits so that the loop
         // control stays on the scalar unit
         const int n = (int)min(e - m, (int64_t)__double_as_longlong(c[13]));
-        const double R0 = xq0 - c[0], R1 = xq1 - c[1], R2 = xq2 - c[2];
+        A.arrived();
+        const double R0 = xq0 - A.v[0], R1 = xq1 - A.v[1], R2 = xq2 - A.v[2];
         double r1 = rsqrt64(fma(R2, R2, fma(R1, R1, fma(R0, R0, 1.0))));
         double r1c = r1 * r1 * r1;
         int k = 0;
@@ -53,16 +78,24 @@ __device__ __forceinline__ void pair64_range(const double *__restrict__ ra, int6
             double w0 = 0.0, w1 = 0.0, w2 = 0.0;
             // two sources per iteration: the second takes the first's far-end
             // values and leaves its own where the first's near-end values were,
-            // so no register copy is made per source
-            for (; k + 2 <= n; k += 2, c += 2 * RECA) {
+            // so no register copy is made per source; while one is evaluated the
+            // record of the next is on its way
+            const double *const last = c + (int64_t)(n - 1) * RECA;
+            for (; k + 2 <= n; k += 2) {
                 double r2, r2c;
-                pair_run_acc_f64(xq0, xq1, xq2, bj0, bj1, bj2, g0, g1, g2, c[0], c[1], c[2], c[3], c[4], c[5],
-                                 c[6], c[10], c[11], c[12], ikr, nukr, r1, r1c, r2, r2c, a0, a1, a2, w0, w1, w2,
-                                 ak);
-                const double *d = c + RECA;
-                pair_run_acc_f64(xq0, xq1, xq2, bj0, bj1, bj2, g0, g1, g2, d[0], d[1], d[2], d[3], d[4], d[5],
-                                 d[6], d[10], d[11], d[12], ikr, nukr, r2, r2c, r1, r1c, a0, a1, a2, w0, w1, w2,
-                                 ak);
+                A.arrived();
+                RunRec B(c + RECA);
+                __builtin_amdgcn_sched_barrier(0);
+                pair_run_acc_f64(xq0, xq1, xq2, bj0, bj1, bj2, g0, g1, g2, A.v[0], A.v[1], A.v[2], A.v[3], A.v[4],
+                                 A.v[5], A.v[6], A.v[7], A.v[8], A.v[9], ikr, nukr, r1, r1c, r2, r2c, a0, a1, a2, w0,
+                                 w1, w2, ak);
+                B.arrived();
+                c = k + 2 < n ? c + 2 * RECA : last;
+                A = RunRec(c);
+                __builtin_amdgcn_sched_barrier(0);
+                pair_run_acc_f64(xq0, xq1, xq2, bj0, bj1, bj2, g0, g1, g2, B.v[0], B.v[1], B.v[2], B.v[3], B.v[4],
+                                 B.v[5], B.v[6], B.v[7], B.v[8], B.v[9], ikr, nukr, r2, r2c, r1, r1c, a0, a1, a2, w0,
+                                 w1, w2, ak);
             }
             a0 = fma(-kr, fma(w1, b2, -w2 * b1), a0);
             a1 = fma(-kr, fma(w2, b0, -w0 * b2), a1);
