@@ -28,29 +28,49 @@ namespace dd {
 // wavefronts per SIMD forced by launch bounds (80 VGPRs for 96): 1.473 ms.
 // With few wavefronts per SIMD (up to a few thousand segments) the wait for a
 // record's scalar load shows: the next record is therefore asked for before a
-// source is evaluated.  A step of 1,024 segments 60.0 -> 54.2 us, 16 volumes of
-// 512 segments 73.0 -> 68.6 us per step, 16,384 segments unchanged.
+// source is evaluated, in a run and between runs.  Before (each record loaded
+// when it is needed) and now: a step of 1,024 segments 60.0 and 52.6 us, of
+// 1,107 shuffled ones with close pairs exact 246 and 220 us, 64 volumes of 256
+// segments 76 and 69 us per step, 4,096 shuffled segments 180 and 167 us;
+// 16,384 segments 1.39 ms as before.
 //
 // Runs of fewer than RUN_MIN sources take the form that needs no set-up: the
 // run form costs 15 instructions per run and saves 7 per source.
 constexpr int RUN_MIN = 4;
 
-// What a run reads of a source's record (x1, t, L, c), in scalar registers.
-struct RunRec {
-    double v[10];
-    __device__ __forceinline__ explicit RunRec(const double *r)
+// N consecutive words of a source's record, from the FIRST-th, in scalar registers.
+template <int FIRST, int N>
+struct RecWords {
+    double v[N];
+    __device__ __forceinline__ void load(const double *r)
     {
 #pragma unroll
-        for (int i = 0; i < 7; ++i) v[i] = r[i];
-#pragma unroll
-        for (int i = 7; i < 10; ++i) v[i] = r[i + 3];
+        for (int i = 0; i < N; ++i) v[i] = r[FIRST + i];
     }
-    // Loads after this one in the program are issued once these values are here
-    // (scalar loads return in no order, so a wait for one waits for all).
+    // What precedes this in the program is issued before these values are
+    // waited for, loads that follow after it (scalar loads return in no order,
+    // so a wait for one waits for all).
     __device__ __forceinline__ void arrived()
     {
-        asm volatile("" : "+s"(v[0]), "+s"(v[1]), "+s"(v[2]), "+s"(v[3]), "+s"(v[4]), "+s"(v[5]), "+s"(v[6]), "+s"(v[7]),
-                          "+s"(v[8]), "+s"(v[9]) : : "memory");
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int i = 0; i < N; ++i) asm volatile("" : "+s"(v[i]) : : "memory");
+    }
+};
+
+// What a run reads of a source: (x1, t, L) and c.
+struct RunRec {
+    RecWords<0, 7> p;
+    RecWords<10, 3> c;
+    __device__ __forceinline__ void load(const double *r)
+    {
+        p.load(r);
+        c.load(r);
+    }
+    __device__ __forceinline__ void arrived()
+    {
+        p.arrived();
+        c.arrived();
     }
 };
 
@@ -60,68 +80,86 @@ __device__ __forceinline__ void pair64_range(const double *__restrict__ ra, int6
                                              double bj1, double bj2, double kr, double nu, double ikr,
                                              double nukr, double &a0, double &a1, double &a2, double &ak)
 {
-    for (int64_t m = b; m < e;) {
-        const double *c = ra + m * RECA;
-        RunRec A(c);
-        // uniform run length (>= 1), counted in 32 bits so that the loop
-        // control stays on the scalar unit
-        const int n = (int)min(e - m, (int64_t)__double_as_longlong(c[13]));
+    // Counted in 32 bits, so that the loop control stays on the scalar unit (a
+    // volume of 2^31 segments does not fit the device's memory).
+    const double *const c = ra + b * RECA;
+    const int n = (int)(e - b), own = (int)(j - b);
+    if (n <= 0) return;
+    // A: the source to be evaluated; the next one asked for is never past the range's last
+    RecWords<0, 14> A;
+    A.load(c);
+    double r1 = 0.0, r1c = 0.0;
+    int left = 0;   // of the run being evaluated
+    for (int k = 0; k < n;) {
         A.arrived();
-        const double R0 = xq0 - A.v[0], R1 = xq1 - A.v[1], R2 = xq2 - A.v[2];
-        double r1 = rsqrt64(fma(R2, R2, fma(R1, R1, fma(R0, R0, 1.0))));
-        double r1c = r1 * r1 * r1;
-        int k = 0;
-        if (!SELF && n >= RUN_MIN) {
-            const double b0 = c[7], b1 = c[8], b2 = c[9];
-            const double g0 = kr * fma(bj1, b2, -bj2 * b1), g1 = kr * fma(bj2, b0, -bj0 * b2),
-                         g2 = kr * fma(bj0, b1, -bj1 * b0);
-            double w0 = 0.0, w1 = 0.0, w2 = 0.0;
-            // two sources per iteration: the second takes the first's far-end
-            // values and leaves its own where the first's near-end values were,
-            // so no register copy is made per source; while one is evaluated the
-            // record of the next is on its way
-            const double *const last = c + (int64_t)(n - 1) * RECA;
-            for (; k + 2 <= n; k += 2) {
-                double r2, r2c;
-                A.arrived();
-                RunRec B(c + RECA);
-                __builtin_amdgcn_sched_barrier(0);
-                pair_run_acc_f64(xq0, xq1, xq2, bj0, bj1, bj2, g0, g1, g2, A.v[0], A.v[1], A.v[2], A.v[3], A.v[4],
-                                 A.v[5], A.v[6], A.v[7], A.v[8], A.v[9], ikr, nukr, r1, r1c, r2, r2c, a0, a1, a2, w0,
-                                 w1, w2, ak);
-                B.arrived();
-                c = k + 2 < n ? c + 2 * RECA : last;
-                A = RunRec(c);
-                __builtin_amdgcn_sched_barrier(0);
-                pair_run_acc_f64(xq0, xq1, xq2, bj0, bj1, bj2, g0, g1, g2, B.v[0], B.v[1], B.v[2], B.v[3], B.v[4],
-                                 B.v[5], B.v[6], B.v[7], B.v[8], B.v[9], ikr, nukr, r2, r2c, r1, r1c, a0, a1, a2, w0,
-                                 w1, w2, ak);
+        if (left == 0) {
+            left = (int)min((int64_t)(n - k), (int64_t)__double_as_longlong(A.v[13]));
+            const double R0 = xq0 - A.v[0], R1 = xq1 - A.v[1], R2 = xq2 - A.v[2];
+            r1 = rsqrt64(fma(R2, R2, fma(R1, R1, fma(R0, R0, 1.0))));
+            r1c = r1 * r1 * r1;
+            if (!SELF && left >= RUN_MIN) {
+                const double b0 = A.v[7], b1 = A.v[8], b2 = A.v[9];
+                const double g0 = kr * fma(bj1, b2, -bj2 * b1), g1 = kr * fma(bj2, b0, -bj0 * b2),
+                             g2 = kr * fma(bj0, b1, -bj1 * b0);
+                double w0 = 0.0, w1 = 0.0, w2 = 0.0;
+                // two sources per iteration: the second takes the first's far-end
+                // values and leaves its own where the first's near-end values were,
+                // so no register copy is made per source; while one is evaluated the
+                // record of the next is on its way
+                RunRec P, N;
+#pragma unroll
+                for (int i = 0; i < 7; ++i) P.p.v[i] = A.v[i];
+#pragma unroll
+                for (int i = 0; i < 3; ++i) P.c.v[i] = A.v[10 + i];
+                do {
+                    double r2, r2c;
+                    P.arrived();
+                    N.load(c + (k + 1) * (int64_t)RECA);
+                    __builtin_amdgcn_sched_barrier(0);
+                    pair_run_acc_f64(xq0, xq1, xq2, bj0, bj1, bj2, g0, g1, g2, P.p.v[0], P.p.v[1], P.p.v[2],
+                                     P.p.v[3], P.p.v[4], P.p.v[5], P.p.v[6], P.c.v[0], P.c.v[1], P.c.v[2], ikr,
+                                     nukr, r1, r1c, r2, r2c, a0, a1, a2, w0, w1, w2, ak);
+                    N.arrived();
+                    k += 2;
+                    P.load(c + min(k, n - 1) * (int64_t)RECA);
+                    __builtin_amdgcn_sched_barrier(0);
+                    pair_run_acc_f64(xq0, xq1, xq2, bj0, bj1, bj2, g0, g1, g2, N.p.v[0], N.p.v[1], N.p.v[2],
+                                     N.p.v[3], N.p.v[4], N.p.v[5], N.p.v[6], N.c.v[0], N.c.v[1], N.c.v[2], ikr,
+                                     nukr, r2, r2c, r1, r1c, a0, a1, a2, w0, w1, w2, ak);
+                    left -= 2;
+                } while (left >= 2);
+                A.load(c + min(k, n - 1) * (int64_t)RECA);
+                a0 = fma(-kr, fma(w1, b2, -w2 * b1), a0);
+                a1 = fma(-kr, fma(w2, b0, -w0 * b2), a1);
+                a2 = fma(-kr, fma(w0, b1, -w1 * b0), a2);
+                continue;
             }
-            a0 = fma(-kr, fma(w1, b2, -w2 * b1), a0);
-            a1 = fma(-kr, fma(w2, b0, -w0 * b2), a1);
-            a2 = fma(-kr, fma(w0, b1, -w1 * b0), a2);
         }
-        for (; k < n; ++k, c += RECA) {
-            double r2, r2c;
-            if (SELF) {
-                double n0 = a0, n1 = a1, n2 = a2, nk = ak;
-                pair_acc_f64(xq0, xq1, xq2, bj0, bj1, bj2, c[0], c[1], c[2], c[3], c[4], c[5], c[6],
-                             c[7], c[8], c[9], c[10], c[11], c[12], kr, nu, r1, r1c, r2, r2c, n0, n1,
-                             n2, nk);
-                const bool self = m + k == j;
-                a0 = self ? a0 : n0;
-                a1 = self ? a1 : n1;
-                a2 = self ? a2 : n2;
-                ak = self ? ak : nk;
-            } else {
-                pair_acc_f64(xq0, xq1, xq2, bj0, bj1, bj2, c[0], c[1], c[2], c[3], c[4], c[5], c[6],
-                             c[7], c[8], c[9], c[10], c[11], c[12], kr, nu, r1, r1c, r2, r2c, a0, a1,
-                             a2, ak);
-            }
-            r1 = r2;
-            r1c = r2c;
+        double r2, r2c;
+        RecWords<0, 14> B;
+        B.load(c + min(k + 1, n - 1) * (int64_t)RECA);
+        __builtin_amdgcn_sched_barrier(0);
+        if (SELF) {
+            double n0 = a0, n1 = a1, n2 = a2, nk = ak;
+            pair_acc_f64(xq0, xq1, xq2, bj0, bj1, bj2, A.v[0], A.v[1], A.v[2], A.v[3], A.v[4], A.v[5], A.v[6],
+                         A.v[7], A.v[8], A.v[9], A.v[10], A.v[11], A.v[12], kr, nu, r1, r1c, r2, r2c, n0, n1, n2,
+                         nk);
+            const bool self = k == own;
+            a0 = self ? a0 : n0;
+            a1 = self ? a1 : n1;
+            a2 = self ? a2 : n2;
+            ak = self ? ak : nk;
+        } else {
+            pair_acc_f64(xq0, xq1, xq2, bj0, bj1, bj2, A.v[0], A.v[1], A.v[2], A.v[3], A.v[4], A.v[5], A.v[6],
+                         A.v[7], A.v[8], A.v[9], A.v[10], A.v[11], A.v[12], kr, nu, r1, r1c, r2, r2c, a0, a1, a2,
+                         ak);
         }
-        m += n;
+        r1 = r2;
+        r1c = r2c;
+        B.arrived();
+        A = B;
+        ++k;
+        --left;
     }
 }
 
