@@ -1963,12 +1963,16 @@ int setup(Workspace *ws, hipStream_t st, const std::vector<int64_t> &seg_off_h, 
         if ((rc = ensure(ws, WS_NEAR_SPH, sizeof(float4) * ((ns + NEAR_GROUP - 1) / NEAR_GROUP), &p))) return rc;
         N.sph = (float4 *)p;
         // split the source range of an instance over several workgroups when
-        // the targets alone give fewer than ~4096 wavefronts: at least 64
-        // source groups per split, at most 32 splits
+        // the targets alone give fewer than ~4096 wavefronts: at least 8
+        // source groups per split, at most 32 splits.  A search is a serial
+        // pass over its split's groups, so that few long splits leave the
+        // device idle: 1,107 shuffled segments take 56 + 64 us (count, list) in
+        // 3 splits of 64 groups and 13 + 15 us in 18 of 8; from 4,096 segments
+        // on the limit of 32 or the number of wavefronts decides as before.
         int64_t max_inst = 0;
         for (size_t i = 0; i + 1 < seg_off_h.size(); ++i) max_inst = std::max(max_inst, seg_off_h[i + 1] - seg_off_h[i]);
         const int64_t groups = (max_inst + NEAR_GROUP - 1) / NEAR_GROUP;
-        const int64_t want = std::min<int64_t>((groups + 63) / 64, (262144 + ns - 1) / ns);
+        const int64_t want = std::min<int64_t>((groups + 7) / 8, (262144 + ns - 1) / ns);
         N.splits = (int)std::min<int64_t>(32, std::max<int64_t>(1, want));
         // counts: scnt [ns][splits] and cnt [ns] (int32), then loc and ptr [ns] (int64)
         if ((rc = ensure(ws, WS_NEAR_IDX, sizeof(int32_t) * (1 + N.splits) * ns + 2 * sizeof(int64_t) * ns + 16, &p)))

@@ -213,7 +213,7 @@ __global__ __launch_bounds__(256) void k_near_list(NearArgs A)
         }
         // the keys of the chunk's sources, coalesced
         const int64_t kbase = 4 * gc * NEAR_GROUP, kend = 4 * A.ns;
-        for (int q = tid; q < 4 * NEAR_GROUP * NEAR_CHUNK; q += 256)
+        for (int q = tid; q < 4 * NEAR_GROUP * n_here; q += 256)
             shk[q] = kbase + q < kend ? A.key[kbase + q] : 0.0;
         __syncthreads();
         // four spheres per round (independent tests); entries past n_here hold
