@@ -252,6 +252,98 @@ __global__ __launch_bounds__(PREP_BLOCK) void k_seg_prep(PrepArgs A)
 }
 
 // ------------------------------------------- node -> (segment, end) lists --
+// The lists of every instance that fits LDS in one launch: one workgroup per
+// instance counts, scans and fills them there, ranks each entry within its
+// node's list (so that every later gather sums in a fixed order, whatever the
+// order of the atomics) and writes them out.  LDS holds a count per node and two
+// entries per segment: CSR_WORDS words (64 KB) of them.  An instance's entries start at twice its first segment; segments with bad indices are
+// attached to nothing and leave entries of -1 at the end, which readers skip.
+// Bound by latency: what it saves is launches (fill, count, scan, fill, sort)
+// and the insertion sort of long lists in global memory.  Sixteen volumes of
+// 256 to 768 segments and 16 free slots (whose two dummy nodes hold up to 16
+// entries): 41 -> 4.8 us; one volume of 1,107 segments 13 -> 5.0 us.
+// The limit: a step of one volume of 2,048 segments 51.3 -> 46.6 us, of 5,440
+// (all of the LDS) 162.3 -> 159.4 us; with 152 KB of LDS 8,192 segments took 279.3
+// us against 278.8, 12,800 took 621 to 626 against 616 to 620.
+constexpr int CSR_THREADS = 1024;
+constexpr int CSR_WORDS = 16 * 1024;
+
+__global__ __launch_bounds__(CSR_THREADS) void k_csr_block(Layout L, const int32_t *__restrict__ seg_nodes,
+                                                           int32_t *__restrict__ ptr, int32_t *__restrict__ list)
+{
+    __shared__ int32_t sh[CSR_WORDS];
+    __shared__ int32_t wsum[CSR_THREADS / 64];
+    const int inst = blockIdx.x, tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    const int64_t n0 = node_begin(L, inst), s0 = seg_begin(L, inst);
+    const int n_n = (int)node_count(L, inst);
+    const int n_s = (int)((L.seg_off ? L.seg_off[inst + 1] : L.ns) - s0);
+    int32_t *cur = sh, *lst = sh + n_n;
+    for (int i = tid; i < n_n; i += CSR_THREADS) cur[i] = 0;
+    __syncthreads();
+    for (int q = tid; q < n_s; q += CSR_THREADS) {
+        const uint32_t i1 = seg_nodes[s0 + q], i2 = seg_nodes[L.ns + s0 + q];
+        if (i1 >= (uint32_t)n_n || i2 >= (uint32_t)n_n) continue;
+        atomicAdd(&cur[i1], 1);
+        atomicAdd(&cur[i2], 1);
+    }
+    __syncthreads();
+    // exclusive scan, four counts per thread and round
+    int32_t total = 0;
+    for (int base = 0; base < n_n; base += 4 * CSR_THREADS) {
+        const int i0 = base + 4 * tid;
+        int32_t v[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) v[k] = i0 + k < n_n ? cur[i0 + k] : 0;
+        const int32_t t = v[0] + v[1] + v[2] + v[3];
+        int32_t incl = t;
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) {
+            const int32_t u = __shfl_up(incl, off, 64);
+            if (lane >= off) incl += u;
+        }
+        if (lane == 63) wsum[w] = incl;
+        __syncthreads();
+        int32_t run = total + incl - t;
+#pragma unroll
+        for (int k = 0; k < CSR_THREADS / 64; ++k) {
+            run += k < w ? wsum[k] : 0;
+            total += wsum[k];
+        }
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+            if (i0 + k < n_n) {
+                cur[i0 + k] = run;
+                ptr[n0 + i0 + k] = (int32_t)(2 * s0) + run;
+                run += v[k];
+            }
+        __syncthreads();
+    }
+    for (int k = total + tid; k < 2 * n_s; k += CSR_THREADS) lst[k] = -1;
+    for (int q = tid; q < n_s; q += CSR_THREADS) {
+        const uint32_t i1 = seg_nodes[s0 + q], i2 = seg_nodes[L.ns + s0 + q];
+        if (i1 >= (uint32_t)n_n || i2 >= (uint32_t)n_n) continue;
+        lst[atomicAdd(&cur[i1], 1)] = 2 * q;
+        lst[atomicAdd(&cur[i2], 1)] = 2 * q + 1;
+    }
+    __syncthreads();
+    // cur[i] is now the end of node i's list
+    for (int k = tid; k < 2 * n_s; k += CSR_THREADS) {
+        const int32_t v = lst[k];
+        if (v < 0) {
+            list[2 * s0 + k] = -1;
+            continue;
+        }
+        const int32_t i = seg_nodes[(v & 1) * L.ns + s0 + (v >> 1)];
+        const int32_t b = i > 0 ? cur[i - 1] : 0, e = cur[i];
+        int32_t rank = b;
+        for (int32_t m = b; m < e; ++m) rank += lst[m] < v;
+        list[2 * s0 + rank] = (int32_t)(2 * s0) + v;
+    }
+    if (tid == 0 && inst == (int)gridDim.x - 1) ptr[L.nn] = (int32_t)(2 * L.ns);
+}
+
+// Larger instances: a launch each for the counts, their scan, the entries and
+// the order.
 __global__ void k_csr_count(Layout L, const int32_t *seg_nodes, int32_t *cnt)
 {
     int64_t s = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
@@ -376,6 +468,7 @@ __global__ void k_node_gather(const int32_t *__restrict__ ptr, const int32_t *__
     double f0 = 0, f1 = 0, f2 = 0;
     for (int32_t k = ptr[n]; k < ptr[n + 1]; ++k) {
         const int32_t e = list[k];
+        if (e < 0) continue;
         const int64_t s = e >> 1;
         const int end = e & 1;
         f0 += segF[(3 * end + 0) * ns + s];
@@ -447,11 +540,13 @@ __global__ void k_glide(Layout L, const int32_t *__restrict__ ptr, const int32_t
     const int64_t nn = L.nn, ns = L.ns;
     if (n >= nn) return;
     // nodes of an idle instance (active[instance] == 0) do not move
-    const bool idle = active && ptr[n + 1] > ptr[n] && !active[seg_instance(L, list[ptr[n]] >> 1)];
+    const bool idle = active && ptr[n + 1] > ptr[n] && list[ptr[n]] >= 0 &&
+                      !active[seg_instance(L, list[ptr[n]] >> 1)];
     double ell = 0.0;
     double nrm[3][3];
     int cnt = 0;
     for (int32_t k = ptr[n]; k < ptr[n + 1]; ++k) {
+        if (list[k] < 0) continue;
         const int64_t s = list[k] >> 1;
         double Ls;
         if (FROM_REC) {
@@ -1839,6 +1934,8 @@ struct ForceCtx {
     double *segF = nullptr;
     int32_t *csr_ptr = nullptr, *csr_list = nullptr, *csr_cnt = nullptr;
     int32_t *scan_tmp = nullptr;   // scratch of the node-list scan (after csr_cnt)
+    int n_inst = 1;                // instances of a batch, and the most words the node lists of one
+    int64_t csr_words = -1;        // need (nodes + twice its segments); -1: one instance, from its sizes
     Tile *tiles = nullptr;
     Item *items = nullptr;
     int64_t n_items = 0, range = 0;   // work items and their longest source range
@@ -2040,10 +2137,25 @@ int size_near_pairs(ForceCtx &C, Workspace *ws, const double *x, const int32_t *
                                                     (int64_t)(factor * (double)total) + extra * C.L.ns));
 }
 
+// The instances of a batch, for launch_csr.
+void note_instances(ForceCtx &C, const std::vector<int64_t> &no, const std::vector<int64_t> &so)
+{
+    C.n_inst = (int)no.size() - 1;
+    C.csr_words = 0;
+    for (int i = 0; i < C.n_inst; ++i)
+        C.csr_words = std::max(C.csr_words, no[i + 1] - no[i] + 2 * (so[i + 1] - so[i]));
+}
+
 // Topology-only work: CSR of node -> (segment, end).
 void launch_csr(const ForceCtx &C, const int32_t *seg_nodes, hipStream_t st)
 {
     const int64_t nn = C.L.nn, ns = C.L.ns;
+    const int64_t words = C.csr_words >= 0 ? C.csr_words : nn + 2 * ns;
+    if (words <= CSR_WORDS) {
+        hipLaunchKernelGGL(k_csr_block, dim3(C.n_inst), dim3(CSR_THREADS), 0, st, C.L, seg_nodes, C.csr_ptr,
+                           C.csr_list);
+        return;
+    }
     hipLaunchKernelGGL(k_fill_u32, dim3(grid_for(nn)), dim3(256), 0, st, (unsigned *)C.csr_cnt, nn, 0u);
     hipLaunchKernelGGL(k_csr_count, dim3(grid_for(ns, 256, INT32_MAX)), dim3(256), 0, st, C.L, seg_nodes,
                        C.csr_cnt);
@@ -2546,6 +2658,7 @@ int burst_batch_run(const BurstBatch &B, const std::vector<uint8_t> &active, con
     double *vel = (double *)p;
     if ((rc = ensure(ws, WS_FORCE, sizeof(double) * 3 * std::max<int64_t>(nn, 1), &p))) return rc;
     double *F = (double *)p;
+    note_instances(C, B.node_off, B.seg_off);
     launch_csr(C, B.seg_nodes, st);
     uint8_t *held = nullptr;
     JunctionArgs J{};
@@ -2982,6 +3095,7 @@ int burst_graph(Workspace *ws, const Layout &inst, int32_t n_inst, const std::ve
     if (jnodes && (rc = jnode_prepare(ws, C.L, seg_nodes, x, pinned, jnodes, JN, st))) return rc;
     JN.t0 = t0_dev;
 
+    note_instances(C, no, so);
     launch_csr(C, seg_nodes, st);
     hipLaunchKernelGGL(k_fill_f64, dim3(grid_for(12 * (int64_t)n_inst)), dim3(256), 0, st, rate_avg_out,
                        12 * (int64_t)n_inst, 0.0);
