@@ -149,19 +149,17 @@ int ensure(Workspace *ws, Slot s, size_t bytes, void **out);
 __host__ __device__ inline void fcc(int alpha, double n[3], double m[3])
 {
     const double r3 = 0.57735026918962576451, r2 = 0.70710678118654752440;
-    // plane normals
-    const signed char P[4][3] = {{1, 1, 1}, {-1, 1, 1}, {1, -1, 1}, {1, 1, -1}};
-    // directions, per plane: zero x, zero y, zero z
-    const signed char D[4][3][3] = {
-        {{0, 1, -1}, {1, 0, -1}, {1, -1, 0}},
-        {{0, 1, -1}, {1, 0, 1}, {1, 1, 0}},
-        {{0, 1, 1}, {1, 0, -1}, {1, 1, 0}},
-        {{0, 1, 1}, {1, 0, 1}, {1, -1, 0}},
-    };
-    const int p = alpha / 3, d = alpha % 3;
+    // plane normals {1,1,1}, {-1,1,1}, {1,-1,1}, {1,1,-1} and their directions,
+    // {0,1,-1}, {1,0,-1}, {1,-1,0}; {0,1,-1}, {1,0,1}, {1,1,0};
+    // {0,1,1}, {1,0,-1}, {1,1,0}; {0,1,1}, {1,0,1}, {1,-1,0}, packed as component
+    // + 1 in two bits each (an indexed table would be built in scratch memory
+    // by every thread that reads it)
+    const int p = alpha / 3;
+    const unsigned pn = 0x2a2a2au >> (6 * p);
+    const unsigned dm = (unsigned)((alpha < 6 ? 0x6a6252189ull : 0x4a6a5a1a9ull) >> (6 * (alpha % 6)));
     for (int k = 0; k < 3; ++k) {
-        n[k] = P[p][k] * r3;
-        m[k] = D[p][d][k] * r2;
+        n[k] = ((int)(pn >> (2 * k) & 3u) - 1) * r3;
+        m[k] = ((int)(dm >> (2 * k) & 3u) - 1) * r2;
     }
 }
 

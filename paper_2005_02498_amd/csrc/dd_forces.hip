@@ -160,7 +160,7 @@ __global__ __launch_bounds__(PREP_BLOCK) void k_seg_prep(PrepArgs A)
 {
     __shared__ int64_t sh_g1[PREP_BLOCK], sh_g2[PREP_BLOCK];
     __shared__ int sh_inst[PREP_BLOCK];
-    __shared__ unsigned char sh_chain[PREP_BLOCK];
+    __shared__ unsigned long long sh_chain[PREP_BLOCK / 64];   // a bit per segment
     const int tid = threadIdx.x;
     const int64_t s = blockIdx.x * (int64_t)PREP_BLOCK + tid;
     const int64_t ns = A.L.ns, nn = A.L.nn;
@@ -181,7 +181,8 @@ __global__ __launch_bounds__(PREP_BLOCK) void k_seg_prep(PrepArgs A)
     bool chain = live && tid + 1 < PREP_BLOCK && sh_inst[tid + 1] == inst && sh_g1[tid + 1] == g2;
     if (chain)
         for (int k = 0; k < 3; ++k) chain = chain && A.burgers[k * ns + s + 1] == A.burgers[k * ns + s];
-    sh_chain[tid] = chain;
+    const unsigned long long chains = __ballot(chain);
+    if ((tid & 63) == 0) sh_chain[tid >> 6] = chains;
     __syncthreads();
     if (!live) return;
     double rr[13];
@@ -203,8 +204,17 @@ __global__ __launch_bounds__(PREP_BLOCK) void k_seg_prep(PrepArgs A)
     // vector (loops stored in order), within this workgroup's segments: the
     // all-pairs kernel computes the inverse distance to a shared node, and the
     // products with the Burgers vector, once per run
+    // (the set bits from this segment's on; walking them one by one took half of
+    // the kernel's time for loops of 32 in order, 10.2 -> 7.4 us for 16 volumes
+    // of 256 to 768 segments)
     int run = 1;
-    while (tid + run < PREP_BLOCK && sh_chain[tid + run - 1]) ++run;
+    for (int k = tid; k < PREP_BLOCK;) {
+        const unsigned long long open = ~(sh_chain[k >> 6] >> (k & 63));   // zeros: chained
+        const int here = min(open ? __ffsll(open) - 1 : 64, 64 - (k & 63));
+        run += here;
+        k += here;
+        if ((k & 63) != 0 || here == 0) break;
+    }
     r[13 * ns + s] = (double)run;
     {
         double *ra = r + (int64_t)REC64 * ns + s * RECA;
@@ -256,8 +266,9 @@ __global__ __launch_bounds__(PREP_BLOCK) void k_seg_prep(PrepArgs A)
 // instance counts, scans and fills them there, ranks each entry within its
 // node's list (so that every later gather sums in a fixed order, whatever the
 // order of the atomics) and writes them out.  LDS holds a count per node and two
-// entries per segment: CSR_WORDS words (64 KB) of them.  An instance's entries start at twice its first segment; segments with bad indices are
-// attached to nothing and leave entries of -1 at the end, which readers skip.
+// entries per segment: CSR_WORDS words (64 KB) of them.  An instance's entries
+// start at twice its first segment; segments with bad indices are attached to
+// nothing and leave entries of -1 at the end, which readers skip.
 // Bound by latency: what it saves is launches (fill, count, scan, fill, sort)
 // and the insertion sort of long lists in global memory.  Sixteen volumes of
 // 256 to 768 segments and 16 free slots (whose two dummy nodes hold up to 16
@@ -1220,7 +1231,16 @@ __device__ __forceinline__ double seg_rate(const double *t, const double *b, dou
     return bm * Ls * (c0 * n[0] + c1 * n[1] + c2 * n[2]) * invV;
 }
 
-__global__ __launch_bounds__(256) void k_instance_sums(Layout L, int mode,
+//
+// Bound by latency (a chain of loads per segment, one workgroup per instance):
+// SUMS_AHEAD segments per thread are in flight, and the rows of the tree are
+// shared out over the wavefronts.  32 volumes of 256 to 2,048 segments 25.6 ->
+// 12.8 us, 16 of 256 to 768 14.2 -> 7.6 us (of which keeping the sums and the
+// slip-system table out of scratch memory 8 and 4 us).
+constexpr int SUMS_AHEAD = 4;
+
+template <int MODE>
+__global__ __launch_bounds__(256) void k_instance_sums(Layout L,
                                                        const int32_t *__restrict__ seg_nodes,
                                                        const double *__restrict__ rec,
                                                        const int32_t *__restrict__ sys,
@@ -1230,52 +1250,63 @@ __global__ __launch_bounds__(256) void k_instance_sums(Layout L, int mode,
                                                        const double *__restrict__ sig_dev,
                                                        double a, double *__restrict__ out)
 {
-    __shared__ double red[24][256];
+    constexpr int NV = MODE == 0 ? 12 : (MODE == 2 ? 13 : 24);
+    __shared__ double red[NV][256];
     const int inst = blockIdx.x;
     const int64_t s0 = L.seg_off ? L.seg_off[inst] : 0;
     const int64_t s1 = L.seg_off ? L.seg_off[inst + 1] : L.ns;
     const int64_t nn = L.nn, ns = L.ns;
     const double invV = 1.0 / volume[inst];
-    double acc[24];
-    for (int k = 0; k < 24; ++k) acc[k] = 0.0;
-    for (int64_t s = s0 + threadIdx.x; s < s1; s += blockDim.x) {
-        const int al = sys[s];
-        if (al < 0) continue;
-        double n[3], m[3];
-        fcc(al, n, m);
-        const double Ls = rec[6 * ns + s] * a;
-        if (mode == 2) acc[12] += Ls * invV;
-        if (mode == 0 || mode == 2) {
+    double acc[NV];
+    for (int k = 0; k < NV; ++k) acc[k] = 0.0;
+    // SUMS_AHEAD segments' loads, and then their nodes' velocities, in flight at a time
+    for (int64_t sf = s0 + threadIdx.x; sf < s1; sf += SUMS_AHEAD * blockDim.x) {
+        int al[SUMS_AHEAD];
+        double Ls[SUMS_AHEAD], val[SUMS_AHEAD];
+        bool ses[SUMS_AHEAD];
+#pragma unroll
+        for (int u = 0; u < SUMS_AHEAD; ++u) {
+            const int64_t su = sf + u * blockDim.x, s = su < s1 ? su : s1 - 1;
+            al[u] = su < s1 ? sys[s] : -1;
+            Ls[u] = rec[6 * ns + s] * a;
             int64_t g1, g2;
             seg_ends(L, seg_nodes, s, g1, g2);
-            const double t[3] = {rec[3 * ns + s], rec[4 * ns + s], rec[5 * ns + s]};
-            const double b[3] = {rec[7 * ns + s], rec[8 * ns + s], rec[9 * ns + s]};
-            const double val = seg_rate(t, b, Ls, vel, nn, g1, g2, n, m, a, invV);
-            for (int k = 0; k < 12; ++k)
-                if (k == al) acc[k] += val;
-        } else {
-            int64_t g1, g2;
-            seg_ends(L, seg_nodes, s, g1, g2);
-            const bool ses = pinned && pinned[g1] && pinned[g2];
-            for (int k = 0; k < 12; ++k)
-                if (k == al) {
-                    if (ses) acc[12 + k] += Ls * invV;
-                    else acc[k] += Ls * invV;
-                }
+            if (MODE != 1) {
+                double n[3], m[3];
+                fcc(al[u] < 0 ? 0 : al[u], n, m);
+                const double t[3] = {rec[3 * ns + s], rec[4 * ns + s], rec[5 * ns + s]};
+                const double b[3] = {rec[7 * ns + s], rec[8 * ns + s], rec[9 * ns + s]};
+                val[u] = seg_rate(t, b, Ls[u], vel, nn, g1, g2, n, m, a, invV);
+            } else {
+                ses[u] = pinned && pinned[g1] && pinned[g2];
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < SUMS_AHEAD; ++u) {
+            if (al[u] < 0) continue;
+            if (MODE == 2) acc[12] += Ls[u] * invV;
+            // (a select per sum: an indexed one would put the sums in scratch memory)
+            const int to = MODE == 1 && ses[u] ? 12 + al[u] : al[u];
+            const double v = MODE == 1 ? Ls[u] * invV : val[u];
+#pragma unroll
+            for (int k = 0; k < (MODE == 1 ? 24 : 12); ++k) acc[k] += k == to ? v : 0.0;
         }
     }
-    const int nv = mode == 0 ? 12 : (mode == 2 ? 13 : 24);
-    for (int k = 0; k < nv; ++k) red[k][threadIdx.x] = acc[k];
+    for (int k = 0; k < NV; ++k) red[k][threadIdx.x] = acc[k];
     __syncthreads();
-    for (int off = 128; off > 0; off >>= 1) {
-        if ((int)threadIdx.x < off)
-            for (int k = 0; k < nv; ++k) red[k][threadIdx.x] += red[k][threadIdx.x + off];
-        __syncthreads();
+    // each wavefront sums rows of 256: lane l and l + 128, l + 64, ... , l + 1
+    for (int k = threadIdx.x >> 6; k < NV; k += 4) {
+        const int l = threadIdx.x & 63;
+        double v = (red[k][l] + red[k][l + 128]) + (red[k][l + 64] + red[k][l + 192]);
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) v += __shfl_down(v, off, 64);
+        if (l == 0) red[k][0] = v;
     }
+    __syncthreads();
     if (threadIdx.x == 0) {
-        if (mode == 0) {
+        if (MODE == 0) {
             for (int k = 0; k < 12; ++k) out[12 * inst + k] += red[k][0];
-        } else if (mode == 2) {
+        } else if (MODE == 2) {
             for (int k = 0; k < 13; ++k) out[13 * inst + k] += red[k][0];
         } else {
             double S[3][3];
@@ -2704,7 +2735,7 @@ int burst_batch_run(const BurstBatch &B, const std::vector<uint8_t> &active, con
             hipLaunchKernelGGL(k_glide<true>, dim3(grid_for(nn, 256, INT32_MAX)), dim3(256), 0, cs, C.L,
                                C.csr_ptr, C.csr_list, B.seg_nodes, B.normal, C.rec64, C.a, B.x, F, B.pinned,
                                (const uint8_t *)held, (const uint8_t *)d_act, 1.0 / B.mat.B, B.dt, vel);
-            hipLaunchKernelGGL(k_instance_sums, dim3(n_inst), dim3(256), 0, cs, C.L, 2, B.seg_nodes, C.rec64,
+            hipLaunchKernelGGL(k_instance_sums<2>, dim3(n_inst), dim3(256), 0, cs, C.L, B.seg_nodes, C.rec64,
                                C.sys, vel, B.pinned, B.volume, sigma_dev, C.a, sums_dev);
         }
         return DD_OK;
@@ -3116,7 +3147,7 @@ int burst_graph(Workspace *ws, const Layout &inst, int32_t n_inst, const std::ve
         A.sys = C.sys;
         A.flags = ws->flags_dev;
         hipLaunchKernelGGL(k_seg_prep, dim3(grid_for(ns, PREP_BLOCK, INT32_MAX)), dim3(PREP_BLOCK), 0, st, A);
-        hipLaunchKernelGGL(k_instance_sums, dim3(n_inst), dim3(256), 0, st, C.L, 1, seg_nodes, C.rec64, C.sys,
+        hipLaunchKernelGGL(k_instance_sums<1>, dim3(n_inst), dim3(256), 0, st, C.L, seg_nodes, C.rec64, C.sys,
                            (const double *)nullptr, pinned, volume, sigma_app, C.a, features_out);
     } else if (features_out) {
         hipLaunchKernelGGL(k_fill_f64, dim3(grid_for(36 * (int64_t)n_inst)), dim3(256), 0, st, features_out,
@@ -3165,7 +3196,7 @@ int burst_graph(Workspace *ws, const Layout &inst, int32_t n_inst, const std::ve
                 hipLaunchKernelGGL(k_glide<true>, dim3(grid_for(nn, 256, INT32_MAX)), dim3(256), 0, cs, C.L,
                                    C.csr_ptr, C.csr_list, seg_nodes, normal, C.rec64, C.a, x, F, pinned,
                                    (const uint8_t *)held, (const uint8_t *)nullptr, 1.0 / m->B, dt, vel);
-                hipLaunchKernelGGL(k_instance_sums, dim3(n_inst), dim3(256), 0, cs, C.L, 0, seg_nodes, C.rec64,
+                hipLaunchKernelGGL(k_instance_sums<0>, dim3(n_inst), dim3(256), 0, cs, C.L, seg_nodes, C.rec64,
                                    C.sys, vel, pinned, volume, sigma_app, C.a, rate_avg_out);
             }
             return DD_OK;
@@ -3260,7 +3291,7 @@ int burst_batch_impl(int32_t n_inst, const int64_t *node_off, const int64_t *seg
                 A.sys = (int32_t *)p;
                 A.flags = ws->flags_dev;
                 hipLaunchKernelGGL(k_seg_prep, dim3(grid_for(ns, PREP_BLOCK, INT32_MAX)), dim3(PREP_BLOCK), 0, st, A);
-                hipLaunchKernelGGL(k_instance_sums, dim3(n_inst), dim3(256), 0, st, L, 1, seg_nodes, A.rec64, A.sys,
+                hipLaunchKernelGGL(k_instance_sums<1>, dim3(n_inst), dim3(256), 0, st, L, seg_nodes, A.rec64, A.sys,
                                    (const double *)nullptr, pinned, volume, sigma_app, m->a, features_out);
             }
             if ((rc = launch_persistent(ws, L, no, G, x, seg_nodes, burgers, normal, pinned, sigma_app, volume, m, n_gauss,
