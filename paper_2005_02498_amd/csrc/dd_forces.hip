@@ -469,7 +469,8 @@ __global__ void k_segment_ends(Layout L, const Tile *__restrict__ tiles,
     }
 }
 
-// F_n = sum over the node's (segment, end) list in sorted order.
+// F_n = sum over the node's (segment, end) list in sorted order (a force
+// evaluation by itself; a step gathers in k_glide).
 __global__ void k_node_gather(const int32_t *__restrict__ ptr, const int32_t *__restrict__ list,
                               int64_t nn, int64_t ns, const double *__restrict__ segF,
                               double *__restrict__ F)
@@ -536,14 +537,18 @@ __device__ __forceinline__ void glide_velocity(double F0, double F1, double F2, 
 
 // Per node: ell = 1/2 sum L_s over attached segments, v = P F / (B ell), with
 // P from the distinct slip-plane normals among them.  FROM_REC: lengths from
-// the segment records (x unchanged since they were made), so the node can be
-// advanced in the same pass; otherwise lengths come from x and the Euler
-// update is a separate kernel.
+// the segment records (x unchanged since they were made) and F gathered here
+// from their end forces (as k_node_gather does, in the same order; it is
+// written to F_out unless that is null), so that the node can be advanced in
+// the same pass; otherwise F is read, lengths come from x and the Euler update
+// is a separate kernel.  Bound by latency (list, then what its entries name):
+// gather and glide took 4.6 + 4.8 us as two launches for 36,000 nodes, 5.8 + 7.6 us
+// for 16 volumes whose dummy nodes have 16 entries; together 5.2 and 8.4 us.
 template <bool FROM_REC>
 __global__ void k_glide(Layout L, const int32_t *__restrict__ ptr, const int32_t *__restrict__ list,
                         const int32_t *__restrict__ seg_nodes, const double *__restrict__ normal,
-                        const double *__restrict__ rec, double a, double *x,
-                        const double *__restrict__ F, const uint8_t *__restrict__ pinned,
+                        const double *__restrict__ rec, const double *__restrict__ segF, double a, double *x,
+                        const double *__restrict__ F, double *__restrict__ F_out, const uint8_t *__restrict__ pinned,
                         const uint8_t *__restrict__ held, const uint8_t *__restrict__ active, double invB,
                         double dt, double *__restrict__ vel)
 {
@@ -553,27 +558,55 @@ __global__ void k_glide(Layout L, const int32_t *__restrict__ ptr, const int32_t
     // nodes of an idle instance (active[instance] == 0) do not move
     const bool idle = active && ptr[n + 1] > ptr[n] && list[ptr[n]] >= 0 &&
                       !active[seg_instance(L, list[ptr[n]] >> 1)];
-    double ell = 0.0;
+    double ell = 0.0, f0 = 0.0, f1 = 0.0, f2 = 0.0;
     double nrm[3][3];
     int cnt = 0;
-    for (int32_t k = ptr[n]; k < ptr[n + 1]; ++k) {
-        if (list[k] < 0) continue;
-        const int64_t s = list[k] >> 1;
-        double Ls;
-        if (FROM_REC) {
-            Ls = rec[6 * ns + s] * a;
-        } else {
-            int64_t g1, g2;
-            seg_ends(L, seg_nodes, s, g1, g2);
-            double d0 = x[g2] - x[g1], d1 = x[nn + g2] - x[nn + g1], d2 = x[2 * nn + g2] - x[2 * nn + g1];
-            Ls = sqrt(d0 * d0 + d1 * d1 + d2 * d2);
+    // two entries' loads in flight at a time (most nodes have two)
+    const int32_t kb = ptr[n], ke = ptr[n + 1];
+    for (int32_t k = kb; k < ke; k += 2) {
+        const int32_t en[2] = {list[k], k + 1 < ke ? list[k + 1] : -1};
+        double Ls[2], g[2][3], nv[2][3];
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            const int64_t s = en[u] < 0 ? 0 : en[u] >> 1;
+            if (FROM_REC) {
+                Ls[u] = rec[6 * ns + s] * a;
+                const int end = en[u] & 1;
+                for (int c = 0; c < 3; ++c) g[u][c] = segF[(3 * end + c) * ns + s];
+            } else {
+                int64_t g1, g2;
+                seg_ends(L, seg_nodes, s, g1, g2);
+                double d0 = x[g2] - x[g1], d1 = x[nn + g2] - x[nn + g1], d2 = x[2 * nn + g2] - x[2 * nn + g1];
+                Ls[u] = sqrt(d0 * d0 + d1 * d1 + d2 * d2);
+            }
+            for (int c = 0; c < 3; ++c) nv[u][c] = normal[c * ns + s];
         }
-        ell += 0.5 * Ls;
-        add_normal(normal[s], normal[ns + s], normal[2 * ns + s], nrm, cnt);
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            if (en[u] < 0) continue;
+            if (FROM_REC) {
+                f0 += g[u][0];
+                f1 += g[u][1];
+                f2 += g[u][2];
+            }
+            ell += 0.5 * Ls[u];
+            add_normal(nv[u][0], nv[u][1], nv[u][2], nrm, cnt);
+        }
     }
     double v0 = 0, v1 = 0, v2 = 0;
     const bool fixed = idle || (pinned && pinned[n]) || (held && held[n]) || !(ell > 0.0) || cnt == 0 || cnt >= 3;
-    if (!fixed) glide_velocity(F[n], F[nn + n], F[2 * nn + n], ell, invB, nrm, cnt, v0, v1, v2);
+    if (FROM_REC) {
+        if (F_out) {
+            F_out[n] = f0;
+            F_out[nn + n] = f1;
+            F_out[2 * nn + n] = f2;
+        }
+    } else if (!fixed) {
+        f0 = F[n];
+        f1 = F[nn + n];
+        f2 = F[2 * nn + n];
+    }
+    if (!fixed) glide_velocity(f0, f1, f2, ell, invB, nrm, cnt, v0, v1, v2);
     if (vel) {
         vel[n] = v0;
         vel[nn + n] = v1;
@@ -2214,7 +2247,8 @@ void launch_jnode_step(const ForceCtx &C, JNodeArgs J, double tk, int k, int n_i
 }
 
 
-// a1..a4 for positions x: segment records, pair kernel, epilogue, gather.
+// a1..a4 for positions x: segment records, pair kernel, epilogue, gather (left
+// to the glide kernel where F is null).
 // With the exact band, size_pairs = true counts the near pairs first, reads
 // the count back (one synchronisation) and sizes the pair store to fit;
 // false (graph capture) uses the store as sized beforehand.
@@ -2291,7 +2325,7 @@ int launch_forces(ForceCtx &C, Workspace *ws, const double *x, const int32_t *se
                            C.segF, C.near_on ? (const int64_t *)C.near.ptr : nullptr,
                            (const int32_t *)C.near.cnt, (const double *)C.near.corr, C.near.pair_cap);
     }
-    hipLaunchKernelGGL(k_node_gather, dim3(grid_for(nn, 256, INT32_MAX)), dim3(256), 0, st, C.csr_ptr,
+    if (F) hipLaunchKernelGGL(k_node_gather, dim3(grid_for(nn, 256, INT32_MAX)), dim3(256), 0, st, C.csr_ptr,
                        C.csr_list, nn, ns, C.segF, F);
     return DD_OK;
 }
@@ -2687,8 +2721,6 @@ int burst_batch_run(const BurstBatch &B, const std::vector<uint8_t> &active, con
     void *p;
     if ((rc = ensure(ws, WS_VEL, sizeof(double) * 3 * std::max<int64_t>(nn, 1), &p))) return rc;
     double *vel = (double *)p;
-    if ((rc = ensure(ws, WS_FORCE, sizeof(double) * 3 * std::max<int64_t>(nn, 1), &p))) return rc;
-    double *F = (double *)p;
     note_instances(C, B.node_off, B.seg_off);
     launch_csr(C, B.seg_nodes, st);
     uint8_t *held = nullptr;
@@ -2730,10 +2762,11 @@ int burst_batch_run(const BurstBatch &B, const std::vector<uint8_t> &active, con
                 hipLaunchKernelGGL(k_junctions, dim3(grid_for(nn, 256, INT32_MAX)), dim3(256), 0, cs, C.L,
                                    B.seg_nodes, (const double *)B.x, B.pinned, J, n_inst, (const uint8_t *)d_act,
                                    B.fast_steps_dev, B.dt, k, held);
-            const int r = launch_forces(C, ws, B.x, B.seg_nodes, B.burgers, B.normal, sigma_dev, sv, F, cs, false);
+            const int r = launch_forces(C, ws, B.x, B.seg_nodes, B.burgers, B.normal, sigma_dev, sv, nullptr, cs, false);
             if (r) return r;
             hipLaunchKernelGGL(k_glide<true>, dim3(grid_for(nn, 256, INT32_MAX)), dim3(256), 0, cs, C.L,
-                               C.csr_ptr, C.csr_list, B.seg_nodes, B.normal, C.rec64, C.a, B.x, F, B.pinned,
+                               C.csr_ptr, C.csr_list, B.seg_nodes, B.normal, (const double *)C.rec64,
+                               (const double *)C.segF, C.a, B.x, (const double *)nullptr, (double *)nullptr, B.pinned,
                                (const uint8_t *)held, (const uint8_t *)d_act, 1.0 / B.mat.B, B.dt, vel);
             hipLaunchKernelGGL(k_instance_sums<2>, dim3(n_inst), dim3(256), 0, cs, C.L, B.seg_nodes, C.rec64,
                                C.sys, vel, B.pinned, B.volume, sigma_dev, C.a, sums_dev);
@@ -2890,8 +2923,8 @@ extern "C" int dd_glide_step(int64_t n_nodes, double *x, const double *force, in
         hipLaunchKernelGGL(k_seg_prep, dim3(grid_for(n_segs, PREP_BLOCK, INT32_MAX)), dim3(PREP_BLOCK), 0, st, A);
     }
     hipLaunchKernelGGL(k_glide<false>, dim3(grid_for(n_nodes, 256, INT32_MAX)), dim3(256), 0, st, L,
-                       C.csr_ptr, C.csr_list, seg_nodes, normal, (const double *)nullptr, 1.0, x, force,
-                       pinned, (const uint8_t *)nullptr, (const uint8_t *)nullptr, 1.0 / m->B, dt, vel);
+                       C.csr_ptr, C.csr_list, seg_nodes, normal, (const double *)nullptr, (const double *)nullptr, 1.0, x,
+                       force, (double *)nullptr, pinned, (const uint8_t *)nullptr, (const uint8_t *)nullptr, 1.0 / m->B, dt, vel);
     hipLaunchKernelGGL(k_euler, dim3(grid_for(3 * n_nodes, 256, INT32_MAX)), dim3(256), 0, st, n_nodes, x,
                        vel, dt);
     DD_HIP(hipGetLastError());
@@ -2955,11 +2988,11 @@ extern "C" int dd_step(int64_t n_nodes, double *x, int64_t n_segs, const int32_t
         C.variant = (int)(choice % MIXED_VARIANTS);
         g_last_variant = C.variant;
         launch_csr(C, seg_nodes, st);
-        if ((rc = launch_forces(C, ws, x, seg_nodes, burgers, normal, nullptr, sv, F, st, true))) return rc;
-        // lengths from the segment records of this force pass: x can move in the same kernel
+        if ((rc = launch_forces(C, ws, x, seg_nodes, burgers, normal, nullptr, sv, nullptr, st, true))) return rc;
+        // forces and lengths from the end forces and records of this force pass: x can move in the same kernel
         hipLaunchKernelGGL(k_glide<true>, dim3(grid_for(n_nodes, 256, INT32_MAX)), dim3(256), 0, st, C.L, C.csr_ptr,
-                           C.csr_list, seg_nodes, normal, (const double *)C.rec64, C.a, x, (const double *)F, pinned,
-                           (const uint8_t *)nullptr, (const uint8_t *)nullptr, 1.0 / m->B, dt, vel);
+                           C.csr_list, seg_nodes, normal, (const double *)C.rec64, (const double *)C.segF, C.a, x,
+                           (const double *)nullptr, F, pinned, (const uint8_t *)nullptr, (const uint8_t *)nullptr, 1.0 / m->B, dt, vel);
     }
     DD_HIP(hipGetLastError());
     if (validation_on()) {
@@ -3114,8 +3147,6 @@ int burst_graph(Workspace *ws, const Layout &inst, int32_t n_inst, const std::ve
     C.L.tile_begin = (const int64_t *)ws->ptr[WS_OFFS];
     if ((rc = ensure(ws, WS_VEL, sizeof(double) * 3 * std::max<int64_t>(nn, 1), &p))) return rc;
     double *vel = (double *)p;
-    if ((rc = ensure(ws, WS_FORCE, sizeof(double) * 3 * std::max<int64_t>(nn, 1), &p))) return rc;
-    double *F = (double *)p;
     uint8_t *held = nullptr;
     if ((rc = ensure(ws, WS_T0, sizeof(double), &p))) return rc;
     double *t0_dev = (double *)p;
@@ -3191,10 +3222,11 @@ int burst_graph(Workspace *ws, const Layout &inst, int32_t n_inst, const std::ve
                                        seg_nodes, (const double *)x, pinned, J, n_inst, (const uint8_t *)nullptr,
                                        (const int64_t *)nullptr, dt, k, held);
                 }
-                const int r = launch_forces(C, ws, x, seg_nodes, burgers, normal, sigma_app, sv, F, cs, false);
+                const int r = launch_forces(C, ws, x, seg_nodes, burgers, normal, sigma_app, sv, nullptr, cs, false);
                 if (r) return r;
                 hipLaunchKernelGGL(k_glide<true>, dim3(grid_for(nn, 256, INT32_MAX)), dim3(256), 0, cs, C.L,
-                                   C.csr_ptr, C.csr_list, seg_nodes, normal, C.rec64, C.a, x, F, pinned,
+                                   C.csr_ptr, C.csr_list, seg_nodes, normal, (const double *)C.rec64,
+                                   (const double *)C.segF, C.a, x, (const double *)nullptr, (double *)nullptr, pinned,
                                    (const uint8_t *)held, (const uint8_t *)nullptr, 1.0 / m->B, dt, vel);
                 hipLaunchKernelGGL(k_instance_sums<0>, dim3(n_inst), dim3(256), 0, cs, C.L, seg_nodes, C.rec64,
                                    C.sys, vel, pinned, volume, sigma_app, C.a, rate_avg_out);
