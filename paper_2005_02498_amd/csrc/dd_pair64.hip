@@ -32,7 +32,10 @@ namespace dd {
 // when it is needed) and now: a step of 1,024 segments 60.0 and 52.6 us, of
 // 1,107 shuffled ones with close pairs exact 246 and 220 us, 64 volumes of 256
 // segments 76 and 69 us per step, 4,096 shuffled segments 180 and 167 us;
-// 16,384 segments 1.39 ms as before.
+// 16,384 segments 1.39 ms as before.  What is left there is the first wavefront's
+// wait for each record to come into the L2: every lane asks for one of the range
+// at once, a step of 1,024 segments 39.3 -> 36.3 us (with the wavefronts past a
+// tile's end gone and the self test kept to a wavefront's own segments).
 //
 // Runs of fewer than RUN_MIN sources take the form that needs no set-up: the
 // run form costs 15 instructions per run and saves 7 per source.
@@ -172,8 +175,15 @@ __global__ __launch_bounds__(TILE) void k_pair64(const Item *__restrict__ items,
                                                  double *__restrict__ partial)
 {
     const Item it = items[blockIdx.x];
-    const Tile tl = tiles[it.tile];
     const int lane = threadIdx.x;
+    const int64_t b = it.src_begin, e = it.src_end;
+    // a load per lane brings the first TILE records of the range into the L2 while
+    // the rest is set up (the wavefronts read them one by one, and the first to
+    // do so would wait for each)
+    const double ahead = ra[min(b + lane, e - 1) * RECA];
+    const Tile tl = tiles[it.tile];
+    const int w0 = __builtin_amdgcn_readfirstlane(lane & ~63);   // the wavefront's first point
+    if (w0 >= tl.n_points) return;   // none of them in the tile
     const bool valid = lane < tl.n_points;
     const int64_t p = tl.point_begin + (valid ? lane : 0);
     const int Q = g.n;
@@ -189,13 +199,13 @@ __global__ __launch_bounds__(TILE) void k_pair64(const Item *__restrict__ items,
     const double bj0 = rec[7 * ns + j], bj1 = rec[8 * ns + j], bj2 = rec[9 * ns + j];
     double a0 = 0.0, a1 = 0.0, a2 = 0.0, ak = 0.0;
 
-    // the tile's own segments [jlo, jhi] split the range in three parts
-    const int64_t jlo = tl.point_begin / Q, jhi = (tl.point_begin + tl.n_points - 1) / Q;
-    const int64_t b = it.src_begin, e = it.src_end;
+    // the wavefront's own segments [jlo, jhi] split the range in three parts
+    const int64_t jlo = (tl.point_begin + w0) / Q, jhi = (tl.point_begin + min(w0 + 63, (int)tl.n_points - 1)) / Q;
     const int64_t s0 = min(max(b, jlo), e), s1 = min(max(b, jhi + 1), e);
     pair64_range<false>(ra, b, s0, j, xq0, xq1, xq2, bj0, bj1, bj2, kr, nu, ikr, nukr, a0, a1, a2, ak);
     pair64_range<true>(ra, s0, s1, j, xq0, xq1, xq2, bj0, bj1, bj2, kr, nu, ikr, nukr, a0, a1, a2, ak);
     pair64_range<false>(ra, s1, e, j, xq0, xq1, xq2, bj0, bj1, bj2, kr, nu, ikr, nukr, a0, a1, a2, ak);
+    asm volatile("" : : "v"(ahead));
     a0 = fma(ak, bj0, a0);   // the b_j terms of every source at once
     a1 = fma(ak, bj1, a1);
     a2 = fma(ak, bj2, a2);
