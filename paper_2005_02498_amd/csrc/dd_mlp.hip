@@ -39,11 +39,17 @@ __device__ __forceinline__ float from_bf16(__bf16 v) { return __bfloat162float(v
 // C[m][n] = sum_k A(m, k) B(n, k) for one ensemble member (blockIdx.z):
 //   A(m, k) = TA ? A[k lda + m] : A[m lda + k]      (bf16)
 //   B(n, k) = TB ? B[k ldb + n] : B[n ldb + k]      (bf16)
-// Workgroup tile 64 x 64, K step 32, four waves in a 2 x 2 arrangement each
+// Workgroup tile 64 x 64, K steps of 32 staged through LDS four at a time
+// (a slab), the next slab's loads in flight meanwhile; four waves in a 2 x 2 arrangement each
 // owning 32 x 32 = 2 x 2 tiles of v_mfma_f32_16x16x32_bf16.  Operand layout
 // of that instruction: lane l holds row (A) / column (B) l % 16 and the eight
 // k values 8 (l / 16) .. 8 (l / 16) + 7; the accumulator holds column l % 16,
 // rows 4 (l / 16) .. 4 (l / 16) + 3.
+//
+// Bound by latency: a mini-batch of 1,024 rows gives each of four members 64
+// workgroups, and a K of 256 is eight steps.  With one step staged at a time the
+// wait for its loads was paid eight times, 9.2 us for a hidden layer; in two slabs
+// 5.9 us.  The steps enter the accumulators in the same order.
 enum Epi {
     EPI_BIAS_RELU_BF16 = 0,   // out_h = bf16(relu(acc + bias))
     EPI_BIAS_F32 = 1,         // out_f = acc + bias
@@ -65,7 +71,8 @@ struct GemmArgs {
     int kc, nsp; int64_t ssplit;
 };
 
-constexpr int BM = 64, BN = 64, BK = 32, LDSK = BK + 8;
+constexpr int BM = 64, BN = 64, BK = 32, SLAB = 4 * BK, LDSK = SLAB + 8;
+constexpr int LOADS = SLAB * BM / (8 * 256);   // 16-byte loads per thread and operand of a slab
 
 // Eight consecutive bf16 of a row of P (elements c .. c + 7 of row `row`,
 // leading dimension ld), zero where c + i >= lim or the row is out of range:
@@ -85,41 +92,49 @@ __device__ __forceinline__ bf16x8 load8(const __bf16 *P, int64_t ld, int row, bo
     return v;
 }
 
-template <bool TA, bool TB>
-__device__ __forceinline__ void stage(const GemmArgs &g, int member, int m0, int n0, int k0, int ke,
-                                      __bf16 (*As)[LDSK], __bf16 (*Bs)[LDSK])
+// A thread's part of one operand's slab (k0 .. k0 + SLAB - 1 of rows r0 .. r0 +
+// 63), zero from ke on.  T = false, rows of k: eight k of row t / 16 + 16 u.  T =
+// true, rows of m or n: eight of the k rows 2 (t / 8 + 32 (u / 2)) + u % 2.
+template <bool T>
+__device__ __forceinline__ void slab_load(const __bf16 *P, int64_t ld, int r0, int nrows, int k0, int ke,
+                                          bf16x8 (&v)[LOADS])
 {
     const int t = threadIdx.x;
-    const __bf16 *A = g.A + member * g.sA;
-    const __bf16 *B = g.B + member * g.sB;
-    if (!TA) {   // row r, k offset 8 (t % 4): eight k of one row
-        const int r = t / 4, kk = (t % 4) * 8, m = m0 + r;
-        const bf16x8 v = load8(A, g.lda, m, m < g.M, k0 + kk, ke);
 #pragma unroll
-        for (int i = 0; i < 8; ++i) As[r][kk + i] = v[i];
-    } else {     // k row t / 8, m offset 8 (t % 8): eight m of one k row, stored transposed
-        const int kr = t / 8, mm = (t % 8) * 8, k = k0 + kr;
-        const bf16x8 v = load8(A, g.lda, k, k < ke, m0 + mm, g.M);
-#pragma unroll
-        for (int i = 0; i < 8; ++i) As[mm + i][kr] = v[i];
+    for (int u = 0; u < LOADS; ++u) {
+        if (!T) {
+            const int r = r0 + t / 16 + 16 * u;
+            v[u] = load8(P, ld, r, r < nrows, k0 + (t % 16) * 8, ke);
+        } else {
+            const int k = k0 + 2 * (t / 8 + 32 * (u / 2)) + u % 2;
+            v[u] = load8(P, ld, k, k < ke, r0 + (t % 8) * 8, nrows);
+        }
     }
-    if (!TB) {
-        const int r = t / 4, kk = (t % 4) * 8, n = n0 + r;
-        const bf16x8 v = load8(B, g.ldb, n, n < g.N, k0 + kk, ke);
+}
+
+template <bool T>
+__device__ __forceinline__ void slab_store(const bf16x8 (&v)[LOADS], __bf16 (*S)[LDSK])
+{
+    const int t = threadIdx.x;
 #pragma unroll
-        for (int i = 0; i < 8; ++i) Bs[r][kk + i] = v[i];
-    } else {
-        const int kr = t / 8, nn = (t % 8) * 8, k = k0 + kr;
-        const bf16x8 v = load8(B, g.ldb, k, k < ke, n0 + nn, g.N);
+    for (int u = 0; u < LOADS; ++u) {
+        if (!T) {
+            *reinterpret_cast<bf16x8 *>(&S[t / 16 + 16 * u][(t % 16) * 8]) = v[u];
+        } else if (u % 2 == 0) {   // transposed, two k at a time
+            const int k = 2 * (t / 8 + 32 * (u / 2));
 #pragma unroll
-        for (int i = 0; i < 8; ++i) Bs[nn + i][kr] = v[i];
+            for (int i = 0; i < 8; ++i) {
+                typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+                *reinterpret_cast<bf16x2 *>(&S[(t % 8) * 8 + i][k]) = bf16x2{v[u][i], v[u + 1][i]};
+            }
+        }
     }
 }
 
 template <bool TA, bool TB, int EPI>
 __global__ __launch_bounds__(256) void k_gemm(GemmArgs g)
 {
-    // rows of LDSK = 40 bf16 (80 bytes): every 16-byte fragment at k = 8 q is aligned
+    // rows of LDSK = 136 bf16 (272 bytes): every 16-byte fragment at k = 8 q is aligned
     __shared__ __attribute__((aligned(16))) __bf16 As[BM][LDSK];
     __shared__ __attribute__((aligned(16))) __bf16 Bs[BN][LDSK];
     const int members = (int)gridDim.z / g.nsp;
@@ -129,20 +144,47 @@ __global__ __launch_bounds__(256) void k_gemm(GemmArgs g)
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int wm = (wave >> 1) * 32, wn = (wave & 1) * 32;
     const int lr = lane & 15, lk = (lane >> 4) * 8;
+    const __bf16 *A = g.A + member * g.sA, *B = g.B + member * g.sB;
     f32x4 acc[2][2];
     for (int i = 0; i < 2; ++i)
         for (int j = 0; j < 2; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-    for (int k0 = kb; k0 < ke; k0 += BK) {
+    bf16x8 va[LOADS], vb[LOADS];
+    slab_load<TA>(A, g.lda, m0, g.M, kb, ke, va);
+    slab_load<TB>(B, g.ldb, n0, g.N, kb, ke, vb);
+    // what the epilogue reads, asked for here: the columns' biases, the mask
+    float bias[2] = {0.f, 0.f};
+    __bf16 mask[2][2][4];
+    for (int j = 0; j < 2; ++j) {
+        const int n = n0 + wn + 16 * j + lr;
+        if ((EPI == EPI_BIAS_RELU_BF16 || EPI == EPI_BIAS_F32) && n < g.nbias) bias[j] = g.bias[member * g.sbias + n];
+        if (EPI == EPI_MASK)
+            for (int i = 0; i < 2; ++i)
+                for (int e = 0; e < 4; ++e) {
+                    const int m = m0 + wm + 16 * i + (lane >> 4) * 4 + e;
+                    mask[i][j][e] = to_bf16(0.f);
+                    if (n < g.N && m < g.M) mask[i][j][e] = g.mask[member * g.smask + (int64_t)m * g.ldmask + n];
+                }
+    }
+    for (int k0 = kb; k0 < ke; k0 += SLAB) {
+        __syncthreads();   // the previous slab is no longer read
+        slab_store<TA>(va, As);
+        slab_store<TB>(vb, Bs);
         __syncthreads();
-        stage<TA, TB>(g, member, m0, n0, k0, ke, As, Bs);
-        __syncthreads();
-        bf16x8 a[2], b[2];
-        for (int i = 0; i < 2; ++i) a[i] = *reinterpret_cast<const bf16x8 *>(&As[wm + 16 * i + lr][lk]);
-        for (int j = 0; j < 2; ++j) b[j] = *reinterpret_cast<const bf16x8 *>(&Bs[wn + 16 * j + lr][lk]);
-        for (int i = 0; i < 2; ++i)
-            for (int j = 0; j < 2; ++j)
-                acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[i], b[j], acc[i][j], 0, 0, 0);
+        if (k0 + SLAB < ke) {
+            slab_load<TA>(A, g.lda, m0, g.M, k0 + SLAB, ke, va);
+            slab_load<TB>(B, g.ldb, n0, g.N, k0 + SLAB, ke, vb);
+        }
+#pragma unroll
+        for (int kk = 0; kk < SLAB; kk += BK) {
+            if (k0 + kk >= ke) break;
+            bf16x8 a[2], b[2];
+            for (int i = 0; i < 2; ++i) a[i] = *reinterpret_cast<const bf16x8 *>(&As[wm + 16 * i + lr][kk + lk]);
+            for (int j = 0; j < 2; ++j) b[j] = *reinterpret_cast<const bf16x8 *>(&Bs[wn + 16 * j + lr][kk + lk]);
+            for (int i = 0; i < 2; ++i)
+                for (int j = 0; j < 2; ++j)
+                    acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[i], b[j], acc[i][j], 0, 0, 0);
+        }
     }
 
     // epilogue: lane owns column n, rows r .. r+3 of each 16 x 16 tile
@@ -150,23 +192,19 @@ __global__ __launch_bounds__(256) void k_gemm(GemmArgs g)
         for (int j = 0; j < 2; ++j) {
             const int n = n0 + wn + 16 * j + lr;
             if (n >= g.N) continue;
-            float bias = 0.f;
-            if (EPI == EPI_BIAS_RELU_BF16 || EPI == EPI_BIAS_F32)
-                bias = (n < g.nbias) ? g.bias[member * g.sbias + n] : 0.f;
             for (int e = 0; e < 4; ++e) {
                 const int m = m0 + wm + 16 * i + (lane >> 4) * 4 + e;
                 if (m >= g.M) continue;
                 const float v = acc[i][j][e];
                 const int64_t o = (int64_t)m * g.ldo + n;
                 if (EPI == EPI_BIAS_RELU_BF16) {
-                    g.out_h[member * g.so_h + o] = to_bf16(fmaxf(v + bias, 0.f));
+                    g.out_h[member * g.so_h + o] = to_bf16(fmaxf(v + bias[j], 0.f));
                 } else if (EPI == EPI_BIAS_F32) {
-                    g.out_f[member * g.so_f + o] = v + bias;
+                    g.out_f[member * g.so_f + o] = v + bias[j];
                 } else if (EPI == EPI_F32) {
                     g.out_f[split * g.ssplit + member * g.so_f + o] = v;
                 } else {
-                    const float h = from_bf16(g.mask[member * g.smask + (int64_t)m * g.ldmask + n]);
-                    const float d = h > 0.f ? v : 0.f;
+                    const float d = from_bf16(mask[i][j][e]) > 0.f ? v : 0.f;
                     g.out_h[member * g.so_h + o] = to_bf16(d);
                     g.out_f[member * g.so_f + o] = d;
                 }
