@@ -54,7 +54,7 @@ enum Epi {
     EPI_BIAS_RELU_BF16 = 0,   // out_h = bf16(relu(acc + bias))
     EPI_BIAS_F32 = 1,         // out_f = acc + bias
     EPI_F32 = 2,              // out_f = acc
-    EPI_MASK = 3,             // g = acc * (mask_h > 0): out_h = bf16(g), out_f = g
+    EPI_MASK = 3,             // g = acc * (mask_h > 0): out_h = bf16(g), and the tile's column sums of g
 };
 
 struct GemmArgs {
@@ -64,11 +64,11 @@ struct GemmArgs {
     const float *bias; int64_t sbias; int nbias;
     const __bf16 *mask; int64_t ldmask, smask;
     __bf16 *out_h; float *out_f; int64_t ldo, so_h, so_f;
-    // split K (EPI_F32 only): nsp splits, blockIdx.z = split * members +
-    // member; split s covers k in [s kc, min(K, (s + 1) kc)) and writes its
-    // partial product at out_f + s ssplit.  kc is a multiple of BK; one
-    // split: kc >= K.
-    int kc, nsp; int64_t ssplit;
+    float *part; int64_t spart;             // EPI_MASK: column sums [member][row tile][N]
+    // split K (EPI_F32 only): split s covers k in [s kc, min(K, (s + 1) kc)) and
+    // writes its partial product at out_f + s ssplit.  kc is a multiple of BK;
+    // one split: kc >= K.
+    int kc; int64_t ssplit;
 };
 
 constexpr int BM = 64, BN = 64, BK = 32, SLAB = 4 * BK, LDSK = SLAB + 8;
@@ -90,6 +90,28 @@ __device__ __forceinline__ bf16x8 load8(const __bf16 *P, int64_t ld, int row, bo
         for (int i = 0; i < 8; ++i) v[i] = (row_ok && c + i < lim) ? q[i] : zero;
     }
     return v;
+}
+
+// Column sums (bias gradients) of a gradient G [n][columns], in two steps that
+// depend on n only, not on the launch: per block of 64 rows, lane l of four adds
+// rows l, l + 4, ... in order and the four lanes are added in a fixed order
+// (block_colsum, in the kernels that make the gradient, from LDS); k_grad_sums
+// then adds the blocks of each column.
+constexpr int CS_ROWS = 64;
+static_assert(BM == CS_ROWS, "a row tile is a block of the column sums");
+
+// Column c's sum over the block's rows, tile[row * ld + c] (zero past the last
+// row), by the four lanes rl = 0 .. 3; valid for rl = 0.  For c < 64; ends with
+// the lanes' sums read.
+__device__ __forceinline__ float block_colsum(const float *tile, int ld, int c, int rl)
+{
+    __shared__ float p4[4][64];
+    float s = 0.f;
+#pragma unroll
+    for (int k = 0; k < CS_ROWS / 4; ++k) s += tile[(rl + 4 * k) * ld + c];
+    p4[rl][c] = s;
+    __syncthreads();
+    return ((p4[0][c] + p4[1][c]) + p4[2][c]) + p4[3][c];
 }
 
 // A thread's part of one operand's slab (k0 .. k0 + SLAB - 1 of rows r0 .. r0 +
@@ -132,15 +154,13 @@ __device__ __forceinline__ void slab_store(const bf16x8 (&v)[LOADS], __bf16 (*S)
 }
 
 template <bool TA, bool TB, int EPI>
-__global__ __launch_bounds__(256) void k_gemm(GemmArgs g)
+__device__ __forceinline__ void gemm_tile(const GemmArgs &g, int bx, int by, int member, int split)
 {
     // rows of LDSK = 136 bf16 (272 bytes): every 16-byte fragment at k = 8 q is aligned
     __shared__ __attribute__((aligned(16))) __bf16 As[BM][LDSK];
     __shared__ __attribute__((aligned(16))) __bf16 Bs[BN][LDSK];
-    const int members = (int)gridDim.z / g.nsp;
-    const int member = (int)blockIdx.z % members, split = (int)blockIdx.z / members;
     const int kb = split * g.kc, ke = min(g.K, kb + g.kc);
-    const int m0 = blockIdx.y * BM, n0 = blockIdx.x * BN;
+    const int m0 = by * BM, n0 = bx * BN;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int wm = (wave >> 1) * 32, wn = (wave & 1) * 32;
     const int lr = lane & 15, lk = (lane >> 4) * 8;
@@ -188,40 +208,83 @@ __global__ __launch_bounds__(256) void k_gemm(GemmArgs g)
     }
 
     // epilogue: lane owns column n, rows r .. r+3 of each 16 x 16 tile
+    float (*tile)[BN + 1] = reinterpret_cast<float (*)[BN + 1]>(As);   // EPI_MASK: g, over the slabs
+    static_assert(sizeof(float) * BM * (BN + 1) <= sizeof(__bf16) * BM * LDSK, "the tile fits a slab");
+    if (EPI == EPI_MASK) __syncthreads();   // the slabs are no longer read
     for (int i = 0; i < 2; ++i)
         for (int j = 0; j < 2; ++j) {
             const int n = n0 + wn + 16 * j + lr;
-            if (n >= g.N) continue;
             for (int e = 0; e < 4; ++e) {
-                const int m = m0 + wm + 16 * i + (lane >> 4) * 4 + e;
-                if (m >= g.M) continue;
+                const int mt = wm + 16 * i + (lane >> 4) * 4 + e, m = m0 + mt;
                 const float v = acc[i][j][e];
+                if (EPI == EPI_MASK) {
+                    const float d = from_bf16(mask[i][j][e]) > 0.f ? v : 0.f;
+                    tile[mt][wn + 16 * j + lr] = d;
+                    if (n < g.N && m < g.M) g.out_h[member * g.so_h + (int64_t)m * g.ldo + n] = to_bf16(d);
+                    continue;
+                }
+                if (n >= g.N || m >= g.M) continue;
                 const int64_t o = (int64_t)m * g.ldo + n;
                 if (EPI == EPI_BIAS_RELU_BF16) {
                     g.out_h[member * g.so_h + o] = to_bf16(fmaxf(v + bias[j], 0.f));
                 } else if (EPI == EPI_BIAS_F32) {
                     g.out_f[member * g.so_f + o] = v + bias[j];
-                } else if (EPI == EPI_F32) {
-                    g.out_f[split * g.ssplit + member * g.so_f + o] = v;
                 } else {
-                    const float d = from_bf16(mask[i][j][e]) > 0.f ? v : 0.f;
-                    g.out_h[member * g.so_h + o] = to_bf16(d);
-                    g.out_f[member * g.so_f + o] = d;
+                    g.out_f[split * g.ssplit + member * g.so_f + o] = v;
                 }
             }
         }
+    if (EPI == EPI_MASK) {
+        __syncthreads();
+        const int c = threadIdx.x & 63;
+        const float s = block_colsum(&tile[0][0], BN + 1, c, threadIdx.x >> 6);
+        if (threadIdx.x < 64 && n0 + c < g.N)
+            g.part[member * g.spart + (int64_t)by * g.N + n0 + c] = s;
+    }
 }
 
-// Returns the number of K splits launched (at most `splits`).
 template <bool TA, bool TB, int EPI>
-static int gemm(const GemmArgs &g0, int members, hipStream_t st, int splits = 1)
+__global__ __launch_bounds__(256) void k_gemm(GemmArgs g)
 {
-    GemmArgs g = g0;
-    g.kc = splits <= 1 ? std::max(g.K, 1) : (g.K + splits * BK - 1) / (splits * BK) * BK;
-    g.nsp = std::max(1, (g.K + g.kc - 1) / g.kc);
-    dim3 grid((g.N + BN - 1) / BN, (g.M + BM - 1) / BM, members * g.nsp);
+    gemm_tile<TA, TB, EPI>(g, blockIdx.x, blockIdx.y, blockIdx.z, 0);
+}
+
+// The weight gradients of all layers in one launch, one after the other in
+// the grid: tile, then member, then K split.
+constexpr int N_LAYERS = 4;
+struct GradGemms {
+    GemmArgs g[N_LAYERS];
+    int first[N_LAYERS + 1];   // of each product's workgroups
+    int members;
+};
+
+__global__ __launch_bounds__(256) void k_gemm_grads(GradGemms G)
+{
+    int l = 0;
+    while (l + 1 < N_LAYERS && (int)blockIdx.x >= G.first[l + 1]) ++l;
+    const GemmArgs &g = G.g[l];
+    int b = (int)blockIdx.x - G.first[l];
+    const int nx = (g.N + BN - 1) / BN, ny = (g.M + BM - 1) / BM;
+    const int bx = b % nx;
+    b /= nx;
+    const int by = b % ny;
+    b /= ny;
+    gemm_tile<true, true, EPI_F32>(g, bx, by, b % G.members, b / G.members);
+}
+
+template <bool TA, bool TB, int EPI>
+static void gemm(GemmArgs g, int members, hipStream_t st)
+{
+    g.kc = std::max(g.K, 1);
+    dim3 grid((g.N + BN - 1) / BN, (g.M + BM - 1) / BM, members);
     hipLaunchKernelGGL((k_gemm<TA, TB, EPI>), grid, dim3(256), 0, st, g);
-    return g.nsp;
+}
+
+// Sets g's K splits (at most `splits`) and returns their number.
+static int split_k(GemmArgs &g, int splits)
+{
+    g.kc = splits <= 1 ? std::max(g.K, 1) : (g.K + splits * BK - 1) / (splits * BK) * BK;
+    return std::max(1, (g.K + g.kc - 1) / g.kc);
 }
 
 // K splits of a weight-gradient GEMM (K = batch rows) with `tiles` output
@@ -282,15 +345,18 @@ __global__ void k_standardize(const float *__restrict__ feat, int64_t n, const f
 // Loss and output gradient on one block of LOSS_ROWS rows of one member:
 //   T'[r][o] = (target[r][o] - out_shift[o]) / out_scale[o]
 //   dY[r][o] = 2 (Y[r][o] - T'[r][o]) / (n 12) (0 in the padding columns)
-// in f32 and bf16, and the block's sum of (Y - T')^2 in fp64 into
-// lpart[member][block]; k_loss_fin turns the block sums into the mean.
+// in bf16, its column sums over the block (from f32) into part[member][block][o]
+// and the block's sum of (Y - T')^2 in fp64 into lpart[member][block];
+// k_grad_sums turns the block sums into the bias gradient and the mean.
 constexpr int LOSS_ROWS = 64;
+static_assert(LOSS_ROWS == CS_ROWS, "one block for the loss and the column sums");
 __global__ __launch_bounds__(256) void k_loss(const float *__restrict__ Y, int64_t sY, const float *__restrict__ target,
-                                              int64_t n, const float *__restrict__ scal, float *__restrict__ dYf,
-                                              __bf16 *__restrict__ dYh, int64_t sdY, double *__restrict__ lpart,
-                                              int64_t slp)
+                                              int64_t n, const float *__restrict__ scal,
+                                              __bf16 *__restrict__ dYh, int64_t sdY, float *__restrict__ part,
+                                              int64_t spart, double *__restrict__ lpart, int64_t slp)
 {
     __shared__ double red[256];
+    __shared__ float tile[LOSS_ROWS * (OUTP + 1)];
     const int member = blockIdx.y;
     const float *Ym = Y + member * sY;
     double acc = 0.0;
@@ -299,9 +365,13 @@ __global__ __launch_bounds__(256) void k_loss(const float *__restrict__ Y, int64
 #pragma unroll
     for (int k = 0; k < LOSS_ROWS * OUTP / 256; ++k) {
         const int64_t i = i0 + threadIdx.x + 256 * k;
-        if (i >= i1) break;
         const int64_t r = i / OUTP;
         const int o = (int)(i % OUTP);
+        float *const cell = tile + (threadIdx.x + 256 * k) / OUTP * (OUTP + 1) + o;
+        if (i >= i1) {
+            *cell = 0.f;
+            continue;
+        }
         float d = 0.f;
         if (o < OUT) {
             const float tt = (target[r * OUT + o] - scal[2 * IN + o]) / scal[2 * IN + OUT + o];
@@ -309,11 +379,16 @@ __global__ __launch_bounds__(256) void k_loss(const float *__restrict__ Y, int64
             acc += (double)e * e;
             d = inv * e;
         }
-        dYf[member * sdY + i] = d;
+        *cell = d;
         dYh[member * sdY + i] = to_bf16(d);
     }
     red[threadIdx.x] = acc;
     __syncthreads();
+    {
+        const int c = threadIdx.x & 63;
+        const float s = block_colsum(tile, OUTP + 1, c % OUTP, threadIdx.x >> 6);
+        if (threadIdx.x < OUTP) part[member * spart + blockIdx.x * (int64_t)OUTP + c] = s;
+    }
     for (int off = 128; off > 0; off >>= 1) {
         if ((int)threadIdx.x < off) red[threadIdx.x] += red[threadIdx.x + off];
         __syncthreads();
@@ -321,73 +396,53 @@ __global__ __launch_bounds__(256) void k_loss(const float *__restrict__ Y, int64
     if (threadIdx.x == 0) lpart[member * slp + blockIdx.x] = red[0];
 }
 
-// Per-member loss = (sum of the nb block sums) / (n OUT); lanes take blocks
-// lane, lane + 64, ... in order, then a fixed tree adds the 64 lanes.
-__global__ __launch_bounds__(64) void k_loss_fin(const double *__restrict__ lpart, int64_t slp, int nb, int64_t n,
-                                                 float *__restrict__ loss_out)
-{
-    __shared__ double red[64];
-    const int member = blockIdx.x;
-    double s = 0.0;
-    for (int b = threadIdx.x; b < nb; b += 64) s += lpart[member * slp + b];
-    red[threadIdx.x] = s;
-    __syncthreads();
-    for (int off = 32; off > 0; off >>= 1) {
-        if ((int)threadIdx.x < off) red[threadIdx.x] += red[threadIdx.x + off];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) loss_out[member] = (float)(red[0] / (double)(n * OUT));
-}
+// The bias gradients of all layers from their block sums, and the loss:
+// workgroup x = 64 columns (4 per hidden layer, then the 16 outputs), lane l of
+// four takes blocks l, l + 4, ... in order, again 4 lanes in a fixed order; the
+// last workgroup, present if loss_out is not null: per-member loss = (sum of the
+// nb block sums) / (n OUT), lanes taking blocks lane, lane + 64, ... in order, then
+// a fixed tree over the 64 lanes.
+struct SumArgs {
+    const float *part[N_LAYERS];   // [member][block][columns]
+    const double *lpart;
+    int nb;
+    int64_t n;
+    float *db;                     // [member][4 HID]
+    float *loss_out;
+};
+constexpr int SUM_GROUPS = 3 * (HID / 64) + 1;   // without the loss
 
-// Column sums (bias gradients): out[member][c] = sum_r G[member][r][c], in
-// two passes so that the whole device takes part.  k_colsum_part: workgroup
-// = 64 columns x 4 row lanes over one block of CS_ROWS rows; lane l adds rows
-// l, l + 4, ... of the block in order, the 4 lanes are added in a fixed order
-// into part[member][block][c].  k_colsum_fin then adds the blocks of each
-// column: lane l takes blocks l, l + 4, ... in order, again 4 lanes in a
-// fixed order.  The result depends on n only, not on the launch.
-constexpr int CS_ROWS = 64;
-__global__ __launch_bounds__(256) void k_colsum_part(const float *__restrict__ G, int64_t sG, int64_t n, int ld,
-                                                     int ncols, float *__restrict__ part, int64_t spm)
+__global__ __launch_bounds__(256) void k_grad_sums(SumArgs A)
 {
+    const int member = blockIdx.y, t = threadIdx.x;
+    if (blockIdx.x == SUM_GROUPS) {
+        __shared__ double red[64];
+        double s = 0.0;
+        if (t < 64) {
+            for (int b = t; b < A.nb; b += 64) s += A.lpart[member * (int64_t)A.nb + b];
+            red[t] = s;
+        }
+        __syncthreads();
+        for (int off = 32; off > 0; off >>= 1) {
+            if (t < off) red[t] += red[t + off];
+            __syncthreads();
+        }
+        if (t == 0) A.loss_out[member] = (float)(red[0] / (double)(A.n * OUT));
+        return;
+    }
     __shared__ float p4[4][64];
-    const int member = blockIdx.y;
-    const int c = blockIdx.x * 64 + (threadIdx.x & 63), rl = threadIdx.x >> 6;
-    const int64_t r0 = (int64_t)blockIdx.z * CS_ROWS;
-    const float *g = G + member * sG;
+    const int l = blockIdx.x / (HID / 64), ncols = l < 3 ? HID : OUTP;
+    const int c = blockIdx.x % (HID / 64) * 64 + (t & 63), rl = t >> 6;
+    const float *p = A.part[l] + member * (int64_t)A.nb * ncols;
     float s = 0.f;
     if (c < ncols) {
-        float v[CS_ROWS / 4];
-#pragma unroll
-        for (int k = 0; k < CS_ROWS / 4; ++k) {
-            const int64_t r = r0 + rl + 4 * k;
-            v[k] = r < n ? g[r * ld + c] : 0.f;
-        }
-#pragma unroll
-        for (int k = 0; k < CS_ROWS / 4; ++k) s += v[k];
+#pragma unroll 4
+        for (int b = rl; b < A.nb; b += 4) s += p[(int64_t)b * ncols + c];
     }
-    p4[rl][threadIdx.x & 63] = s;
+    p4[rl][t & 63] = s;
     __syncthreads();
     if (rl == 0 && c < ncols)
-        part[member * spm + blockIdx.z * (int64_t)ncols + c] =
-            ((p4[0][threadIdx.x] + p4[1][threadIdx.x]) + p4[2][threadIdx.x]) + p4[3][threadIdx.x];
-}
-
-__global__ __launch_bounds__(256) void k_colsum_fin(const float *__restrict__ part, int64_t spm, int nb, int ncols,
-                                                    float *__restrict__ out, int64_t sout)
-{
-    __shared__ float p4[4][64];
-    const int member = blockIdx.y;
-    const int c = blockIdx.x * 64 + (threadIdx.x & 63), rl = threadIdx.x >> 6;
-    const float *p = part + member * spm;
-    float s = 0.f;
-    if (c < ncols)
-        for (int b = rl; b < nb; b += 4) s += p[(int64_t)b * ncols + c];
-    p4[rl][threadIdx.x & 63] = s;
-    __syncthreads();
-    if (rl == 0 && c < ncols)
-        out[member * sout + c] = ((p4[0][threadIdx.x] + p4[1][threadIdx.x]) + p4[2][threadIdx.x]) +
-                                 p4[3][threadIdx.x];
+        A.db[member * (int64_t)(4 * HID) + l * HID + c] = ((p4[0][t] + p4[1][t]) + p4[2][t]) + p4[3][t];
 }
 
 // Adam on the flat master parameters; gradients are read from the padded
@@ -1018,10 +1073,9 @@ struct dd_mlp {
     int64_t cap = 0;
     bool cap_train = false;
     __bf16 *X0 = nullptr, *H1 = nullptr, *H2 = nullptr, *H3 = nullptr, *dYh = nullptr;
-    __bf16 *Dh[2] = {nullptr, nullptr};
-    float *Y = nullptr, *dYf = nullptr;
-    float *Df[2] = {nullptr, nullptr};
-    float *part = nullptr;                                // column-sum block partials
+    __bf16 *Dh[3] = {nullptr, nullptr, nullptr};          // dZ1 .. dZ3
+    float *Y = nullptr;
+    float *part = nullptr;                                // column-sum block partials of the four layers
     double *lpart = nullptr;                              // loss block partials
 };
 
@@ -1032,12 +1086,12 @@ constexpr int64_t TRAIN_MAX = 65536;
 
 void free_rows(dd_mlp *h)
 {
-    void *ps[] = {h->X0, h->H1, h->H2, h->H3, h->dYh, h->Dh[0], h->Dh[1], h->Y, h->dYf, h->Df[0], h->Df[1],
-                  h->part, h->lpart};
+    void *ps[] = {h->X0, h->H1, h->H2, h->H3, h->dYh, h->Dh[0], h->Dh[1], h->Dh[2], h->Y, h->part,
+                  h->lpart};
     for (void *p : ps)
         if (p) (void)hipFree(p);
-    h->X0 = h->H1 = h->H2 = h->H3 = h->dYh = h->Dh[0] = h->Dh[1] = nullptr;
-    h->Y = h->dYf = h->Df[0] = h->Df[1] = h->part = nullptr;
+    h->X0 = h->H1 = h->H2 = h->H3 = h->dYh = h->Dh[0] = h->Dh[1] = h->Dh[2] = nullptr;
+    h->Y = h->part = nullptr;
     h->lpart = nullptr;
     h->cap = 0;
     h->cap_train = false;
@@ -1069,13 +1123,10 @@ int ensure_rows(dd_mlp *h, int64_t rows, bool training)
     if ((rc = dev_alloc((void **)&h->Y, sizeof(float) * M * rows * OUTP))) return rc;
     if (train) {
         if ((rc = dev_alloc((void **)&h->dYh, sizeof(__bf16) * M * rows * OUTP))) return rc;
-        if ((rc = dev_alloc((void **)&h->dYf, sizeof(float) * M * rows * OUTP))) return rc;
-        for (int k = 0; k < 2; ++k) {
+        for (int k = 0; k < 3; ++k)
             if ((rc = dev_alloc((void **)&h->Dh[k], sizeof(__bf16) * M * rows * HID))) return rc;
-            if ((rc = dev_alloc((void **)&h->Df[k], sizeof(float) * M * rows * HID))) return rc;
-        }
         const int64_t nb = (rows + CS_ROWS - 1) / CS_ROWS, nbl = (rows + LOSS_ROWS - 1) / LOSS_ROWS;
-        if ((rc = dev_alloc((void **)&h->part, sizeof(float) * M * nb * HID))) return rc;
+        if ((rc = dev_alloc((void **)&h->part, sizeof(float) * M * nb * (3 * HID + OUTP)))) return rc;
         if ((rc = dev_alloc((void **)&h->lpart, sizeof(double) * M * nbl))) return rc;
     }
     h->cap = rows;
@@ -1159,18 +1210,6 @@ GradPtrs grad_ptrs(const dd_mlp *h)
     return G;
 }
 
-// Two passes; part holds members x ceil(n / CS_ROWS) x ncols floats.
-void colsum(const float *G, int64_t sG, int64_t n, int ld, int ncols, float *out, int members, float *part,
-            hipStream_t st)
-{
-    const int nb = (int)((n + CS_ROWS - 1) / CS_ROWS);
-    const int64_t spm = (int64_t)nb * ncols;
-    hipLaunchKernelGGL(k_colsum_part, dim3((ncols + 63) / 64, members, nb), dim3(256), 0, st, G, sG, n, ld, ncols,
-                       part, spm);
-    hipLaunchKernelGGL(k_colsum_fin, dim3((ncols + 63) / 64, members), dim3(256), 0, st, part, spm, nb, ncols, out,
-                       (int64_t)4 * HID);
-}
-
 // Forward + backward on n rows.  Gradients land in dW1..dW4 (padded GEMM
 // layouts) and db; per-member losses in loss_out (nullable).
 int gradients(dd_mlp *h, int64_t n, const float *feat, const float *target, float *loss_out, hipStream_t st)
@@ -1181,59 +1220,51 @@ int gradients(dd_mlp *h, int64_t n, const float *feat, const float *target, floa
     hipLaunchKernelGGL(k_standardize, dim3((unsigned)((n * INP + 255) / 256)), dim3(256), 0, st, feat, n,
                        h->scal, h->X0);
     forward(h, n, st);
-    const int nbl = (int)((n + LOSS_ROWS - 1) / LOSS_ROWS);
-    hipLaunchKernelGGL(k_loss, dim3(nbl, M), dim3(256), 0, st, h->Y, n * OUTP, target, n, h->scal, h->dYf,
-                       h->dYh, n * OUTP, h->lpart, (int64_t)nbl);
-    if (loss_out)
-        hipLaunchKernelGGL(k_loss_fin, dim3(M), dim3(64), 0, st, h->lpart, (int64_t)nbl, nbl, n, loss_out);
-    GemmArgs g{};
-    // output layer: dW4 [16][256] = dY^T H3, db4 = colsum(dY)
-    g.A = h->dYh; g.lda = OUTP; g.sA = n * OUTP;
-    g.B = h->H3; g.ldb = HID; g.sB = n * HID;
-    g.M = OUTP; g.N = HID; g.K = (int)n;
-    g.out_f = h->dW4; g.ldo = HID; g.so_f = (int64_t)OUTP * HID; g.ssplit = M * g.so_f;
-    h->ks[3] = gemm<true, true, EPI_F32>(g, M, st, ksplit(TILES_W4, M, n));
-    colsum(h->dYf, n * OUTP, n, OUTP, OUTP, h->db + 3 * HID, M, h->part, st);
-    // dZ3 = (dY W4p) * (H3 > 0)  -> buffer 0
-    g = GemmArgs{};
-    g.A = h->dYh; g.lda = OUTP; g.sA = n * OUTP;
-    g.B = h->W4p; g.ldb = HID; g.sB = (int64_t)OUTP * HID;
-    g.M = (int)n; g.N = HID; g.K = OUTP;
-    g.mask = h->H3; g.ldmask = HID; g.smask = n * HID;
-    g.out_h = h->Dh[0]; g.out_f = h->Df[0]; g.ldo = HID; g.so_h = n * HID; g.so_f = n * HID;
-    gemm<false, true, EPI_MASK>(g, M, st);
-    // hidden layers 3 and 2: dW = dZ^T H_prev, db = colsum(dZ),
-    // dZ_prev = (dZ W) * (H_prev > 0) into the other buffer
-    const __bf16 *Hprev[2] = {h->H2, h->H1};
-    float *dWs[2] = {h->dW3, h->dW2};
-    const __bf16 *Ws[2] = {h->W3, h->W2};
-    const int dbo[2] = {2 * HID, 1 * HID};
-    int cur = 0;
-    for (int l = 0; l < 2; ++l) {
-        g = GemmArgs{};
-        g.A = h->Dh[cur]; g.lda = HID; g.sA = n * HID;
-        g.B = Hprev[l]; g.ldb = HID; g.sB = n * HID;
-        g.M = HID; g.N = HID; g.K = (int)n;
-        g.out_f = dWs[l]; g.ldo = HID; g.so_f = (int64_t)HID * HID; g.ssplit = M * g.so_f;
-        h->ks[2 - l] = gemm<true, true, EPI_F32>(g, M, st, ksplit(TILES_W23, M, n));
-        colsum(h->Df[cur], n * HID, n, HID, HID, h->db + dbo[l], M, h->part, st);
-        g = GemmArgs{};
-        g.A = h->Dh[cur]; g.lda = HID; g.sA = n * HID;
-        g.B = Ws[l]; g.ldb = HID; g.sB = (int64_t)HID * HID;   // B(n = i, k = o) = W[o][i]
-        g.M = (int)n; g.N = HID; g.K = HID;
-        g.mask = Hprev[l]; g.ldmask = HID; g.smask = n * HID;
-        g.out_h = h->Dh[1 - cur]; g.out_f = h->Df[1 - cur]; g.ldo = HID; g.so_h = n * HID; g.so_f = n * HID;
+    const int nb = (int)((n + CS_ROWS - 1) / CS_ROWS);
+    SumArgs S{};
+    for (int l = 0; l < N_LAYERS; ++l) S.part[l] = h->part + l * (int64_t)M * nb * HID;
+    S.lpart = h->lpart;
+    S.nb = nb;
+    S.n = n;
+    S.db = h->db;
+    S.loss_out = loss_out;
+    hipLaunchKernelGGL(k_loss, dim3(nb, M), dim3(256), 0, st, h->Y, n * OUTP, target, n, h->scal, h->dYh, n * OUTP,
+                       const_cast<float *>(S.part[3]), (int64_t)nb * OUTP, h->lpart, (int64_t)nb);
+    // dZ3 = (dY W4p) * (H3 > 0), dZ2 = (dZ3 W3) * (H2 > 0), dZ1 = (dZ2 W2) * (H1 > 0);
+    // B(n = i, k = o) = W[o][i]
+    const __bf16 *H[3] = {h->H1, h->H2, h->H3}, *Wt[3] = {h->W2, h->W3, h->W4p};
+    for (int l = 2; l >= 0; --l) {
+        const int out = l == 2 ? OUTP : HID;
+        GemmArgs g{};
+        g.A = l == 2 ? h->dYh : h->Dh[l + 1]; g.lda = out; g.sA = n * out;
+        g.B = Wt[l]; g.ldb = HID; g.sB = (int64_t)out * HID;
+        g.M = (int)n; g.N = HID; g.K = out;
+        g.mask = H[l]; g.ldmask = HID; g.smask = n * HID;
+        g.out_h = h->Dh[l]; g.ldo = HID; g.so_h = n * HID;
+        g.part = const_cast<float *>(S.part[l]); g.spart = (int64_t)nb * HID;
         gemm<false, true, EPI_MASK>(g, M, st);
-        cur = 1 - cur;
     }
-    // first layer: dW1 [256][64] = dZ1^T X0, db1
-    g = GemmArgs{};
-    g.A = h->Dh[cur]; g.lda = HID; g.sA = n * HID;
-    g.B = h->X0; g.ldb = INP; g.sB = 0;
-    g.M = HID; g.N = INP; g.K = (int)n;
-    g.out_f = h->dW1; g.ldo = INP; g.so_f = (int64_t)HID * INP; g.ssplit = M * g.so_f;
-    h->ks[0] = gemm<true, true, EPI_F32>(g, M, st, ksplit(TILES_W1, M, n));
-    colsum(h->Df[cur], n * HID, n, HID, HID, h->db, M, h->part, st);
+    // weight gradients: dW2, dW3 [256][256] = dZ^T H_prev, dW1 [256][64] = dZ1^T X0,
+    // dW4 [16][256] = dY^T H3, the largest first in the grid
+    const int order[N_LAYERS] = {1, 2, 0, 3};
+    const int tiles[N_LAYERS] = {TILES_W1, TILES_W23, TILES_W23, TILES_W4};
+    const __bf16 *in[N_LAYERS] = {h->X0, h->H1, h->H2, h->H3}, *dZ[N_LAYERS] = {h->Dh[0], h->Dh[1], h->Dh[2], h->dYh};
+    float *dW[N_LAYERS] = {h->dW1, h->dW2, h->dW3, h->dW4};
+    GradGemms G{};
+    G.members = M;
+    for (int k = 0; k < N_LAYERS; ++k) {
+        const int l = order[k];
+        const int rows = l == 3 ? OUTP : HID, cols = l == 0 ? INP : HID;
+        GemmArgs &g = G.g[k];
+        g.A = dZ[l]; g.lda = rows; g.sA = n * rows;
+        g.B = in[l]; g.ldb = cols; g.sB = l == 0 ? 0 : n * cols;   // the members share the inputs
+        g.M = rows; g.N = cols; g.K = (int)n;
+        g.out_f = dW[l]; g.ldo = cols; g.so_f = (int64_t)rows * cols; g.ssplit = M * g.so_f;
+        h->ks[l] = split_k(g, ksplit(tiles[l], M, n));
+        G.first[k + 1] = G.first[k] + tiles[l] * M * h->ks[l];
+    }
+    hipLaunchKernelGGL(k_gemm_grads, dim3(G.first[N_LAYERS]), dim3(256), 0, st, G);
+    hipLaunchKernelGGL(k_grad_sums, dim3(SUM_GROUPS + (loss_out ? 1 : 0), M), dim3(256), 0, st, S);
     DD_HIP(hipGetLastError());
     return DD_OK;
 }
