@@ -458,8 +458,18 @@ struct GradPtrs {
 
 __device__ __forceinline__ float split_sum(const float *q, int k, int64_t ss)
 {
+    // added in split order, eight loads in flight (one after the other they took
+    // most of k_adam's time: 10.7 -> 9.6 us with 8 splits of 1,024 rows, 4,096
+    // rows 8 us less)
     float v = q[0];
-    for (int s = 1; s < k; ++s) v += q[s * ss];
+    for (int s = 1; s < k; s += 8) {
+        float u[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) u[i] = s + i < k ? q[(s + i) * ss] : 0.f;
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+            if (s + i < k) v += u[i];
+    }
     return v;
 }
 
