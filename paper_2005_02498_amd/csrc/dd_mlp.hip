@@ -21,6 +21,7 @@ namespace dd {
 namespace mlp {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int IN = DD_MLP_IN, HID = DD_MLP_HIDDEN, OUT = DD_MLP_OUT;
@@ -543,27 +544,58 @@ __global__ void k_refresh(const float *__restrict__ w, int members, __bf16 *__re
     W4p[member * (int64_t)OUTP * HID + j] = to_bf16(o < OUT ? wm[OW4 + j] : 0.f);
 }
 
-// Ensemble reduction per point: rates = member mean (unstandardised),
-// spread = |population std|_2 / max(|mean|_2, spread floor), needs_dd =
-// spread > tol.  A member's 12 outputs are the first three float4s of its
-// 64-byte row of Y; VEC: rates rows as float4s too (16-byte aligned rates).
-template <bool VEC>
-__global__ __launch_bounds__(256) void k_ensemble(const float *__restrict__ Y, int64_t sY, int members, int64_t n,
-                                                  const float *__restrict__ scal, float tol,
-                                                  float *__restrict__ rates, float *__restrict__ spread,
-                                                  uint8_t *__restrict__ needs_dd)
+// Ensemble reduction of point r: rates = member mean (unstandardised), spread =
+// |population std|_2 / max(|mean|_2, spread floor), needs_dd = spread > tol.  A
+// member's 12 outputs are the first three float4s of its 64-byte row of Y; VEC:
+// rates rows as float4s too (16-byte aligned rates).  SHARED: Y is written by
+// other workgroups of the same launch (y_store), read past the caches.
+struct EnsembleArgs {
+    const float *Y;
+    int64_t sY;
+    int members;
+    int64_t n;
+    const float *scal;
+    float tol;
+    float *rates, *spread;
+    uint8_t *needs_dd;
+};
+
+// Y between workgroups of one launch: stores and loads at the device's point of
+// coherence, two floats at a time, so that no cache is written back or
+// invalidated for them.
+__device__ __forceinline__ void y_store(float *p, float4 v)
 {
-    const int64_t r = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (r >= n) return;
+    unsigned long long *const q = reinterpret_cast<unsigned long long *>(p);
+    __hip_atomic_store(q, __builtin_bit_cast(unsigned long long, f32x2{v.x, v.y}), __ATOMIC_RELAXED,
+                       __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(q + 1, __builtin_bit_cast(unsigned long long, f32x2{v.z, v.w}), __ATOMIC_RELAXED,
+                       __HIP_MEMORY_SCOPE_AGENT);
+}
+
+template <bool SHARED>
+__device__ __forceinline__ float4 y_load(const float *p)
+{
+    if (!SHARED) return *reinterpret_cast<const float4 *>(p);
+    const unsigned long long *const q = reinterpret_cast<const unsigned long long *>(p);
+    const f32x2 a = __builtin_bit_cast(f32x2, __hip_atomic_load(q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+    const f32x2 b = __builtin_bit_cast(f32x2, __hip_atomic_load(q + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+    return float4{a[0], a[1], b[0], b[1]};
+}
+
+template <bool VEC, bool SHARED>
+__device__ __forceinline__ void ensemble_point(const EnsembleArgs &E, int64_t r)
+{
+    const float *const scal = E.scal;
+    const int members = E.members;
     float mean[OUT], var[OUT];
 #pragma unroll
     for (int o = 0; o < OUT; ++o) mean[o] = var[o] = 0.f;
     const float *osh = scal + 2 * IN, *osc = scal + 2 * IN + OUT;
     for (int m = 0; m < members; ++m) {
-        const float4 *y = reinterpret_cast<const float4 *>(Y + m * sY + r * OUTP);
+        const float *y = E.Y + m * E.sY + r * OUTP;
 #pragma unroll
         for (int q = 0; q < OUT / 4; ++q) {
-            const float4 v = y[q];
+            const float4 v = y_load<SHARED>(y + 4 * q);
             mean[4 * q] += v.x * osc[4 * q] + osh[4 * q];
             mean[4 * q + 1] += v.y * osc[4 * q + 1] + osh[4 * q + 1];
             mean[4 * q + 2] += v.z * osc[4 * q + 2] + osh[4 * q + 2];
@@ -574,10 +606,10 @@ __global__ __launch_bounds__(256) void k_ensemble(const float *__restrict__ Y, i
 #pragma unroll
     for (int o = 0; o < OUT; ++o) mean[o] *= im;
     for (int m = 0; m < members; ++m) {
-        const float4 *y = reinterpret_cast<const float4 *>(Y + m * sY + r * OUTP);
+        const float *y = E.Y + m * E.sY + r * OUTP;
 #pragma unroll
         for (int q = 0; q < OUT / 4; ++q) {
-            const float4 v = y[q];
+            const float4 v = y_load<SHARED>(y + 4 * q);
             const float d[4] = {v.x * osc[4 * q] + osh[4 * q] - mean[4 * q],
                                 v.y * osc[4 * q + 1] + osh[4 * q + 1] - mean[4 * q + 1],
                                 v.z * osc[4 * q + 2] + osh[4 * q + 2] - mean[4 * q + 2],
@@ -593,16 +625,23 @@ __global__ __launch_bounds__(256) void k_ensemble(const float *__restrict__ Y, i
         m2 += mean[o] * mean[o];
     }
     if (VEC) {
-        float4 *ro = reinterpret_cast<float4 *>(rates + r * OUT);
+        float4 *ro = reinterpret_cast<float4 *>(E.rates + r * OUT);
 #pragma unroll
         for (int q = 0; q < OUT / 4; ++q) ro[q] = float4{mean[4 * q], mean[4 * q + 1], mean[4 * q + 2], mean[4 * q + 3]};
     } else {
 #pragma unroll
-        for (int o = 0; o < OUT; ++o) rates[r * OUT + o] = mean[o];
+        for (int o = 0; o < OUT; ++o) E.rates[r * OUT + o] = mean[o];
     }
     const float sp = sqrtf(s2) / fmaxf(sqrtf(m2), scal[2 * IN + 2 * OUT + 2]);
-    spread[r] = sp;
-    needs_dd[r] = sp > tol ? 1 : 0;
+    E.spread[r] = sp;
+    E.needs_dd[r] = sp > E.tol ? 1 : 0;
+}
+
+template <bool VEC>
+__global__ __launch_bounds__(256) void k_ensemble(EnsembleArgs E)
+{
+    const int64_t r = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+    if (r < E.n) ensemble_point<VEC, false>(E, r);
 }
 
 // ------------------------------------------------- fused inference kernel --
@@ -662,7 +701,6 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef short s16x2 __attribute__((ext_vector_type(2)));
 typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
-typedef float f32x2 __attribute__((ext_vector_type(2)));
 
 // Input index of slot s in lane half h of K step t, for layers 2-4.
 __host__ __device__ __forceinline__ int perm_k(int t, int h, int s)
@@ -1126,6 +1164,160 @@ __global__ __launch_bounds__(64 * IWAVES, 1) void k_mlp_infer(const float *__res
     }
 }
 
+// The same for few points: tiles of SP = 32 points, one per workgroup, so that
+// they cover the device where tiles of 128 leave most of it idle, and the members'
+// workgroups of a tile counted as they end: the last one reduces the ensemble.
+// Every product enters its accumulator in the order of k_mlp_infer (a point is a
+// column of the same instructions): same results bit for bit.
+//
+// Bound by latency and by the 278 KB of weights a workgroup takes from the L2:
+// all three layers' are asked for at the start.  A call for 1,500 points of four
+// members 14.7 -> 10.7 us, for one point 12.3 -> 9.1 us (a kernel is 4 us at least).  The
+// line is where the tiles of all members fill the compute units once: 2,000 points
+// 14.7 and 11.1 us; 2,200, in a second round, 14.8 and 16.3 us.  With a device-wide
+// fence for each workgroup's outputs, in place of y_store, 1,500 points took 20.8 us.
+constexpr int SP = 32;
+
+template <bool VEC>
+__global__ __launch_bounds__(64 * IWAVES, 1) void k_mlp_infer_small(const float *__restrict__ feat,
+                                                                    const __bf16 *__restrict__ Wi,
+                                                                    const float *__restrict__ w, float *Y,
+                                                                    unsigned *done, EnsembleArgs E)
+{
+    __shared__ bf16x8 act[2][IKS][64];   // activations: [buffer][K step][lane] of 8 bf16
+    __shared__ bf16x8 xin[IK1][64];
+    __shared__ __attribute__((aligned(16))) float bias_s[3 * HID + OUTP];
+    __shared__ __attribute__((aligned(16))) float coef_s[2 * IN];
+    __shared__ unsigned s_last;
+    const int member = blockIdx.y, tile = blockIdx.x;
+    const int tid = threadIdx.x, lane = tid & 63, h = lane >> 5;
+    const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const unsigned lane16 = 16u * lane;
+    const float *wm = w + member * P, *const scal = E.scal;
+    const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<__bf16 *>(Wi + member * WI_PER), 0, (int)(2 * WI_PER), 0x00020000);
+    const int w1 = (int)(wv * IK1 * IMT * 512);
+    const int w2 = (int)(WI1 + wv * IKS * IMT * 512), w3 = (int)(WI1 + WI2 + wv * IKS * IMT * 512);
+    const int w4 = (int)(WI1 + 2 * WI2);
+    const float dfloor = scal[2 * IN + 2 * OUT + 1], dscale = scal[2 * IN + 2 * OUT];
+    const bool dlog = dfloor > 0.f;
+    // thread: point tid % SP, group tid / SP of eight inputs (groups 0 .. 5; 5 is
+    // padding, 4 half); rows past n read row n - 1
+    const int pt = tid % SP, grp = tid / SP;
+    float4 f0{}, f1{};
+    if (grp < 5) {
+        const int64_t row = (int64_t)tile * SP + pt;
+        const float4 *q = reinterpret_cast<const float4 *>(feat) + (row < E.n ? row : E.n - 1) * 9 + 2 * grp;
+        f0 = q[0];
+        if (grp < 4) f1 = q[1];
+    }
+    float ca = 0.f, cb = 0.f;
+    if (tid < IN) {
+        const float sh = scal[tid], sc = scal[IN + tid];
+        ca = tid >= 12 && dlog ? sc * LOG10_2 : sc;
+        cb = -sh * sc;
+    }
+    const float bl1 = wm[OB1 + tid], bl2 = wm[OB2 + tid], bl3 = wm[OB3 + tid];
+    const float bl4 = tid < OUT ? wm[OB4 + tid] : 0.f;
+    bf16x8 W1r[IK1][IMT], W2r[IKS][IMT], W3r[IKS][IMT];
+#pragma unroll
+    for (int t = 0; t < IK1; ++t)
+#pragma unroll
+        for (int jj = 0; jj < IMT; ++jj) W1r[t][jj] = ldfrag(rs, w1, t * IMT + jj, lane16);
+#pragma unroll
+    for (int t = 0; t < IKS; ++t)
+#pragma unroll
+        for (int jj = 0; jj < IMT; ++jj) W2r[t][jj] = ldfrag(rs, w2, t * IMT + jj, lane16);
+#pragma unroll
+    for (int t = 0; t < IKS; ++t)
+#pragma unroll
+        for (int jj = 0; jj < IMT; ++jj) W3r[t][jj] = ldfrag(rs, w3, t * IMT + jj, lane16);
+    if (tid < IN) {
+        coef_s[tid] = ca;
+        coef_s[IN + tid] = cb;
+    }
+    bias_s[tid] = bl1;
+    bias_s[HID + tid] = bl2;
+    bias_s[2 * HID + tid] = bl3;
+    if (tid < OUTP) bias_s[3 * HID + tid] = bl4;
+    __syncthreads();
+    if (grp < 6) {
+        bf16x8 o{};
+        if (grp < 5) {
+            const float v[8] = {f0.x, f0.y, f0.z, f0.w, f1.x, f1.y, f1.z, f1.w};
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                const int k = 8 * grp + e;
+                if (k < IN)
+                    o[e] = to_bf16(std_in(k >= 12 && dlog ? dens_log2(v[e], dscale, dfloor) : v[e], coef_s[k],
+                                          coef_s[IN + k]));
+            }
+        }
+        xin[grp / 2][pt + 32 * (grp % 2)] = o;
+    }
+    const int J0 = IMT * wv;
+    f32x16 acc[IMT];
+    // a hidden layer's accumulators to the next layer's B fragments (as epi_unit)
+    auto store = [&](bf16x8 (*dst)[64]) {
+#pragma unroll
+        for (int jj = 0; jj < IMT; ++jj) {
+            u32x4 frag{};
+#pragma unroll
+            for (int g = 0; g < 4; ++g) {
+                frag[2 * (g % 2)] = relu_pk(acc[jj][4 * g], acc[jj][4 * g + 1]);
+                frag[2 * (g % 2) + 1] = relu_pk(acc[jj][4 * g + 2], acc[jj][4 * g + 3]);
+                if (g % 2 == 1) dst[2 * (J0 + jj) + g / 2][lane] = __builtin_bit_cast(bf16x8, frag);
+            }
+        }
+    };
+    auto layer = [&](const auto &W, int steps, bf16x8 (*src)[64], const float *bias) {
+#pragma unroll
+        for (int jj = 0; jj < IMT; ++jj) load_bias(acc[jj], bias, J0 + jj, h);
+#pragma unroll
+        for (int t = 0; t < steps; ++t) {
+            const bf16x8 b = src[t][lane];
+#pragma unroll
+            for (int jj = 0; jj < IMT; ++jj)
+                acc[jj] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(W[t][jj], b, acc[jj], 0, 0, 0);
+        }
+    };
+    __syncthreads();
+    layer(W1r, IK1, xin, bias_s);
+    store(act[1]);
+    bf16x8 W4r[IK4];
+#pragma unroll
+    for (int t = 0; t < IK4; ++t) W4r[t] = ldfrag(rs, w4, t, lane16);
+    __syncthreads();
+    layer(W2r, IKS, act[1], bias_s + HID);
+    store(act[0]);
+    __syncthreads();
+    layer(W3r, IKS, act[0], bias_s + 2 * HID);
+    store(act[1]);
+    __syncthreads();
+    if (wv < 2) {   // the output layer: wave 0 the first 16 points, wave 1 the others
+        const int c = lane >> 4;
+        f32x4 o = {};
+#pragma unroll
+        for (int T = 0; T < IK4; ++T) {
+            const bf16x8 b = act[1][2 * T + (c >> 1)][32 * (c & 1) + 16 * wv + (lane & 15)];
+            o = __builtin_amdgcn_mfma_f32_16x16x32_bf16(W4r[T], b, o, 0, 0, 0);
+        }
+        const float4 bb = *reinterpret_cast<const float4 *>(bias_s + 3 * HID + 4 * c);
+        const int64_t r = (int64_t)tile * SP + 16 * wv + (lane & 15);
+        if (r < E.n)
+            y_store(Y + member * E.sY + r * OUTP + 4 * c,
+                    float4{o[0] + bb.x, o[1] + bb.y, o[2] + bb.z, o[3] + bb.w});
+        asm volatile("s_waitcnt vmcnt(0)" : : : "memory");   // there before the count below
+    }
+    __syncthreads();
+    // (counts modulo the number of members, so that it is 0 again for the next call)
+    if (tid == 0) s_last = atomicInc(&done[tile], (unsigned)E.members - 1u) == (unsigned)E.members - 1u;
+    __syncthreads();
+    if (!s_last) return;
+    const int64_t r = (int64_t)tile * SP + tid;
+    if (tid < SP && r < E.n) ensemble_point<VEC, true>(E, r);
+}
+
 }  // namespace mlp
 }  // namespace dd
 
@@ -1141,6 +1333,7 @@ struct dd_mlp {
     int64_t t = 0;                                        // Adam steps taken
     __bf16 *W1p = nullptr, *W2 = nullptr, *W3 = nullptr, *W4p = nullptr;
     __bf16 *Wi = nullptr;                                 // inference fragments [members][WI_PER]
+    unsigned *done = nullptr;                             // members done with a tile of k_mlp_infer_small (0 between calls)
     float *scal = nullptr;                                // device [2*36 + 2*12]
     float h_scal[SCAL];                                   // host copy
     float *dW1 = nullptr, *dW2 = nullptr, *dW3 = nullptr, *dW4 = nullptr, *db = nullptr;
@@ -1378,6 +1571,7 @@ extern "C" int dd_mlp_create(int n_members, uint64_t seed, dd_mlp **out)
     if (!rc) rc = dev_alloc((void **)&h->W4p, sizeof(__bf16) * M * OUTP * HID);
     if (!rc) rc = dev_alloc((void **)&h->Wi, sizeof(__bf16) * M * WI_PER);
     if (!rc) rc = dev_alloc((void **)&h->scal, sizeof(float) * SCAL);
+    if (!rc) rc = dev_alloc((void **)&h->done, sizeof(unsigned) * h->cus);
     // weight gradients hold one partial product per K split
     const int64_t k1 = ksplit(TILES_W1, n_members, TRAIN_MAX), k23 = ksplit(TILES_W23, n_members, TRAIN_MAX),
                   k4 = ksplit(TILES_W4, n_members, TRAIN_MAX);
@@ -1415,6 +1609,7 @@ extern "C" int dd_mlp_create(int n_members, uint64_t seed, dd_mlp **out)
     if (hipMemcpy(h->w, p.data(), sizeof(float) * M * P, hipMemcpyHostToDevice) != hipSuccess ||
         hipMemset(h->m1, 0, sizeof(float) * M * P) != hipSuccess ||
         hipMemset(h->m2, 0, sizeof(float) * M * P) != hipSuccess ||
+        hipMemset(h->done, 0, sizeof(unsigned) * h->cus) != hipSuccess ||
         hipMemcpy(h->scal, h->h_scal, sizeof h->h_scal, hipMemcpyHostToDevice) != hipSuccess) {
         dd_mlp_destroy(h);
         return set_error(DD_EHIP, "initialising the surrogate failed");
@@ -1432,7 +1627,7 @@ extern "C" int dd_mlp_destroy(dd_mlp *h)
     if (!h) return DD_OK;
     (void)hipDeviceSynchronize();
     free_rows(h);
-    void *ps[] = {h->w, h->m1, h->m2, h->W1p, h->W2, h->W3, h->W4p, h->Wi, h->scal, h->dW1, h->dW2, h->dW3, h->dW4,
+    void *ps[] = {h->w, h->m1, h->m2, h->W1p, h->W2, h->W3, h->W4p, h->Wi, h->done, h->scal, h->dW1, h->dW2, h->dW3, h->dW4,
                   h->db};
     for (void *p : ps)
         if (p) (void)hipFree(p);
@@ -1723,17 +1918,20 @@ extern "C" int dd_surrogate_rates(const dd_mlp *hc, int64_t n, const float *feat
     if ((rc = ensure_rows(h, chunk, false))) return rc;
     for (int64_t r0 = 0; r0 < n; r0 += chunk) {
         const int64_t m = std::min(chunk, n - r0);
+        float *ro = rates + r0 * OUT;
+        const EnsembleArgs E = {h->Y, m * OUTP, h->members, m, h->scal, spread_tol, ro, spread + r0, needs_dd + r0};
+        const bool vec = (uintptr_t)ro % 16 == 0;
+        const int64_t small = (m + SP - 1) / SP;
+        if (small * h->members <= h->cus) {
+            hipLaunchKernelGGL(vec ? k_mlp_infer_small<true> : k_mlp_infer_small<false>, dim3((unsigned)small, h->members), dim3(64 * IWAVES), 0, st,
+                               feat + r0 * IN, h->Wi, h->w, h->Y, h->done, E);
+            continue;
+        }
         const int ntiles = (int)((m + IP - 1) / IP);
         dim3 grid((unsigned)std::min(ntiles, std::max(1, h->cus / h->members)), h->members);
         hipLaunchKernelGGL(k_mlp_infer, grid, dim3(64 * IWAVES), 0, st, feat + r0 * IN, m, ntiles, h->scal, h->Wi,
                            h->w, h->Y, m * OUTP);
-        float *ro = rates + r0 * OUT;
-        if ((uintptr_t)ro % 16 == 0)
-            hipLaunchKernelGGL(k_ensemble<true>, dim3((unsigned)((m + 255) / 256)), dim3(256), 0, st, h->Y,
-                               m * OUTP, h->members, m, h->scal, spread_tol, ro, spread + r0, needs_dd + r0);
-        else
-            hipLaunchKernelGGL(k_ensemble<false>, dim3((unsigned)((m + 255) / 256)), dim3(256), 0, st, h->Y,
-                               m * OUTP, h->members, m, h->scal, spread_tol, ro, spread + r0, needs_dd + r0);
+        hipLaunchKernelGGL(vec ? k_ensemble<true> : k_ensemble<false>, dim3((unsigned)((m + 255) / 256)), dim3(256), 0, st, E);
     }
     DD_HIP(hipGetLastError());
     return DD_OK;
