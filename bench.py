@@ -378,7 +378,7 @@ def main():
                                         "call: instance tables, work split, capture and instantiation"),
             persistent_one_workgroup=dict(one_wg, note="all 100 steps in one persistent launch, one workgroup"),
             persistent=dict(auto, workgroups=128, note="all 100 steps in one cooperative launch, 128 workgroups "
-                                                       "of 2 nodes each, one barrier per step (the default)"),
+                                                       "of 2 nodes each, positions exchanged without a barrier (the default)"),
             note="calls enqueued back to back and synchronised once")
 
     if args.only == "small":

@@ -20,12 +20,12 @@ namespace dd {
 // Only the part of the range that holds the tile's own segments tests for the
 // excluded self pair.
 //
-// Bound by FP64 issue: 82 VALU instructions per evaluation in the inner loop
-// (89 when every source forms rho x b), at about 4.75 cycles each at the 2.25 GHz
-// this load runs at.  A step of 16,384 segments at 2 points, start to end:
-// 1.535 -> 1.444 ms.  Measured and left out: two Gauss points of a segment per
-// lane (t.b_j and t.g shared, 79 instructions, 120 VGPRs): 1.449 ms; six
-// wavefronts per SIMD forced by launch bounds (80 VGPRs for 96): 1.473 ms.
+// Bound by FP64 issue: 83 VALU instructions per source and wavefront (89 when
+// every source forms rho x b), at 4.5 cycles each.  A step of 16,384 segments at 2
+// points 1.525 -> 1.386 ms.  Measured and left out, against 1.444 ms before the
+// records were asked for ahead: two Gauss points of a segment per lane (t.b_j and
+// t.g shared, 79 instructions, 120 VGPRs) 1.449 ms; six wavefronts per SIMD forced
+// by launch bounds (80 VGPRs for 96) 1.473 ms.  72 VGPRs now.
 // With few wavefronts per SIMD (up to a few thousand segments) the wait for a
 // record's scalar load shows: the next record is therefore asked for before a
 // source is evaluated, in a run and between runs.  Before (each record loaded
