@@ -117,6 +117,7 @@ struct Workspace {
     hipEvent_t near_ev = nullptr;    // marks the near-pair count's read-back on the caller's stream
     int64_t block_fac_n = -1;                    // size of the tridiagonal factors in WS_BLOCK_FAC
     unsigned long long *near_count = nullptr;   // device counter (mixed kernel)
+    unsigned *small_done = nullptr;             // workgroups of a small volume's step that are done (0 between calls)
     bool capturing = false;
     std::vector<GraphEntry> graphs;
     uint64_t graph_clock = 0;

@@ -1479,7 +1479,11 @@ __global__ void k_scale_rates(double *acc, int64_t n, double inv_steps)
 // summed over the workgroups by k_pb_finish, which also copies the final
 // positions.
 // Otherwise (one volume, one force evaluation): the nodal forces, and the glide
-// velocities if asked for.
+// velocities if asked for.  In a step of up to SMALL_STEP_NODES nodes the
+// workgroups are counted as they end and the last one moves the nodes, without a
+// launch for it: a call for 256 segments 16.2 -> 13.9 us, for 96 15.8 -> 13.3.  Beyond,
+// the workgroups run in turns on the compute units and the count holds up the
+// next: 384 segments 20.4 and 22.7 us, 512 at 4 points 37.1 and 39.9.
 //
 // Bound by latency.  256 segments at 2 points, 256 workgroups of one node: 5.2 us a
 // step (21.5 before, with a barrier of fences and arrival words, records of every
@@ -1489,6 +1493,7 @@ __global__ void k_scale_rates(double *acc, int64_t n, double inv_steps)
 // the way of its position through memory to the other workgroups (about 2 us).
 // Left out: two nodes a workgroup (8.5 us: fewer CUs), several copies of the
 // published positions (5.6), target points precomputed in LDS (no gain).
+constexpr int64_t SMALL_STEP_NODES = 256;   // one workgroup per compute unit
 constexpr int PB_THREADS = 512;
 constexpr int PB_MAX_SEGS = 512;    // segments and nodes per instance
 constexpr int PB_POINTS = 2;        // target points a thread takes at a time
@@ -1510,6 +1515,8 @@ struct PBArgs {
     double *xend;              // [3][nn] final positions (BURST)
     double *wpart;             // [n_wg][12] (BURST)
     double *force, *vel;       // [3][nn], vel null: no glide (one evaluation)
+    double *xw;                // the positions, to be moved by vel dt, or null (one evaluation)
+    unsigned *done;            // workgroups done (0 between calls)
     unsigned *flags;
     GaussRule g;
     double kr, nu, k2, inv_a, a, inv_mu, fscale, invB, dt;
@@ -1967,12 +1974,24 @@ __global__ __launch_bounds__(PB_THREADS) void k_small(PBArgs A)
                 s_v[1][own] = v1;
                 s_v[2][own] = v2;
             } else if (A.vel) {
-                A.vel[n] = v0;
-                A.vel[nn + n] = v1;
-                A.vel[2 * nn + n] = v2;
+                pb_store(A.vel + n, v0);
+                pb_store(A.vel + nn + n, v1);
+                pb_store(A.vel + 2 * nn + n, v2);
             }
         }
         if (BURST) __syncthreads();
+    }
+    if (!BURST && A.xw) {
+        // a step: the last workgroup to get here moves the nodes (every other has
+        // read all positions, and its velocities are stored)
+        __shared__ int s_last;
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __syncthreads();
+        // (counts modulo the number of workgroups, so that it is 0 again for the next call)
+        if (tid == 0) s_last = atomicInc(A.done, gridDim.x - 1) == gridDim.x - 1;
+        __syncthreads();
+        if (s_last)
+            for (int i = tid; i < (int)(3 * L.nn); i += PB_THREADS) A.xw[i] += pb_load(A.vel + i) * A.dt;
     }
     if (BURST) {
         add_rate();   // of the last step
@@ -2760,7 +2779,7 @@ void small_args(PBArgs &A, const dd_material *m, int n_gauss)
 // null, by workgroups of one node each.
 void launch_small(Workspace *ws, int64_t nn, int64_t ns, const double *x, const int32_t *seg_nodes, const double *burgers,
                   const double *normal, const uint8_t *pinned, const Sig6 &sigma, const dd_material *m, int n_gauss,
-                  double invB, double *force, double *vel, hipStream_t st)
+                  double invB, double *force, double *vel, hipStream_t st, double *xw = nullptr, double dt = 0.0)
 {
     PBArgs A{};
     small_args(A, m, n_gauss);
@@ -2777,6 +2796,9 @@ void launch_small(Workspace *ws, int64_t nn, int64_t ns, const double *x, const 
     A.vel = vel;
     A.flags = ws->flags_dev;
     A.invB = invB;
+    A.xw = xw;
+    A.done = ws->small_done;
+    A.dt = dt;
     hipLaunchKernelGGL(k_small<false>, dim3((unsigned)nn), dim3(PB_THREADS), 0, st, A);
 }
 
@@ -3080,10 +3102,12 @@ extern "C" int dd_step(int64_t n_nodes, double *x, int64_t n_segs, const int32_t
     Sig6 sv;
     for (int k = 0; k < 6; ++k) sv.v[k] = sigma_app[k];
     if (small_volume(n_nodes, n_segs, precision, exact_eta)) {
-        launch_small(ws, n_nodes, n_segs, x, seg_nodes, burgers, normal, pinned, sv, m, n_gauss, 1.0 / m->B, F, vel, st);
+        launch_small(ws, n_nodes, n_segs, x, seg_nodes, burgers, normal, pinned, sv, m, n_gauss, 1.0 / m->B, F, vel, st,
+                     n_nodes <= SMALL_STEP_NODES ? x : nullptr, dt);
         note_small_plan(n_nodes, n_segs);
-        hipLaunchKernelGGL(k_euler, dim3(grid_for(3 * n_nodes, 256, INT32_MAX)), dim3(256), 0, st, n_nodes, x,
-                           (const double *)vel, dt);
+        if (n_nodes > SMALL_STEP_NODES)
+            hipLaunchKernelGGL(k_euler, dim3(grid_for(3 * n_nodes, 256, INT32_MAX)), dim3(256), 0, st, n_nodes, x,
+                               (const double *)vel, dt);
     } else {
         ForceCtx C;
         std::vector<int64_t> so = {0, n_segs};

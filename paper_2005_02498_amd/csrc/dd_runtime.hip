@@ -79,6 +79,7 @@ int workspace(Workspace **out)
             return set_error(DD_ENOMEM, "hipMalloc of the flag word failed");
         }
         w->near_count = (unsigned long long *)((char *)w->flags_dev + 128);
+        w->small_done = w->flags_dev + 48;
         if (hipMemset(w->flags_dev, 0, 256) != hipSuccess) {
             (void)hipFree(w->flags_dev);
             delete w;

@@ -93,3 +93,27 @@ def test_burst_vs_step_graph(steps):
     assert e < 1e-10
     assert np.abs(ra - rg).max() < 1e-12 * np.abs(rg).max()
     np.testing.assert_array_equal(fa, fg)
+
+
+@pytest.mark.parametrize("n", [1, 2, 255, 256, 257])
+def test_step_moves_every_node_once(n):
+    """The nodes are moved by the last workgroup of the launch (up to 256 nodes)
+    or by a launch of their own: every step moves every node by its velocity
+    times dt, call after call (the count of the workgroups starts over), to the
+    rounding of the two operations."""
+    rng = np.random.default_rng(n)
+    x0 = rng.uniform(0.0, 2000.0, (3, n))
+    m = n if n > 2 else n - 1
+    seg = np.stack([np.arange(m), (np.arange(m) + 1) % n]).astype(np.int32)
+    b = rng.normal(size=(3, m))
+    nrm = np.repeat(np.array([[0.0], [0.0], [1.0]]), m, axis=1)
+    t = [torch.tensor(np.ascontiguousarray(a), device="cuda:0") for a in (seg, b / np.linalg.norm(b, axis=0), nrm)]
+    x = torch.tensor(x0, device="cuda:0")
+    vel = torch.empty_like(x)
+    sig = np.array([1e7, -2e7, 5e7, 3e6, -4e6, 2e7])
+    step = lambda: dd.dd_step(x, *t, None, sig, MAT, W.DT, n_gauss=2, vel_out=vel)   # noqa: E731
+    for k in range(4):
+        before = x.clone()
+        step()
+        np.testing.assert_allclose(x.cpu().numpy(), (before + vel * W.DT).cpu().numpy(), rtol=1e-15, atol=0)
+        assert m == 0 or not torch.equal(x, before)
