@@ -566,7 +566,8 @@ __device__ __forceinline__ void glide_velocity(double F0, double F1, double F2, 
 // the same pass; otherwise F is read, lengths come from x and the Euler update
 // is a separate kernel.  Bound by latency (list, then what its entries name):
 // gather and glide took 4.6 + 4.8 us as two launches for 36,000 nodes, 5.8 + 7.6 us
-// for 16 volumes whose dummy nodes have 16 entries; together 5.2 and 8.4 us.
+// for 16 volumes whose dummy nodes have 16 entries; together 5.2 and 8.4 us, the
+// latter 4.8 since nodes that stay are not walked.
 template <bool FROM_REC>
 __global__ void k_glide(Layout L, const int32_t *__restrict__ ptr, const int32_t *__restrict__ list,
                         const int32_t *__restrict__ seg_nodes, const double *__restrict__ normal,
@@ -584,8 +585,11 @@ __global__ void k_glide(Layout L, const int32_t *__restrict__ ptr, const int32_t
     double ell = 0.0, f0 = 0.0, f1 = 0.0, f2 = 0.0;
     double nrm[3][3];
     int cnt = 0;
-    // two entries' loads in flight at a time (most nodes have two)
-    const int32_t kb = ptr[n], ke = ptr[n + 1];
+    // two entries' loads in flight at a time (most nodes have two); none for a node
+    // that stays where it is, such as the dummy nodes of free junction slots, whose
+    // lists are the longest, unless its force is asked for
+    const bool stuck = idle || (pinned && pinned[n]) || (held && held[n]);
+    const int32_t kb = ptr[n], ke = stuck && !(FROM_REC && F_out) ? kb : ptr[n + 1];
     for (int32_t k = kb; k < ke; k += 2) {
         const int32_t en[2] = {list[k], k + 1 < ke ? list[k + 1] : -1};
         double Ls[2], g[2][3], nv[2][3];
@@ -617,7 +621,7 @@ __global__ void k_glide(Layout L, const int32_t *__restrict__ ptr, const int32_t
         }
     }
     double v0 = 0, v1 = 0, v2 = 0;
-    const bool fixed = idle || (pinned && pinned[n]) || (held && held[n]) || !(ell > 0.0) || cnt == 0 || cnt >= 3;
+    const bool fixed = stuck || !(ell > 0.0) || cnt == 0 || cnt >= 3;
     if (FROM_REC) {
         if (F_out) {
             F_out[n] = f0;
