@@ -232,7 +232,7 @@ struct NearArgs {
 // pairs), then, once the pair arrays hold at least that many entries, the
 // fill pass and the exact integrals.  Pairs beyond pair_cap are dropped (they
 // keep the Q-point rule) and FLAG_NEAR_FULL is raised.
-void launch_near_count(const NearArgs &A, hipStream_t st);
+void launch_near_count(const NearArgs &A, hipStream_t st, bool keys_done = false);
 void launch_near_fill(const NearArgs &A, hipStream_t st);
 
 // Glide steps of a batch of independent volumes in which only some instances
