@@ -113,8 +113,9 @@ struct Workspace {
     size_t cap[WS_NSLOTS] = {};
     unsigned *flags_dev = nullptr;   // one word (sticky: cleared only when reported)
     unsigned *flags_host = nullptr;  // pinned mirror (bytes 64..71: near-pair count read-back)
+    int64_t *near_total = nullptr, *near_total_dev = nullptr;   // that word, as host and device address it
     hipStream_t capture_stream = nullptr;
-    hipEvent_t near_ev = nullptr;    // marks the near-pair count's read-back on the caller's stream
+    hipEvent_t near_ev = nullptr;    // marks the near-pair count as written, on the caller's stream
     int64_t block_fac_n = -1;                    // size of the tridiagonal factors in WS_BLOCK_FAC
     unsigned long long *near_count = nullptr;   // device counter (mixed kernel)
     unsigned *small_done = nullptr;             // workgroups of a small volume's step that are done (0 between calls)
@@ -232,7 +233,8 @@ struct NearArgs {
 // pairs), then, once the pair arrays hold at least that many entries, the
 // fill pass and the exact integrals.  Pairs beyond pair_cap are dropped (they
 // keep the Q-point rule) and FLAG_NEAR_FULL is raised.
-void launch_near_count(const NearArgs &A, hipStream_t st, bool keys_done = false);
+void launch_near_count(const NearArgs &A, hipStream_t st, bool keys_done = false,
+                       int64_t *total_host = nullptr);
 void launch_near_fill(const NearArgs &A, hipStream_t st);
 
 // Glide steps of a batch of independent volumes in which only some instances

@@ -2358,11 +2358,9 @@ int size_near_pairs(ForceCtx &C, Workspace *ws, const double *x, const int32_t *
     N.seg_inst = C.L.seg_inst;
     N.seg_off = C.L.seg_off;
     N.node_off = C.L.node_off;
-    launch_near_count(N, st);
-    int64_t *host = (int64_t *)((char *)ws->flags_host + 64);
-    DD_HIP(hipMemcpyAsync(host, N.woff + N.n_waves, sizeof(int64_t), hipMemcpyDeviceToHost, st));
+    launch_near_count(N, st, false, ws->near_total_dev);
     DD_HIP(hipStreamSynchronize(st));
-    const int64_t total = *host;
+    const int64_t total = *ws->near_total;
     if (total < 0 || total > (int64_t)INT32_MAX)
         return set_error(DD_ECAPACITY, "exact band: %lld near pairs (at most %d); use a narrower band",
                          (long long)total, INT32_MAX);
@@ -2492,13 +2490,10 @@ int launch_forces(ForceCtx &C, Workspace *ws, const double *x, const int32_t *se
         // it.  With size_pairs the count is read back behind the pair kernel:
         // the host waits for the count (an event), not for the pair kernel, and
         // sizes the pair store before the list is written.
-        int64_t *count_host = nullptr;
         if (C.near_on) {
-            launch_near_count(N, st, one_launch);
+            launch_near_count(N, st, one_launch, size_pairs ? ws->near_total_dev : nullptr);
             if (size_pairs) {
                 if (!ws->near_ev) DD_HIP(hipEventCreateWithFlags(&ws->near_ev, hipEventDisableTiming));
-                count_host = (int64_t *)((char *)ws->flags_host + 64);
-                DD_HIP(hipMemcpyAsync(count_host, N.woff + N.n_waves, sizeof(int64_t), hipMemcpyDeviceToHost, st));
                 DD_HIP(hipEventRecord(ws->near_ev, st));
             }
         }
@@ -2514,7 +2509,7 @@ int launch_forces(ForceCtx &C, Workspace *ws, const double *x, const int32_t *se
         if (C.near_on) {
             if (size_pairs) {
                 DD_HIP(hipEventSynchronize(ws->near_ev));
-                const int64_t total = *count_host;
+                const int64_t total = *ws->near_total;
                 if (total < 0 || total > (int64_t)INT32_MAX)
                     return set_error(DD_ECAPACITY, "exact band: %lld near pairs (at most %d); use a narrower band",
                                      (long long)total, INT32_MAX);

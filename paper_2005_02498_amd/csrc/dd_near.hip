@@ -360,14 +360,15 @@ __global__ __launch_bounds__(256) void k_near_exact(NearArgs A)
 
 }  // namespace
 
-void launch_near_count(const NearArgs &A, hipStream_t st, bool keys_done)
+void launch_near_count(const NearArgs &A, hipStream_t st, bool keys_done, int64_t *total_host)
 {
     if (A.ns <= 0) return;
     const unsigned tb = (unsigned)((A.ns + 255) / 256);
     if (!keys_done) hipLaunchKernelGGL(k_near_keys, dim3(tb), dim3(256), 0, st, A);
     hipLaunchKernelGGL(k_near_list<0>, dim3(tb, (unsigned)A.splits), dim3(256), 0, st, A);
     hipLaunchKernelGGL(k_near_count, dim3(tb), dim3(256), 0, st, A);
-    hipLaunchKernelGGL(k_scan, dim3(1), dim3(1024), 0, st, (const int64_t *)A.wtot, A.n_waves, A.woff);
+    hipLaunchKernelGGL(k_scan, dim3(1), dim3(1024), 0, st, (const int64_t *)A.wtot, A.n_waves, A.woff,
+                       total_host);
 }
 
 void launch_near_fill(const NearArgs &A, hipStream_t st)

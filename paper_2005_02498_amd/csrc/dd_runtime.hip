@@ -90,6 +90,13 @@ int workspace(Workspace **out)
             delete w;
             return set_error(DD_ENOMEM, "hipHostMalloc of the flag mirror failed");
         }
+        w->near_total = (int64_t *)((char *)w->flags_host + 64);
+        if (hipHostGetDevicePointer((void **)&w->near_total_dev, w->near_total, 0) != hipSuccess) {
+            (void)hipHostFree(w->flags_host);
+            (void)hipFree(w->flags_dev);
+            delete w;
+            return set_error(DD_EHIP, "hipHostGetDevicePointer of the flag mirror failed");
+        }
         g_ws[dev] = w;
     }
     *out = g_ws[dev];
