@@ -430,6 +430,12 @@ __global__ void k_csr_sort(const int32_t *ptr, int64_t nn, int32_t *list)
 // ------------------------------ a3 + a4: Peach-Koehler and the quadrature --
 struct Sig6 { double v[6]; };
 
+// (one wavefront a workgroup: bound by latency, so the wavefronts are spread over
+// as many compute units as there are; workgroups of 256, now of 64: a step of 1,024
+// segments 30.8 -> 28.2 us, of 1,107 with the exact band 108.0 -> 103.0 us, of which
+// 1.7 us are the corrections of four near pairs loaded at a time, of 4,096 with
+// the band 184.6 -> 180.8 us, this kernel at 16,384 6.8 -> 5.6 us)
+constexpr int ENDS_BLOCK = 64;
 __global__ void k_segment_ends(Layout L, const Tile *__restrict__ tiles,
                                const double *__restrict__ partial,
                                const double *__restrict__ rec, GaussRule g,
@@ -455,6 +461,8 @@ __global__ void k_segment_ends(Layout L, const Tile *__restrict__ tiles,
     const double ab1 = S[5] * b0 + S[1] * b1 + S[3] * b2;
     const double ab2 = S[4] * b0 + S[3] * b1 + S[2] * b2;
     double F1[3] = {0, 0, 0}, F2[3] = {0, 0, 0};
+    const int64_t p0 = near_ptr ? near_ptr[j] : 0;
+    const int nc = near_ptr ? (int)max((int64_t)0, min((int64_t)near_cnt[j], pair_cap - p0)) : 0;
     // an instance left out of the work plan (idle in this pass) has no tiles
     const bool has_tiles = !L.tile_begin || L.tile_begin[inst + 1] > tb;
     for (int q = 0; q < Q; ++q) {
@@ -485,9 +493,8 @@ __global__ void k_segment_ends(Layout L, const Tile *__restrict__ tiles,
     }
     // exact band: (exact - Q-point) for this target's near sources, in source order
     if (near_ptr) {
-        const int64_t p0 = near_ptr[j];
-        const int nc = near_cnt[j];
-        for (int k = 0; k < nc && p0 + k < pair_cap; ++k) {
+#pragma unroll 4
+        for (int k = 0; k < nc; ++k) {
             const double *o = near_corr + 6 * (p0 + k);
             F1[0] += o[0]; F1[1] += o[1]; F1[2] += o[2];
             F2[0] += o[3]; F2[1] += o[4]; F2[2] += o[5];
@@ -2522,7 +2529,7 @@ int launch_forces(ForceCtx &C, Workspace *ws, const double *x, const int32_t *se
             }
             launch_near_fill(N, st);
         }
-        hipLaunchKernelGGL(k_segment_ends, dim3(grid_for(ns, 256, INT32_MAX)), dim3(256), 0, st, C.L,
+        hipLaunchKernelGGL(k_segment_ends, dim3(grid_for(ns, ENDS_BLOCK, INT32_MAX)), dim3(ENDS_BLOCK), 0, st, C.L,
                            C.tiles, C.partial, C.rec64, C.g, sig_dev, sig_val, C.inv_mu, C.fscale,
                            C.segF, C.near_on ? (const int64_t *)C.near.ptr : nullptr,
                            (const int32_t *)C.near.cnt, (const double *)C.near.corr, C.near.pair_cap);
@@ -2675,7 +2682,7 @@ int tuned_chunk(Workspace *ws, hipStream_t st, const std::vector<int64_t> &so, i
                 launch_pair64(C.items, C.tiles, C.rec64, ns, C.g, C.k1, C.k2, C.partial, C.n_items, st);
             // the reduction of the partial sums grows with the number of work
             // items, so it is part of the cost being compared
-            hipLaunchKernelGGL(k_segment_ends, dim3(grid_for(ns, 256, INT32_MAX)), dim3(256), 0, st, A.L,
+            hipLaunchKernelGGL(k_segment_ends, dim3(grid_for(ns, ENDS_BLOCK, INT32_MAX)), dim3(ENDS_BLOCK), 0, st, A.L,
                                C.tiles, C.partial, C.rec64, C.g, (const double *)nullptr, Sig6{}, C.inv_mu,
                                C.fscale, C.segF, (const int64_t *)nullptr, (const int32_t *)nullptr,
                                (const double *)nullptr, (int64_t)0);
