@@ -436,6 +436,10 @@ struct Sig6 { double v[6]; };
 // 1.7 us are the corrections of four near pairs loaded at a time, of 4,096 with
 // the band 184.6 -> 180.8 us, this kernel at 16,384 6.8 -> 5.6 us)
 constexpr int ENDS_BLOCK = 64;
+// (the same for the kernels of a thread per node: a step of 1,024 segments 28.00 ->
+// 27.75 us, of 4,096 with the band 179.1 -> 178.6 us)
+constexpr int NODE_BLOCK = 64;
+
 __global__ void k_segment_ends(Layout L, const Tile *__restrict__ tiles,
                                const double *__restrict__ partial,
                                const double *__restrict__ rec, GaussRule g,
@@ -2535,7 +2539,7 @@ int launch_forces(ForceCtx &C, Workspace *ws, const double *x, const int32_t *se
                            (const int32_t *)C.near.cnt, (const double *)C.near.corr, C.near.pair_cap);
     }
     if (with_lists && ns == 0) launch_csr(C, seg_nodes, st);
-    if (F) hipLaunchKernelGGL(k_node_gather, dim3(grid_for(nn, 256, INT32_MAX)), dim3(256), 0, st, C.csr_ptr,
+    if (F) hipLaunchKernelGGL(k_node_gather, dim3(grid_for(nn, NODE_BLOCK, INT32_MAX)), dim3(NODE_BLOCK), 0, st, C.csr_ptr,
                        C.csr_list, nn, ns, C.segF, F);
     return DD_OK;
 }
@@ -2980,7 +2984,7 @@ int burst_batch_run(const BurstBatch &B, const std::vector<uint8_t> &active, con
                                    B.fast_steps_dev, B.dt, k, held);
             const int r = launch_forces(C, ws, B.x, B.seg_nodes, B.burgers, B.normal, sigma_dev, sv, nullptr, cs, false);
             if (r) return r;
-            hipLaunchKernelGGL(k_glide<true>, dim3(grid_for(nn, 256, INT32_MAX)), dim3(256), 0, cs, C.L,
+            hipLaunchKernelGGL(k_glide<true>, dim3(grid_for(nn, NODE_BLOCK, INT32_MAX)), dim3(NODE_BLOCK), 0, cs, C.L,
                                C.csr_ptr, C.csr_list, B.seg_nodes, B.normal, (const double *)C.rec64,
                                (const double *)C.segF, C.a, B.x, (const double *)nullptr, (double *)nullptr, B.pinned,
                                (const uint8_t *)held, (const uint8_t *)d_act, 1.0 / B.mat.B, B.dt, vel);
@@ -3206,7 +3210,7 @@ extern "C" int dd_step(int64_t n_nodes, double *x, int64_t n_segs, const int32_t
         g_last_variant = C.variant;
         if ((rc = launch_forces(C, ws, x, seg_nodes, burgers, normal, nullptr, sv, nullptr, st, true, true))) return rc;
         // forces and lengths from the end forces and records of this force pass: x can move in the same kernel
-        hipLaunchKernelGGL(k_glide<true>, dim3(grid_for(n_nodes, 256, INT32_MAX)), dim3(256), 0, st, C.L, C.csr_ptr,
+        hipLaunchKernelGGL(k_glide<true>, dim3(grid_for(n_nodes, NODE_BLOCK, INT32_MAX)), dim3(NODE_BLOCK), 0, st, C.L, C.csr_ptr,
                            C.csr_list, seg_nodes, normal, (const double *)C.rec64, (const double *)C.segF, C.a, x,
                            (const double *)nullptr, F, pinned, (const uint8_t *)nullptr, (const uint8_t *)nullptr, 1.0 / m->B, dt, vel);
     }
@@ -3441,7 +3445,7 @@ int burst_graph(Workspace *ws, const Layout &inst, int32_t n_inst, const std::ve
                 }
                 const int r = launch_forces(C, ws, x, seg_nodes, burgers, normal, sigma_app, sv, nullptr, cs, false);
                 if (r) return r;
-                hipLaunchKernelGGL(k_glide<true>, dim3(grid_for(nn, 256, INT32_MAX)), dim3(256), 0, cs, C.L,
+                hipLaunchKernelGGL(k_glide<true>, dim3(grid_for(nn, NODE_BLOCK, INT32_MAX)), dim3(NODE_BLOCK), 0, cs, C.L,
                                    C.csr_ptr, C.csr_list, seg_nodes, normal, (const double *)C.rec64,
                                    (const double *)C.segF, C.a, x, (const double *)nullptr, (double *)nullptr, pinned,
                                    (const uint8_t *)held, (const uint8_t *)nullptr, 1.0 / m->B, dt, vel);
