@@ -131,15 +131,23 @@ int dd_set_autotune(int on);
  * for the split).  The positions do not depend on the split; the slip rates, and
  * the results of the step graph, differ only in the order of floating-point
  * sums.  Returns the previous mode, or DD_EINVAL for a mode other than 0, 1 and
- * 2.  A persistent burst whose workgroups wait too long for a position raises
- * DD_EHIP (reported as the device-side checks are). */
+ * 2.  A persistent burst whose workgroups wait too long for a position (see
+ * dd_set_burst_wait) raises DD_EHIP, reported as the device-side checks are;
+ * it leaves the positions of every instance of the call as they were and
+ * writes NaN to every slip rate. */
 int dd_set_burst_mode(int mode);
+
+/* The longest time, in microseconds, that a workgroup of a persistent burst
+ * waits for another's positions of a step: 2 s unless set, 0 to give up at the
+ * first look that does not find them, at most 3 hours.  Returns the previous
+ * time, or DD_EINVAL for one outside that range. */
+int64_t dd_set_burst_wait(int64_t microseconds);
 
 /* Report, and clear, the conditions the device-side checks raised since the
  * last report: synchronises `stream` (hipStream_t, may be null) and returns
  * DD_OK, or the error code and message of the first condition in the order
  * DD_EINVAL (bad node index, zero-length segment, normal not of unit
- * length), DD_ENONFINITE, DD_ECAPACITY (exact band: a captured step's near
+ * length), DD_EHIP (a persistent burst that waited too long), DD_ENONFINITE, DD_ECAPACITY (exact band: a captured step's near
  * pairs outgrew the pair store, see dd_burst_batch).  Calls made with
  * validation on report them themselves; with validation off they stay
  * pending until this call or the next validating call. */

@@ -1563,7 +1563,10 @@ constexpr int64_t SMALL_STEP_NODES = 256;   // one workgroup per compute unit
 constexpr int PB_THREADS = 512;
 constexpr int PB_MAX_SEGS = 512;    // segments and nodes per instance
 constexpr int PB_POINTS = 2;        // target points a thread takes at a time
-constexpr uint64_t PB_WAIT_TICKS = 200000000ull;   // longest wait for a position: 2 s of the 100 MHz wall clock
+constexpr int64_t PB_TICKS_PER_US = 100;   // of wall_clock64
+// (waits are compared with this constant: with the limit itself read in the loop
+// a step took 4.9 us instead of 4.8)
+constexpr uint64_t PB_MAX_TICKS = 1ull << 40;   // three hours
 constexpr unsigned long long PB_EMPTY = 0x7ff4dd5e9a3c7b11ull;
 
 struct PBArgs {
@@ -1584,6 +1587,8 @@ struct PBArgs {
     double *xw;                // the positions, to be moved by vel dt, or null (one evaluation)
     unsigned *done;            // workgroups done (0 between calls)
     unsigned *flags;
+    unsigned *gave_up;         // set by a workgroup that waited too long (BURST)
+    uint64_t early;            // PB_MAX_TICKS less the longest wait for a position
     GaussRule g;
     double kr, nu, k2, inv_a, a, inv_mu, fscale, invB, dt;
     int n_steps;
@@ -1824,13 +1829,14 @@ __global__ __launch_bounds__(PB_THREADS) void k_small(PBArgs A)
         if (BURST && k > 0) add_rate();
         if (tid < nn_i) {
             if (BURST && k > 0) {
-                const uint64_t t0 = wall_clock64();
+                const uint64_t t0 = wall_clock64() - A.early;
                 for (;;) {
                     bool all = true;
                     for (int c = 0; c < 3; ++c) all = all && (unsigned long long)__double_as_longlong(v[c]) != PB_EMPTY;
                     if (all) break;
-                    if (wall_clock64() - t0 > PB_WAIT_TICKS) {
+                    if (wall_clock64() - t0 > PB_MAX_TICKS) {
                         atomicOr(A.flags, FLAG_BARRIER);
+                        *A.gave_up = 1u;
                         ok = 0;
                         break;
                     }
@@ -2078,21 +2084,24 @@ __global__ __launch_bounds__(PB_THREADS) void k_small(PBArgs A)
 }
 
 // Buffers of unpublished positions before a burst.
-__global__ void k_pb_empty(double *p, int64_t n)
+__global__ void k_pb_empty(double *p, int64_t n, unsigned *gave_up)
 {
     const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
     if (i < n) p[i] = __longlong_as_double((long long)PB_EMPTY);
+    if (i == 0) *gave_up = 0u;
 }
 
 // After the last step: positions to the caller's array, and per instance the
 // slip-rate sums of its workgroups, in order, over the number of steps; sixteen
 // loads in flight (one after the other, 128 workgroups' sums took 52 us of a
-// burst's 520, now 12).
-__global__ void k_pb_finish(const int32_t *wg, int n_wg, int n_inst, const double *wpart, double inv_steps,
-                            double *rate_out, int64_t n3, const double *xend, double *x)
+// burst's 520, now 12).  A burst that a workgroup gave up has no end positions
+// and no sums: the caller's positions stay, the rates are NaN.
+__global__ void k_pb_finish(const int32_t *wg, int n_wg, int n_inst, const double *wpart, const unsigned *gave_up,
+                            double inv_steps, double *rate_out, int64_t n3, const double *xend, double *x)
 {
     const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (i < n3) x[i] = xend[i];
+    const bool failed = *gave_up != 0u;
+    if (i < n3 && !failed) x[i] = xend[i];
     if (i < 12 * (int64_t)n_wg && wg[n_wg + i / 12] == 0) {
         const int64_t first = i / 12, al = i % 12;
         const int m = wg[2 * n_wg + first];
@@ -2106,7 +2115,7 @@ __global__ void k_pb_finish(const int32_t *wg, int n_wg, int n_inst, const doubl
             for (int k = 0; k < 16; ++k)
                 if (v + k < m) sum += u[k];
         }
-        rate_out[12 * (int64_t)wg[first] + al] = sum * inv_steps;
+        rate_out[12 * (int64_t)wg[first] + al] = failed ? __builtin_nan("") : sum * inv_steps;
     }
 }
 
@@ -2142,13 +2151,13 @@ int read_flags(Workspace *ws, hipStream_t st)
         return set_error(DD_EINVAL, "a segment references a node index outside its instance%s", w);
     if (f & FLAG_ZERO_LENGTH) return set_error(DD_EINVAL, "zero-length (or non-finite) segment%s", w);
     if (f & FLAG_BAD_NORMAL) return set_error(DD_EINVAL, "slip-plane normal is not of unit length%s", w);
+    if (f & FLAG_BARRIER)   // (before the NaN rates it leaves)
+        return set_error(DD_EHIP, "persistent burst: a workgroup waited too long for a position%s", w);
     if (f & FLAG_NONFINITE) return set_error(DD_ENONFINITE, "non-finite value in an output%s", w);
     if (f & FLAG_NEAR_FULL)
         return set_error(DD_ECAPACITY, "exact band: the near pairs of a captured step outgrew the pair store "
                          "sized at the start of the burst%s", w);
     if (f & FLAG_NEAR_PANELS) return set_error(DD_EINVAL, "exact band: a pair integral did not converge%s", w);
-    if (f & FLAG_BARRIER)
-        return set_error(DD_EHIP, "persistent burst: a workgroup waited too long at a step barrier%s", w);
     return DD_OK;
 }
 
@@ -2557,6 +2566,7 @@ int launch_forces(ForceCtx &C, Workspace *ws, const double *x, const int32_t *se
 // to the file named by DD_AUTOTUNE_CACHE, read back at start-up).
 std::atomic<int> g_autotune{1};
 std::atomic<int> g_burst_mode{0};   // dd_set_burst_mode: 0 automatic, 1 step graphs, 2 persistent, one workgroup each
+std::atomic<int64_t> g_burst_wait{2000000};   // dd_set_burst_wait, in us
 std::atomic<int64_t> g_forced_choice{-1};   // dd_set_plan: encoded split, or -1
 
 struct TuneKey {
@@ -3011,6 +3021,15 @@ extern "C" int dd_set_burst_mode(int mode)
     return dd::g_burst_mode.exchange(mode);
 }
 
+extern "C" int64_t dd_set_burst_wait(int64_t microseconds)
+{
+    clear_error();
+    const int64_t most = (int64_t)PB_MAX_TICKS / PB_TICKS_PER_US;
+    if (microseconds < 0 || microseconds > most)
+        return set_error(DD_EINVAL, "burst wait must be in 0..%lld us", (long long)most);
+    return dd::g_burst_wait.exchange(microseconds);
+}
+
 extern "C" int dd_check(void *stream)
 {
     clear_error();
@@ -3299,14 +3318,15 @@ int launch_persistent(Workspace *ws, const Layout &L, const std::vector<int64_t>
     const int64_t nn = no.back(), n3 = 3 * std::max<int64_t>(nn, 1);
     void *p;
     int rc;
-    if ((rc = ensure(ws, WS_PB, sizeof(double) * (4 * (size_t)n3 + 12 * (size_t)n_wg), &p))) return rc;
-    double *xbuf = (double *)p;
+    if ((rc = ensure(ws, WS_PB, sizeof(double) * (4 * (size_t)n3 + 12 * (size_t)n_wg + 1), &p))) return rc;
+    double *xbuf = (double *)p, *wpart = xbuf + 4 * n3;
+    unsigned *gave_up = (unsigned *)(wpart + 12 * (size_t)n_wg);
     int32_t *wgtab = (int32_t *)ws->ptr[WS_PB_INT];
     if (tab != ws->pb_tab || !wgtab) {   // uploaded (one synchronisation) only when the table changes
         if ((rc = upload(ws, WS_PB_INT, tab, &wgtab, st))) return rc;
         ws->pb_tab = tab;
     }
-    hipLaunchKernelGGL(k_pb_empty, dim3(grid_for(3 * n3, 256, INT32_MAX)), dim3(256), 0, st, xbuf, 3 * n3);
+    hipLaunchKernelGGL(k_pb_empty, dim3(grid_for(3 * n3, 256, INT32_MAX)), dim3(256), 0, st, xbuf, 3 * n3, gave_up);
     PBArgs A{};
     small_args(A, m, n_gauss);
     A.L = L;
@@ -3321,8 +3341,10 @@ int launch_persistent(Workspace *ws, const Layout &L, const std::vector<int64_t>
     A.x = x;
     A.xbuf = xbuf;
     A.xend = xbuf + 3 * n3;
-    A.wpart = A.xend + n3;
+    A.wpart = wpart;
     A.flags = ws->flags_dev;
+    A.gave_up = gave_up;
+    A.early = PB_MAX_TICKS - (uint64_t)(g_burst_wait.load() * PB_TICKS_PER_US);
     A.invB = 1.0 / m->B;
     A.dt = dt;
     A.n_steps = n_steps;
@@ -3334,8 +3356,8 @@ int launch_persistent(Workspace *ws, const Layout &L, const std::vector<int64_t>
         return DD_OK;
     }
     hipLaunchKernelGGL(k_pb_finish, dim3(grid_for(std::max<int64_t>(3 * nn, 12 * (int64_t)n_wg), 256, INT32_MAX)), dim3(256),
-                       0, st, (const int32_t *)wgtab, n_wg, n_inst, (const double *)A.wpart, 1.0 / n_steps, rate_avg_out,
-                       3 * nn, (const double *)A.xend, x);
+                       0, st, (const int32_t *)wgtab, n_wg, n_inst, (const double *)wpart, (const unsigned *)gave_up,
+                       1.0 / n_steps, rate_avg_out, 3 * nn, (const double *)A.xend, x);
     *used = true;
     return DD_OK;
 }
