@@ -2899,11 +2899,11 @@ void launch_small(Workspace *ws, int64_t nn, int64_t ns, const double *x, const 
     hipLaunchKernelGGL(k_small<false>, dim3((unsigned)nn), dim3(PB_THREADS), 0, st, A);
 }
 
-// (for dd_last_plan: every workgroup takes all sources)
-void note_small_plan(int64_t nn, int64_t ns)
+// (for dd_last_plan: every workgroup takes all sources of its volume)
+void note_small_plan(int64_t workgroups, int64_t ns)
 {
     g_last_chunk = ns;
-    g_last_items = nn;
+    g_last_items = workgroups;
     g_last_variant = 0;
 }
 
@@ -3296,7 +3296,8 @@ int plan_persistent(Workspace *ws, const std::vector<int64_t> &no, const std::ve
     return DD_OK;
 }
 
-int launch_persistent(Workspace *ws, const Layout &L, const std::vector<int64_t> &no, const std::vector<int> &G, double *x,
+int launch_persistent(Workspace *ws, const Layout &L, const std::vector<int64_t> &no, const std::vector<int64_t> &so,
+                      const std::vector<int> &G, double *x,
                       const int32_t *seg_nodes, const double *burgers, const double *normal, const uint8_t *pinned,
                       const double *sigma_app, const double *volume, const dd_material *m, int n_gauss, int n_steps,
                       double dt, double *rate_avg_out, hipStream_t st, bool *used)
@@ -3358,6 +3359,9 @@ int launch_persistent(Workspace *ws, const Layout &L, const std::vector<int64_t>
     hipLaunchKernelGGL(k_pb_finish, dim3(grid_for(std::max<int64_t>(3 * nn, 12 * (int64_t)n_wg), 256, INT32_MAX)), dim3(256),
                        0, st, (const int32_t *)wgtab, n_wg, n_inst, (const double *)wpart, (const unsigned *)gave_up,
                        1.0 / n_steps, rate_avg_out, 3 * nn, (const double *)A.xend, x);
+    int64_t longest = 0;
+    for (int i = 0; i < n_inst; ++i) longest = std::max(longest, so[i + 1] - so[i]);
+    note_small_plan(n_wg, longest);
     *used = true;
     return DD_OK;
 }
@@ -3569,7 +3573,7 @@ int burst_batch_impl(int32_t n_inst, const int64_t *node_off, const int64_t *seg
                 hipLaunchKernelGGL(k_instance_sums<1>, dim3(n_inst), dim3(256), 0, st, L, seg_nodes, A.rec64, A.sys,
                                    (const double *)nullptr, pinned, volume, sigma_app, m->a, features_out);
             }
-            if ((rc = launch_persistent(ws, L, no, G, x, seg_nodes, burgers, normal, pinned, sigma_app, volume, m, n_gauss,
+            if ((rc = launch_persistent(ws, L, no, so, G, x, seg_nodes, burgers, normal, pinned, sigma_app, volume, m, n_gauss,
                                         n_steps, dt, rate_avg_out, st, &persistent)))
                 return rc;
         }
