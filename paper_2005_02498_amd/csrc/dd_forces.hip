@@ -157,7 +157,8 @@ __device__ __forceinline__ int seg_system(const double *b, const double *nv)
     return found;
 }
 
-// The PREP_BLOCK segments from PREP_BLOCK bid, by as many threads.
+// The PREP_BLOCK segments from PREP_BLOCK bid, by the first as many threads of
+// the workgroup; every thread of it has to come here (there are barriers).
 __device__ __forceinline__ void seg_prep(const PrepArgs &A, int64_t bid)
 {
     __shared__ int64_t sh_g1[PREP_BLOCK], sh_g2[PREP_BLOCK];
@@ -166,7 +167,7 @@ __device__ __forceinline__ void seg_prep(const PrepArgs &A, int64_t bid)
     const int tid = threadIdx.x;
     const int64_t s = bid * PREP_BLOCK + tid;
     const int64_t ns = A.L.ns, nn = A.L.nn;
-    const bool live = s < ns;
+    const bool part = tid < PREP_BLOCK, live = part && s < ns;
     unsigned fl = 0;
     int64_t g1 = -1, g2 = -1;
     int inst = -1;
@@ -174,9 +175,11 @@ __device__ __forceinline__ void seg_prep(const PrepArgs &A, int64_t bid)
         if (!seg_ends(A.L, A.seg_nodes, s, g1, g2)) fl |= FLAG_BAD_INDEX;
         inst = seg_instance(A.L, s);
     }
-    sh_g1[tid] = g1;
-    sh_g2[tid] = g2;
-    sh_inst[tid] = inst;
+    if (part) {
+        sh_g1[tid] = g1;
+        sh_g2[tid] = g2;
+        sh_inst[tid] = inst;
+    }
     __syncthreads();
     // does the next segment of this workgroup start at the node where this one
     // ends, with the same Burgers vector?
@@ -184,7 +187,7 @@ __device__ __forceinline__ void seg_prep(const PrepArgs &A, int64_t bid)
     if (chain)
         for (int k = 0; k < 3; ++k) chain = chain && A.burgers[k * ns + s + 1] == A.burgers[k * ns + s];
     const unsigned long long chains = __ballot(chain);
-    if ((tid & 63) == 0) sh_chain[tid >> 6] = chains;
+    if (part && (tid & 63) == 0) sh_chain[tid >> 6] = chains;
     __syncthreads();
     if (!live) return;
     double rr[13];
@@ -375,11 +378,12 @@ template <bool KEYS>
 __global__ __launch_bounds__(CSR_THREADS) void k_prep_lists(PrepArgs A, NearArgs N, int32_t *__restrict__ ptr,
                                                             int32_t *__restrict__ list)
 {
-    if (blockIdx.x == gridDim.x - 1)
+    if (blockIdx.x == gridDim.x - 1) {
         csr_block(A.L, 0, A.seg_nodes, ptr, list);
-    else if (threadIdx.x < PREP_BLOCK)
-        seg_prep(A, blockIdx.x);
-    else if (KEYS && threadIdx.x < 2 * PREP_BLOCK)
+        return;
+    }
+    seg_prep(A, blockIdx.x);
+    if (KEYS && threadIdx.x >= PREP_BLOCK && threadIdx.x < 2 * PREP_BLOCK)
         near_keys(N, blockIdx.x * (int64_t)PREP_BLOCK + threadIdx.x - PREP_BLOCK);
 }
 
