@@ -2643,10 +2643,25 @@ int tuned_chunk(Workspace *ws, hipStream_t st, const std::vector<int64_t> &so, i
     hipDeviceProp_t prop;
     DD_HIP(hipGetDeviceProperties(&prop, ws->device));
     TuneKey key{prop.gcnArchName, Q, prec, ceil_log2(n_inst), ceil_log2(ns), ceil_log2(nmax)};
+    // Source ranges of 64 are the shortest, but in FP64, whose wavefronts need no
+    // staging of sources, 32 where ranges of 64 leave the device short of work items,
+    // fewer than two for each compute unit.  A step in ranges of 64 and 32: 1,024
+    // segments at 2 points, 128 items of 64, 31.5 and 28.2 us, shuffled 41.3 and 32.2;
+    // 1,312 shuffled ones at 3 points, 336 items, 59.0 and 50.2; 2,048 at 2 points, 512
+    // items, 45.6 and 50.4, shuffled 58.7 and 58.6; 4,096, 2,048 items, 115.7 and 128.6.
+    // (A candidate's partial sums, 6 KB per item and quadratic in the segments, stay
+    // in the workspace.)  Where only some sizes of a class are that small, they are a
+    // class of their own.
+    int64_t items64 = 0;
+    for (int i = 0; i < n_inst; ++i) items64 += ((so[i + 1] - so[i]) * Q + TILE - 1) / TILE * ((so[i + 1] - so[i] + 63) / 64);
+    const int64_t enough = 2 * (int64_t)prop.multiProcessorCount;
+    const bool few = prec == DD_FP64 && items64 < enough;
+    if (few && ((int64_t(1) << key.ls) * Q / TILE) * ((int64_t(1) << key.lm) / 64) >= enough) key.lm += 64;
     std::lock_guard<std::mutex> lk(g_tune_mu);
     load_tune_cache();
     auto itk = g_tuned.find(key);
-    if (itk != g_tuned.end()) {
+    // (a saved choice of a range not offered here is passed over)
+    if (itk != g_tuned.end() && (few || prec != DD_FP64 || itk->second / MIXED_VARIANTS != 32)) {
         *out = itk->second;
         return DD_OK;
     }
@@ -2654,10 +2669,7 @@ int tuned_chunk(Workspace *ws, hipStream_t st, const std::vector<int64_t> &so, i
     // a choice is encoded as MIXED_VARIANTS * chunk_length + mixed-kernel variant
     std::vector<int64_t> chunks = {0};
     // short ranges spread small batches over more CUs; long ones need fewer partial sums
-    // (in mixed precision down to 64; in FP64, whose wavefronts need no staging of
-    // sources, down to 32: a step of 1,024 segments 32.8 us in ranges of 64, 30.5 of 32,
-    // 36.6 of 16, of 1,024 shuffled ones 43.2, 35.2 and 40.1)
-    for (int64_t c = prec == DD_FP64 ? 32 : 64; c < nmax; c *= 2) chunks.push_back(c);
+    for (int64_t c = few ? 32 : 64; c < nmax; c *= 2) chunks.push_back(c);
     chunks.push_back(((nmax + TILE - 1) / TILE) * TILE);   // one range per tile
     std::vector<int64_t> cands;
     for (int64_t c : chunks)
