@@ -178,8 +178,10 @@ int dd_set_plan(int64_t chunk_len, int variant);
 int dd_last_plan(int64_t *chunk_len, int64_t *n_items, int *variant);
 
 /* Measurement hooks (for benchmarks and profilers).  With timing on, every
- * launch of the all-pairs kernel made outside graph capture is bracketed by a
- * HIP event pair recorded on the caller's stream.  dd_timing_read waits for
+ * launch of the all-pairs kernel made outside graph capture (for a small FP64
+ * volume, see dd_last_plan, the one launch of its evaluation or step) is
+ * bracketed by a HIP event pair recorded on the caller's stream; nothing else
+ * changes.  dd_timing_read waits for
  * the recorded events and returns, since the last reset: the summed
  * event-to-event time of those launches in milliseconds, the number of
  * launches, and how many (target Gauss point, source segment) evaluations

@@ -2866,13 +2866,12 @@ int presize_near(ForceCtx &C, Workspace *ws, const double *x, const int32_t *seg
 
 // ---------------------------------------------------------- small volumes --
 // Whether one FP64 force evaluation of a volume goes to k_small: a volume that
-// fits, and neither a fixed work split nor event timing of the all-pairs kernel
-// asked for (those are about the general path's kernels).  At 256 segments and
-// 2 points dd_step takes two launches instead of ten.
+// fits, and no fixed work split asked for (that is about the general path's
+// kernels).  At 256 segments and 2 points dd_step takes one launch instead of ten.
 bool small_volume(int64_t nn, int64_t ns, int precision, double eta)
 {
     return ns > 0 && ns <= PB_MAX_SEGS && nn <= PB_MAX_SEGS && precision == DD_FP64 && eta == 0.0 &&
-           g_forced_choice.load() < 0 && !timing_on();
+           g_forced_choice.load() < 0;
 }
 
 void small_args(PBArgs &A, const dd_material *m, int n_gauss)
@@ -2912,7 +2911,9 @@ void launch_small(Workspace *ws, int64_t nn, int64_t ns, const double *x, const 
     A.xw = xw;
     A.done = ws->small_done;
     A.dt = dt;
+    timing_begin(st, ws->capturing);
     hipLaunchKernelGGL(k_small<false>, dim3((unsigned)nn), dim3(PB_THREADS), 0, st, A);
+    timing_end(st, ws->capturing);
 }
 
 // (for dd_last_plan: every workgroup takes all sources of its volume)
