@@ -1865,8 +1865,8 @@ __global__ __launch_bounds__(PB_THREADS) void k_small(PBArgs A)
             p1 = s_x[1][i1] * inv_a;
             p2 = s_x[2][i1] * inv_a;
             const double d0 = s_x[0][i2] * inv_a - p0, d1 = s_x[1][i2] * inv_a - p1, d2 = s_x[2][i2] * inv_a - p2;
-            const double LL = d0 * d0 + d1 * d1 + d2 * d2, iL = rsqrt64(LL);
-            Ls = LL * iL;
+            Ls = sqrt(d0 * d0 + d1 * d1 + d2 * d2);   // (as seg_record)
+            const double iL = 1.0 / Ls;
             t0 = d0 * iL;
             t1 = d1 * iL;
             t2 = d2 * iL;
