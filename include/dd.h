@@ -165,7 +165,8 @@ int dd_set_plan(int64_t chunk_len, int variant);
 /* The work split of the most recent force evaluation on this device: the
  * source-range length of a work item, the number of work items, and the
  * mixed kernel's variant (a single FP64 volume of at most 512 segments and
- * nodes, without the exact band, is one item of all sources per node; the
+ * nodes and few Gauss points per node, without the exact band, is one item of
+ * all sources per node; the
  * persistent launch of a burst one item of all sources of its volume per
  * workgroup, with the longest volume's number of segments).  Variants: 0 = each source is first tested in FP32
  * against a band of max(30 L, cutoff + L/2) around its midpoint, and sources

@@ -2865,13 +2865,33 @@ int presize_near(ForceCtx &C, Workspace *ws, const double *x, const int32_t *seg
 }
 
 // ---------------------------------------------------------- small volumes --
+// Target points a workgroup of k_small takes per round, with ns sources.
+int64_t points_per_round(int64_t ns)
+{
+    const int64_t P = std::max<int64_t>(64, (ns + 63) / 64 * 64);
+    return PB_THREADS / P * PB_POINTS;
+}
+
 // Whether one FP64 force evaluation of a volume goes to k_small: a volume that
-// fits, and no fixed work split asked for (that is about the general path's
-// kernels).  At 256 segments and 2 points dd_step takes one launch instead of ten.
-bool small_volume(int64_t nn, int64_t ns, int precision, double eta)
+// fits, with at most three rounds for a workgroup of mean valence (one beyond 8
+// points), and no fixed work split asked for (that is about the general path's
+// kernels).
+//
+// A workgroup takes every segment of its node, 1.6 us a round.  A step of loops
+// at 2, 4, 6 and 8 points: 256 segments 14.0, 17.5, 22.5 us (1, 2 and 3 rounds) and
+// 29.4, general path 24.9, 27.9, 32.7 and 39.4.  512 segments, in two turns on the
+// compute units: 27.9 us at 2 points (2 rounds), 32.1 at 3, 37.1 at 4; general 24.7,
+// 25.5 and 27.8.  A node of many segments is a long row of rounds, where the general
+// path spreads them.  With one of 16, 254 segments take 34.6, 59, 77, 101 and 186
+// us at 2, 4, 6, 8 and 16 points, general 26, 28, 33, 39 and 63 (before there was a
+// k_small, with lists sorted node by node, 68, 72, 80, 87 and 150); 496 segments 68,
+// 87, 109 and 190 us at 2, 3, 4 and 8, general 30, 31, 31 and 39 (76, 79, 88 and 114);
+// 127 segments at 12 points 94 us (81).  The nodes' valences are on the device, so the
+// line lies where such a volume takes about as long as it did before.
+bool small_volume(int64_t nn, int64_t ns, int n_gauss, int precision, double eta)
 {
     return ns > 0 && ns <= PB_MAX_SEGS && nn <= PB_MAX_SEGS && precision == DD_FP64 && eta == 0.0 &&
-           g_forced_choice.load() < 0;
+           2 * ns * n_gauss <= (n_gauss <= 8 ? 3 : 1) * points_per_round(ns) * nn && g_forced_choice.load() < 0;
 }
 
 void small_args(PBArgs &A, const dd_material *m, int n_gauss)
@@ -3100,7 +3120,7 @@ extern "C" int dd_nodal_forces(int64_t n_nodes, const double *x, int64_t n_segs,
     if ((rc = workspace(&ws))) return rc;
     Sig6 sv;
     for (int k = 0; k < 6; ++k) sv.v[k] = sigma_app[k];
-    if (small_volume(n_nodes, n_segs, precision, exact_eta)) {
+    if (small_volume(n_nodes, n_segs, n_gauss, precision, exact_eta)) {
         launch_small(ws, n_nodes, n_segs, x, seg_nodes, burgers, normal, nullptr, sv, m, n_gauss, 0.0, force_out, nullptr,
                      st);
         note_small_plan(n_nodes, n_segs);
@@ -3224,7 +3244,7 @@ extern "C" int dd_step(int64_t n_nodes, double *x, int64_t n_segs, const int32_t
     }
     Sig6 sv;
     for (int k = 0; k < 6; ++k) sv.v[k] = sigma_app[k];
-    if (small_volume(n_nodes, n_segs, precision, exact_eta)) {
+    if (small_volume(n_nodes, n_segs, n_gauss, precision, exact_eta)) {
         launch_small(ws, n_nodes, n_segs, x, seg_nodes, burgers, normal, pinned, sv, m, n_gauss, 1.0 / m->B, F, vel, st,
                      n_nodes <= SMALL_STEP_NODES ? x : nullptr, dt);
         note_small_plan(n_nodes, n_segs);
@@ -3783,7 +3803,7 @@ extern "C" int dd_nodal_forces_noalloc(int64_t n_nodes, const double *x, int64_t
     ws.flags_dev = cv.take<unsigned>(64);
     ws.near_count = (unsigned long long *)(ws.flags_dev + 32);
     ws.capturing = true;   // no event timing (events would be created on first use)
-    if (small_volume(n_nodes, n_segs, precision, 0.0)) {   // as dd_nodal_forces; needs no scratch
+    if (small_volume(n_nodes, n_segs, n_gauss, precision, 0.0)) {   // as dd_nodal_forces; needs no scratch
         Sig6 sv;
         for (int k = 0; k < 6; ++k) sv.v[k] = sigma_app[k];
         launch_small(&ws, n_nodes, n_segs, x, seg_nodes, burgers, normal, nullptr, sv, m, n_gauss, 0.0, force_out, nullptr,
