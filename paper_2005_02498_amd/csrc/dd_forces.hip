@@ -3285,16 +3285,23 @@ namespace dd {
 namespace {
 // All steps of a batch of small FP64 bursts in one launch, when every instance
 // fits (at most PB_MAX_SEGS segments and nodes), the workgroups can all be
-// resident with at most PB_MAX_NODES_PER_WG nodes each, and none takes more than
-// PB_MAX_ROUNDS rounds of target points: the workgroups per instance into G,
-// empty when the call is left to the step graph.  One workgroup per instance in
-// burst mode 2.
+// resident with at most PB_MAX_NODES_PER_WG nodes each, and a workgroup takes at
+// most PB_MAX_ROUNDS rounds of target points if its nodes are neighbours: the
+// workgroups per instance into G, empty when the call is left to the step graph.
+// One workgroup per instance in burst mode 2.
 //
-// A round is about 1.9 us, the step graph 40-75 us a step.  Measured, us a step
-// (launch, graph): one volume of 256 segments at 2 points, 1 round: 5.2, 41; 16 of
-// them, 9 rounds: 24, 47; 32 of them, 17 rounds: 40, 67; one of 512 at 4 points, 6
-// rounds: 20, 63; 16 of 512 at 2 points, 33 rounds: 81, 73.
-constexpr int PB_MAX_NODES_PER_WG = 32, PB_MAX_ROUNDS = 24;
+// A round is 2.5 to 3 us, the step graph 25 to 50 us a step.  Measured, us a step
+// (launch, graph): one volume of 256 segments at 2 points, 1 round: 5.2, 25; 8 and 16
+// of them, 5 and 9 rounds: 16.8, 28.2 and 25.2, 31.6; 24 and 32, 13 and 17 rounds: 37.1,
+// 35.8 and 41.8, 40.1; 8 and 12 of them at 4 points, 9 and 13 rounds: 29.2, 31.5 and
+// 45.4, 37.2; one and two of 512 at 8 points, 12 and 20 rounds: 34.3, 39.9 and 52.0,
+// 42.1; 16 of 512 at 2 points, 33 rounds: 80.4, 50.3.  The segments of nodes that are
+// no neighbours (a shuffled volume) make up to twice the rounds: 12 of 256 at 2
+// points 34.3, 35.0; 16 of them 41.3, 35.4; 4 at 8 points, 10 rounds by the rule, 48.3,
+// 40.6.  Those of a node of many segments come on top: 4 of 256 with a node of 16 at
+// 4 and 8 points 60 and 113 us, graph 37 and 43 (64 and 77 with lists sorted node by
+// node).
+constexpr int PB_MAX_NODES_PER_WG = 32, PB_MAX_ROUNDS = 12;
 
 int plan_persistent(Workspace *ws, const std::vector<int64_t> &no, const std::vector<int64_t> &so, int Q,
                     std::vector<int> &G)
@@ -3325,9 +3332,9 @@ int plan_persistent(Workspace *ws, const std::vector<int64_t> &no, const std::ve
     bool fits = total <= cap;
     if (mode != 2)
         for (int i = 0; i < n_inst; ++i) {
-            const int64_t P = std::max<int64_t>(64, (so[i + 1] - so[i] + 63) / 64 * 64);
-            const int64_t per_round = PB_THREADS / P * PB_POINTS;
-            fits = fits && ((npw + 1) * Q + per_round - 1) / per_round <= PB_MAX_ROUNDS;
+            const int64_t n = no[i + 1] - no[i], m = so[i + 1] - so[i], per_round = points_per_round(m);
+            const int64_t segs = (npw * m + n - 1) / std::max<int64_t>(n, 1) + 1;   // of npw neighbours
+            fits = fits && (segs * Q + per_round - 1) / per_round <= PB_MAX_ROUNDS;
         }
     if (!fits) G.clear();
     return DD_OK;
