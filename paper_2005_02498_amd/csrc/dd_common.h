@@ -119,6 +119,7 @@ struct Workspace {
     int64_t block_fac_n = -1;                    // size of the tridiagonal factors in WS_BLOCK_FAC
     unsigned long long *near_count = nullptr;   // device counter (mixed kernel)
     unsigned *small_done = nullptr;             // workgroups of a small volume's step that are done (0 between calls)
+    int cus = 0;                                // the device's compute units
     bool capturing = false;
     std::vector<GraphEntry> graphs;
     uint64_t graph_clock = 0;

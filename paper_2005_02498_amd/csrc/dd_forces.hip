@@ -1549,11 +1549,11 @@ __global__ void k_scale_rates(double *acc, int64_t n, double inv_steps)
 // summed over the workgroups by k_pb_finish, which also copies the final
 // positions.
 // Otherwise (one volume, one force evaluation): the nodal forces, and the glide
-// velocities if asked for.  In a step of up to SMALL_STEP_NODES nodes the
+// velocities if asked for.  In a step of as many nodes as compute units the
 // workgroups are counted as they end and the last one moves the nodes, without a
-// launch for it: a call for 256 segments 16.2 -> 13.9 us, for 96 15.8 -> 13.3.  Beyond,
-// the workgroups run in turns on the compute units and the count holds up the
-// next: 384 segments 20.4 and 22.7 us, 512 at 4 points 37.1 and 39.9.
+// launch for it: a call for 256 segments 16.2 -> 13.9 us, for 96 15.8 -> 13.3.  With
+// more nodes than compute units the workgroups run in turns and the count holds
+// up the next: 384 segments 20.4 and 22.7 us, 512 at 4 points 37.1 and 39.9.
 //
 // Bound by latency.  256 segments at 2 points, 256 workgroups of one node: 5.2 us a
 // step (21.5 before, with a barrier of fences and arrival words, records of every
@@ -1563,7 +1563,6 @@ __global__ void k_scale_rates(double *acc, int64_t n, double inv_steps)
 // the way of its position through memory to the other workgroups (about 2 us).
 // Left out: two nodes a workgroup (8.5 us: fewer CUs), several copies of the
 // published positions (5.6), target points precomputed in LDS (no gain).
-constexpr int64_t SMALL_STEP_NODES = 256;   // one workgroup per compute unit
 constexpr int PB_THREADS = 512;
 constexpr int PB_MAX_SEGS = 512;    // segments and nodes per instance
 constexpr int PB_POINTS = 2;        // target points a thread takes at a time
@@ -3246,9 +3245,9 @@ extern "C" int dd_step(int64_t n_nodes, double *x, int64_t n_segs, const int32_t
     for (int k = 0; k < 6; ++k) sv.v[k] = sigma_app[k];
     if (small_volume(n_nodes, n_segs, n_gauss, precision, exact_eta)) {
         launch_small(ws, n_nodes, n_segs, x, seg_nodes, burgers, normal, pinned, sv, m, n_gauss, 1.0 / m->B, F, vel, st,
-                     n_nodes <= SMALL_STEP_NODES ? x : nullptr, dt);
+                     n_nodes <= ws->cus ? x : nullptr, dt);
         note_small_plan(n_nodes, n_segs);
-        if (n_nodes > SMALL_STEP_NODES)
+        if (n_nodes > ws->cus)
             hipLaunchKernelGGL(k_euler, dim3(grid_for(3 * n_nodes, 256, INT32_MAX)), dim3(256), 0, st, n_nodes, x,
                                (const double *)vel, dt);
     } else {
@@ -3312,10 +3311,9 @@ int plan_persistent(Workspace *ws, const std::vector<int64_t> &no, const std::ve
     const int n_inst = (int)no.size() - 1;
     for (int i = 0; i < n_inst; ++i)
         if (no[i + 1] - no[i] > PB_MAX_SEGS || so[i + 1] - so[i] > PB_MAX_SEGS) return DD_OK;
-    int per_cu = 0, cus = 0;
+    int per_cu = 0;
     DD_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_small<true>, PB_THREADS, 0));
-    DD_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, ws->device));
-    const int64_t cap = (int64_t)per_cu * cus;
+    const int64_t cap = (int64_t)per_cu * ws->cus;
     if (n_inst > cap) return DD_OK;
     // nodes per workgroup: the fewest with which all workgroups fit
     G.assign(n_inst, 1);

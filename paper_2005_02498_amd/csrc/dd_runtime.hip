@@ -74,6 +74,10 @@ int workspace(Workspace **out)
     if (!g_ws[dev]) {
         Workspace *w = new Workspace();
         w->device = dev;
+        if (hipDeviceGetAttribute(&w->cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) {
+            delete w;
+            return set_error(DD_EHIP, "hipDeviceGetAttribute of the compute units failed");
+        }
         if (hipMalloc(&w->flags_dev, 256) != hipSuccess) {
             delete w;
             return set_error(DD_ENOMEM, "hipMalloc of the flag word failed");
