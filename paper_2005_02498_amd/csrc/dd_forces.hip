@@ -2192,6 +2192,7 @@ struct ForceCtx {
     int32_t *scan_tmp = nullptr;   // scratch of the node-list scan (after csr_cnt)
     int n_inst = 1;                // instances of a batch, and the most words the node lists of one
     int64_t csr_words = -1;        // need (nodes + twice its segments); -1: one instance, from its sizes
+    int cus = 0;                   // compute units (set up)
     Tile *tiles = nullptr;
     Item *items = nullptr;
     int64_t n_items = 0, range = 0;   // work items and their longest source range
@@ -2241,6 +2242,7 @@ int setup(Workspace *ws, hipStream_t st, const std::vector<int64_t> &seg_off_h, 
     C.cut = (float)near_cut;
     C.L.nn = nn;
     C.L.ns = ns;
+    C.cus = ws->cus;
     void *p;
     int rc;
     if ((rc = ensure(ws, WS_SEG64, rec64_bytes(ns), &p))) return rc;
@@ -2391,13 +2393,22 @@ int size_near_pairs(ForceCtx &C, Workspace *ws, const double *x, const int32_t *
                                                     (int64_t)(factor * (double)total) + extra * C.L.ns));
 }
 
-// The instances of a batch, for launch_csr.
+// The instances of a batch, for the node lists: one workgroup each, if all fit,
+// up to CSR_INSTANCES of them per compute unit.  Two are resident at a time, with
+// 1,024 threads each whatever an instance's size, so that many small ones queue: a
+// step with junction nodes of 512, 1,024, 2,048, 4,096 and 8,192 volumes of 16 segments
+// 43.7, 62.3, 103.7, 180 and 322 us, with launches over all of them 52.2, 67.9, 88.9,
+// 133 and 208; of 1,024, 2,048 and 4,096 volumes of 128 to 256 segments 577, 436 and 808
+// us, with launches 625, 431 and 781.
+constexpr int CSR_INSTANCES = 4;
+
 void note_instances(ForceCtx &C, const std::vector<int64_t> &no, const std::vector<int64_t> &so)
 {
     C.n_inst = (int)no.size() - 1;
     C.csr_words = 0;
     for (int i = 0; i < C.n_inst; ++i)
         C.csr_words = std::max(C.csr_words, no[i + 1] - no[i] + 2 * (so[i + 1] - so[i]));
+    if (C.n_inst > CSR_INSTANCES * C.cus) C.csr_words = INT64_MAX;   // (launches over all)
 }
 
 // Topology-only work: CSR of node -> (segment, end).
