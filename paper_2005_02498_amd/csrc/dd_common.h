@@ -186,14 +186,14 @@ inline size_t rec64_bytes(int64_t ns)
 // structures, read with wavefront-uniform scalar loads or staged in LDS):
 // the midpoint xm/a rounded to FP32 and its rounding remainder xm/a - [XH],
 // t, and for the source quadrature of the kernel variant in use (points
-// xm +- hq t with weight Wo each, plus xm with weight Wc for 3 points) hq,
-// Wo b/a, Wo c, 1 + hq^2, 2 hq, Wc/Wo and the squared band outside which it is
+// xm +- hq t with weight Wo each, plus xm with weight 8/5 Wo for 3 points) hq,
+// Wo b/a, Wo c, 1 + hq^2, 2 hq, a zero and the squared band outside which it is
 // used; then L/a and 1/Wo (read only outside the quadrature) and two zeros.
 // Without a quadrature Wo = 1.  The field is linear in b (c = b x t), so a
 // rule on the scaled b and c needs no weight; the closed form unscales them
 // with 1/Wo.  The quadrature reads the first R32_QUAD_VECS groups of four.
 constexpr int R32_XH = 0, R32_XL = 3, R32_T = 6, R32_HQ = 9, R32_B = 10, R32_C = 13, R32_RA0 = 16, R32_TW = 17,
-              R32_WC = 18, R32_BAND = 19, R32_L = 20, R32_IW = 21;
+              R32_BAND = 19, R32_L = 20, R32_IW = 21;
 constexpr int R32_QUAD_VECS = 5;
 constexpr int REC32A = 24;
 // Mixed kernel variants: 0 = 2-point source quadrature beyond max(30 L,

@@ -234,7 +234,7 @@ __device__ __forceinline__ void seg_prep(const PrepArgs &A, int64_t bid)
     if (A.rec32) {
         float *q = A.rec32 + s * REC32A;
         // source quadrature of the variant: Gauss-Legendre points on the source
-        double hq = 0.0, wo = 1.0, wc = 0.0, band = 0.0;
+        double hq = 0.0, wo = 1.0, band = 0.0;
         if (A.quadn == 2) {
             hq = L * 0.28867513459481288225;            // L / (2 sqrt 3)
             wo = 0.5 * L;
@@ -242,7 +242,6 @@ __device__ __forceinline__ void seg_prep(const PrepArgs &A, int64_t bid)
         } else if (A.quadn == 3) {
             hq = L * 0.38729833462074168852;            // (L / 2) sqrt(3/5)
             wo = L * (5.0 / 18.0);
-            wc = L * (8.0 / 18.0);
             band = fmax(6.0 * L, (double)A.cut + 0.5 * L);
         }
         for (int k = 0; k < 3; ++k) {
@@ -259,8 +258,7 @@ __device__ __forceinline__ void seg_prep(const PrepArgs &A, int64_t bid)
         q[R32_IW] = (float)(1.0 / wo);
         q[R32_RA0] = (float)(1.0 + hq * hq);
         q[R32_TW] = (float)(2.0 * hq);
-        q[R32_WC] = (float)(wc / wo);
-        q[22] = 0.f; q[23] = 0.f;
+        q[18] = 0.f; q[22] = 0.f; q[23] = 0.f;
     }
     if (A.sys) A.sys[s] = seg_system(b, nv);
     if (fl) atomicOr(A.flags, fl);
@@ -1580,7 +1578,7 @@ struct PBArgs {
     const double *sigma_dev;   // [n_inst][6], or null: sigma
     Sig6 sigma;
     const double *volume;      // [n_inst]
-    const int32_t *wg;         // [4][n_wg]: instance, rank in it, the instance's G, its first workgroup (BURST)
+    const int32_t *wg;         // [3][n_wg]: instance, rank in it, the instance's G (BURST)
     int n_wg;
     const double *x;           // positions at the start
     double *xbuf;              // [3][3][nn] published positions (BURST)
@@ -2099,7 +2097,7 @@ __global__ void k_pb_empty(double *p, int64_t n, unsigned *gave_up)
 // loads in flight (one after the other, 128 workgroups' sums took 52 us of a
 // burst's 520, now 12).  A burst that a workgroup gave up has no end positions
 // and no sums: the caller's positions stay, the rates are NaN.
-__global__ void k_pb_finish(const int32_t *wg, int n_wg, int n_inst, const double *wpart, const unsigned *gave_up,
+__global__ void k_pb_finish(const int32_t *wg, int n_wg, const double *wpart, const unsigned *gave_up,
                             double inv_steps, double *rate_out, int64_t n3, const double *xend, double *x)
 {
     const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
@@ -3359,16 +3357,13 @@ int launch_persistent(Workspace *ws, const Layout &L, const std::vector<int64_t>
     const int n_inst = (int)no.size() - 1;
     int n_wg = 0;
     for (int i = 0; i < n_inst; ++i) n_wg += G[i];
-    std::vector<int32_t> tab(4 * (size_t)n_wg);
-    for (int i = 0, k = 0; i < n_inst; ++i) {
-        const int first = k;
+    std::vector<int32_t> tab(3 * (size_t)n_wg);
+    for (int i = 0, k = 0; i < n_inst; ++i)
         for (int w = 0; w < G[i]; ++w, ++k) {
             tab[k] = i;
             tab[n_wg + k] = w;
             tab[2 * n_wg + k] = G[i];
-            tab[3 * n_wg + k] = first;
         }
-    }
     const int64_t nn = no.back(), n3 = 3 * std::max<int64_t>(nn, 1);
     void *p;
     int rc;
@@ -3410,7 +3405,7 @@ int launch_persistent(Workspace *ws, const Layout &L, const std::vector<int64_t>
         return DD_OK;
     }
     hipLaunchKernelGGL(k_pb_finish, dim3(grid_for(std::max<int64_t>(3 * nn, 12 * (int64_t)n_wg), 256, INT32_MAX)), dim3(256),
-                       0, st, (const int32_t *)wgtab, n_wg, n_inst, (const double *)wpart, (const unsigned *)gave_up,
+                       0, st, (const int32_t *)wgtab, n_wg, (const double *)wpart, (const unsigned *)gave_up,
                        1.0 / n_steps, rate_avg_out, 3 * nn, (const double *)A.xend, x);
     int64_t longest = 0;
     for (int i = 0; i < n_inst; ++i) longest = std::max(longest, so[i + 1] - so[i]);

@@ -185,7 +185,7 @@ __device__ __forceinline__ void quad3_acc_f32(float e0, float e1, float e2, floa
                                               float ra0, float tw2, float tb, float cb, float bj0, float bj1, float bj2, float kr, float nu, float three,
                                               float &f0, float &f1, float &f2, float &fk)
 {
-    const float hq = s[R32_HQ], Wc = 1.6f;   // the record's Wc/Wo
+    const float hq = s[R32_HQ], Wc = 1.6f;   // relative to Wo
     const float base = ee + ra0, tw = tw2 * ym;
     const float vA = ym + hq, vB = ym - hq;
     const float iA = __builtin_amdgcn_rsqf(base + tw), iB = __builtin_amdgcn_rsqf(base - tw);
