@@ -335,7 +335,8 @@ def main():
     def small_volume():
         """The 256-segment volume, 100 FP64 glide steps per call, in the three
         burst modes: the cached step graph, the persistent launch with one
-        workgroup, and the default (the persistent launch, 128 workgroups)."""
+        workgroup, and the default (the persistent launch, as many workgroups
+        as the device has room for)."""
         sb = W.pack([W.config0()])
         ds = dict(x=torch.tensor(sb.x, device=dev), sn=torch.tensor(sb.seg_nodes, device=dev),
                   b=torch.tensor(sb.burgers, device=dev), n=torch.tensor(sb.normal, device=dev),
@@ -372,13 +373,15 @@ def main():
         graph = small_timing(dd.BURST_GRAPH)
         one_wg = small_timing(dd.BURST_PERSISTENT_ONE)
         auto = small_timing(dd.BURST_AUTO)
+        workgroups = dd.dd_last_plan()[1]
         return dict(
             auto, segments=256, steps=100,
             step_graph=dict(graph, note="the 100 steps as one cached graph of per-step kernels, relaunched; first "
                                         "call: instance tables, work split, capture and instantiation"),
             persistent_one_workgroup=dict(one_wg, note="all 100 steps in one persistent launch, one workgroup"),
-            persistent=dict(auto, workgroups=128, note="all 100 steps in one cooperative launch, 128 workgroups "
-                                                       "of 2 nodes each, positions exchanged without a barrier (the default)"),
+            persistent=dict(auto, workgroups=workgroups,
+                            note="all 100 steps in one cooperative launch, positions exchanged without a barrier "
+                                 "(the default)"),
             note="calls enqueued back to back and synchronised once")
 
     if args.only == "small":

@@ -278,9 +278,9 @@ __global__ __launch_bounds__(PREP_BLOCK) void k_seg_prep(PrepArgs A) { seg_prep(
 // and the insertion sort of long lists in global memory.  Sixteen volumes of
 // 256 to 768 segments and 16 free slots (whose two dummy nodes hold up to 16
 // entries): 41 -> 4.8 us; one volume of 1,107 segments 13 -> 5.0 us.
-// The limit: a step of one volume of 2,048 segments 51.3 -> 46.6 us, of 5,440
-// (all of the LDS) 162.3 -> 159.4 us; with 152 KB of LDS 8,192 segments took 279.3
-// us against 278.8, 12,800 took 621 to 626 against 616 to 620.
+// The limit: 4.7 us off a step of one volume of 2,048 segments, 2.9 off one of 5,440
+// (all of the LDS); with 152 KB of LDS nothing off 8,192 segments, 5 us more for
+// 12,800.
 constexpr int CSR_THREADS = 1024;
 constexpr int CSR_WORDS = 16 * 1024;
 
@@ -368,10 +368,10 @@ __global__ __launch_bounds__(CSR_THREADS) void k_csr_block(Layout L, const int32
 // builds the lists, the others prepare PREP_BLOCK segments with their first
 // threads (with all of them, 1,024 segments on one compute unit took 10 us).  A
 // launch less per step or force evaluation: 5.0 + 4.4 -> 5.6 us for 1,107
-// segments, a step of 1,024 37.0 -> 32.9 us, of 4,096 120.1 -> 116.2 us.
+// segments, 4 us off a step of 1,024 (28 us as it stands) or 4,096 (112).
 // KEYS: as many threads again make the segments' keys and spheres of the exact
-// band, which need positions and topology only: another launch less, a step of
-// 1,107 segments with the band 112.6 -> 109.8 us, of 2,010 127.0 -> 123.8 us.
+// band, which need positions and topology only: another launch less, 3 us off a
+// step of 1,107 segments with the band (101) or 2,010.
 template <bool KEYS>
 __global__ __launch_bounds__(CSR_THREADS) void k_prep_lists(PrepArgs A, NearArgs N, int32_t *__restrict__ ptr,
                                                             int32_t *__restrict__ list)
@@ -433,13 +433,13 @@ __global__ void k_csr_sort(const int32_t *ptr, int64_t nn, int32_t *list)
 struct Sig6 { double v[6]; };
 
 // (one wavefront a workgroup: bound by latency, so the wavefronts are spread over
-// as many compute units as there are; workgroups of 256, now of 64: a step of 1,024
-// segments 30.8 -> 28.2 us, of 1,107 with the exact band 108.0 -> 103.0 us, of which
-// 1.7 us are the corrections of four near pairs loaded at a time, of 4,096 with
-// the band 184.6 -> 180.8 us, this kernel at 16,384 6.8 -> 5.6 us)
+// as many compute units as there are; with workgroups of 256 a step of 1,024
+// segments took 2.6 us more than its 28, one of 1,107 with the exact band 3.3 more than
+// its 101, one of 4,096 with the band 3.8 more than its 179, and this kernel at 16,384
+// 6.8 us, now 5.6)
 constexpr int ENDS_BLOCK = 64;
-// (the same for the kernels of a thread per node: a step of 1,024 segments 28.00 ->
-// 27.75 us, of 4,096 with the band 179.1 -> 178.6 us)
+// (the same for the kernels of a thread per node: 0.3 us off a step of 1,024
+// segments, 0.5 off one of 4,096 with the band)
 constexpr int NODE_BLOCK = 64;
 
 __global__ void k_segment_ends(Layout L, const Tile *__restrict__ tiles,
@@ -1530,8 +1530,9 @@ __global__ void k_scale_rates(double *acc, int64_t n, double inv_steps)
 // source segment in registers, rebuilt every step from the positions in LDS, and
 // takes PB_POINTS target points at a time; with fewer sources than threads the
 // workgroup splits the points over several copies of the sources.  The stresses
-// of a target point are summed over the sources in a fixed order, so no result
-// depends on G_i.
+// of a target point are summed over the sources in a fixed order, so that forces
+// and positions do not depend on G_i (slip rates do, by the order of the
+// workgroups' sums).
 //
 // BURST: every step of a batch of bursts in one launch (cooperative: all
 // workgroups are resident).  A node's new position is published component by
@@ -1549,18 +1550,19 @@ __global__ void k_scale_rates(double *acc, int64_t n, double inv_steps)
 // Otherwise (one volume, one force evaluation): the nodal forces, and the glide
 // velocities if asked for.  In a step of as many nodes as compute units the
 // workgroups are counted as they end and the last one moves the nodes, without a
-// launch for it: a call for 256 segments 16.2 -> 13.9 us, for 96 15.8 -> 13.3.  With
+// launch for it: 2.4 us off a call for 256 segments (13.6 as it stands) or 96.  With
 // more nodes than compute units the workgroups run in turns and the count holds
 // up the next: 384 segments 20.4 and 22.7 us, 512 at 4 points 37.1 and 39.9.
 //
-// Bound by latency.  256 segments at 2 points, 256 workgroups of one node: 5.2 us a
-// step (21.5 before, with a barrier of fences and arrival words, records of every
-// segment in LDS rows whose reads all met one bank, and serial sums), of which
-// 0.3 us records, 1.2 us stresses (1,024 evaluations a workgroup, 0.8 us of FP64
-// issue on its CU), 0.6 us sums and point forces, and the rest the node's glide and
-// the way of its position through memory to the other workgroups (about 2 us).
-// Left out: two nodes a workgroup (8.5 us: fewer CUs), several copies of the
-// published positions (5.6), target points precomputed in LDS (no gain).
+// Bound by latency.  256 segments at 2 points, 256 workgroups of one node: 4.8 us a
+// step in a burst of 100, 4.4 in the launch itself (22 with a barrier of fences and
+// arrival words, records of every segment in LDS rows whose reads all met one bank,
+// and serial sums), of which 0.3 us records, 1.2 us stresses (1,024 evaluations a
+// workgroup, 0.8 us of FP64 issue on its CU), 0.6 us sums and point forces, and the
+// rest the node's glide and the way of its position through memory to the other
+// workgroups (about 2 us).  Left out: two nodes a workgroup (3.3 us a step more: fewer
+// CUs), several copies of the published positions (0.4 more), target points
+// precomputed in LDS (no gain).
 constexpr int PB_THREADS = 512;
 constexpr int PB_MAX_SEGS = 512;    // segments and nodes per instance
 constexpr int PB_POINTS = 2;        // target points a thread takes at a time
@@ -1823,7 +1825,7 @@ __global__ __launch_bounds__(PB_THREADS) void k_small(PBArgs A)
         if (tid < nn_i) {
             if (BURST && k > 0) xk = A.xbuf + (int64_t)(k % 3) * 3 * nn + n0 + tid;
             // (a look at once would come too early, and the many looks slow the
-            // stores down: 6.7 us a step without the pause, 5.6 with it)
+            // stores down: 5.9 us a step without the pause, 4.8 with it)
             if (BURST && k > 0) __builtin_amdgcn_s_sleep(8);
             for (int c = 0; c < 3; ++c) v[c] = BURST && k > 0 ? pb_load(xk + c * nn) : xk[c * nn];
         }
@@ -2094,8 +2096,8 @@ __global__ void k_pb_empty(double *p, int64_t n, unsigned *gave_up)
 
 // After the last step: positions to the caller's array, and per instance the
 // slip-rate sums of its workgroups, in order, over the number of steps; sixteen
-// loads in flight (one after the other, 128 workgroups' sums took 52 us of a
-// burst's 520, now 12).  A burst that a workgroup gave up has no end positions
+// loads in flight (one after the other, 256 workgroups' sums took 52 us of a
+// burst, now 12).  A burst that a workgroup gave up has no end positions
 // and no sums: the caller's positions stay, the rates are NaN.
 __global__ void k_pb_finish(const int32_t *wg, int n_wg, const double *wpart, const unsigned *gave_up,
                             double inv_steps, double *rate_out, int64_t n3, const double *xend, double *x)
@@ -3298,8 +3300,8 @@ namespace {
 // workgroups per instance into G, empty when the call is left to the step graph.
 // One workgroup per instance in burst mode 2.
 //
-// A round is 2.5 to 3 us, the step graph 25 to 50 us a step.  Measured, us a step
-// (launch, graph): one volume of 256 segments at 2 points, 1 round: 5.2, 25; 8 and 16
+// A round is 2.5 to 3 us, the step graph 25 to 50 us a step.  Bursts of 20 steps, us a
+// step (launch, graph): one volume of 256 segments at 2 points, 1 round: 6.7, 26.2; 8 and 16
 // of them, 5 and 9 rounds: 16.8, 28.2 and 25.2, 31.6; 24 and 32, 13 and 17 rounds: 37.1,
 // 35.8 and 41.8, 40.1; 8 and 12 of them at 4 points, 9 and 13 rounds: 29.2, 31.5 and
 // 45.4, 37.2; one and two of 512 at 8 points, 12 and 20 rounds: 34.3, 39.9 and 52.0,

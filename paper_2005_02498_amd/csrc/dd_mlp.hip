@@ -1171,11 +1171,16 @@ __global__ __launch_bounds__(64 * IWAVES, 1) void k_mlp_infer(const float *__res
 // column of the same instructions): same results bit for bit.
 //
 // Bound by latency and by the 278 KB of weights a workgroup takes from the L2:
-// all three layers' are asked for at the start.  A call for 1,500 points of four
-// members 14.7 -> 10.7 us, for one point 12.3 -> 9.1 us (a kernel is 4 us at least).  The
-// line is where the tiles of all members fill the compute units once: 2,000 points
-// 14.7 and 11.1 us; 2,200, in a second round, 14.8 and 16.3 us.  With a device-wide
-// fence for each workgroup's outputs, in place of y_store, 1,500 points took 20.8 us.
+// all three layers' are asked for at the start.  Calls one after the other, the
+// weights in the L2: 1,500 points of four members 14.7 -> 10.7 us, one point 12.3 -> 9.1
+// us (a kernel is 4 us at least).  The line is where the tiles of all members fill the
+// compute units once, 2,048 points of four members: 14.5 and 11.2 us there; 2,200, in a
+// second round, 14.8 and 16.3 us.  At that line, 8,192 points of one member 12.8 and 9.3,
+// 4,096 of two 13.6 and 9.3, 1,632 of five 15.0 and 11.6, 1,024 of eight 16.7 and 13.9.
+// A call waited for by itself, new points: 2,048 of four 31.6 and 28.0 us, with all
+// caches cold 34.1 and 31.3; 1,024 of eight 34.0 and 30.6, cold 36.7 and 34.3.  With a
+// device-wide fence for each workgroup's outputs, in place of y_store, 1,500 points
+// took 20.8 us.
 constexpr int SP = 32;
 
 template <bool VEC>

@@ -17,25 +17,25 @@ namespace dd {
 // in order): the inverse distance to a run's first node is computed once, then
 // each source reuses the previous source's far-end value, and the cross
 // products by the Burgers vector are taken once per run (pair_run_acc_f64).
-// Only the part of the range that holds the tile's own segments tests for the
-// excluded self pair.
+// Only the part of the range that holds the wavefront's own segments tests for
+// the excluded self pair.
 //
 // Bound by FP64 issue: 83 VALU instructions per source and wavefront (89 when
-// every source forms rho x b), at 4.5 cycles each.  A step of 16,384 segments at 2
-// points 1.525 -> 1.386 ms.  Measured and left out, against 1.444 ms before the
-// records were asked for ahead: two Gauss points of a segment per lane (t.b_j and
-// t.g shared, 79 instructions, 120 VGPRs) 1.449 ms; six wavefronts per SIMD forced
-// by launch bounds (80 VGPRs for 96) 1.473 ms.  72 VGPRs now.
+// every source forms rho x b), at 4.5 cycles each; 72 VGPRs.  A step of 16,384
+// segments at 2 points 1.52 ms without the run form, 1.41 with it.  Measured and
+// left out: two Gauss points of a segment per lane (t.b_j and t.g shared, 79
+// instructions, 120 VGPRs), 0.3 % slower; six wavefronts per SIMD forced by launch
+// bounds, 2 % slower.
 // With few wavefronts per SIMD (up to a few thousand segments) the wait for a
 // record's scalar load shows: the next record is therefore asked for before a
-// source is evaluated, in a run and between runs.  Before (each record loaded
-// when it is needed) and now: a step of 1,024 segments 60.0 and 52.6 us, of
-// 1,107 shuffled ones with close pairs exact 246 and 220 us, 64 volumes of 256
-// segments 76 and 69 us per step, 4,096 shuffled segments 180 and 167 us;
-// 16,384 segments 1.39 ms as before.  What is left there is the first wavefront's
-// wait for each record to come into the L2: every lane asks for one of the range
-// at once, a step of 1,024 segments 39.3 -> 36.3 us (with the wavefronts past a
-// tile's end gone and the self test kept to a wavefront's own segments).
+// source is evaluated, in a run and between runs.  Against records loaded when they
+// are needed that takes 7 us off a step of 1,024 segments (28 us as it stands), 26 off
+// one of 1,107 shuffled segments with close pairs exact (101), 7 off a step of 64
+// volumes of 256 segments, 13 off one of 4,096 shuffled segments, and nothing off
+// 16,384.  What is left there is the first wavefront's wait for each record to come
+// into the L2: every lane asks for one of the range at once, 3 us off a step of
+// 1,024 segments (with the wavefronts past a tile's end gone and the self test kept
+// to a wavefront's own segments).
 //
 // Runs of fewer than RUN_MIN sources take the form that needs no set-up: the
 // run form costs 15 instructions per run and saves 7 per source.
