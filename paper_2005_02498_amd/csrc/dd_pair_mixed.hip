@@ -136,6 +136,12 @@ __device__ __forceinline__ void mixed_pair(const MixedTarget &T, const f32x4 *ld
     }
 }
 
+// A work item that k_pair_mixed_safe leaves to k_pair_mixed: a word in its slot of
+// the partial sums that no sum is (a signaling NaN).
+constexpr long long LEFT_MARK = 0x7ff4c15e77a3b92dll;
+__device__ __forceinline__ bool is_left(const double *slot) { return __double_as_longlong(*slot) == LEFT_MARK; }
+__device__ __forceinline__ void leave(double *slot) { *slot = __longlong_as_double(LEFT_MARK); }
+
 // Mixed precision.  As in the FP64 kernel, every lane of a wavefront works on
 // the same source at the same time.  FP64 records are read with scalar loads.
 // QN = the source-quadrature points of the variant (0: none, 2 or 3).  With
@@ -159,7 +165,7 @@ __device__ __forceinline__ void mixed_pair(const MixedTarget &T, const f32x4 *ld
 // rho alone.  FP32 contributions are summed in FP32 over TILE sources
 // at a time, then added to FP64 sums; all sums are in units of k2 and scaled
 // once at the end.
-template <int QN>
+template <int QN, bool LEFT>
 __global__ __launch_bounds__(TILE) void k_pair_mixed(const Item *__restrict__ items,
                                                      const Tile *__restrict__ tiles,
                                                      const double *__restrict__ rec,
@@ -172,6 +178,7 @@ __global__ __launch_bounds__(TILE) void k_pair_mixed(const Item *__restrict__ it
     __shared__ f32x4 shr[QN ? TILE : 1][REC32A / 4];   // FP32 records of one stage of sources
     __shared__ unsigned n_near_block, n_quad_block;
     const Item it = items[blockIdx.x];
+    if (LEFT && !is_left(partial + it.slot * 3 * TILE)) return;
     const Tile tl = tiles[it.tile];
     const int lane = threadIdx.x;
     const bool valid = lane < tl.n_points;
@@ -333,6 +340,15 @@ __global__ __launch_bounds__(TILE) void k_pair_mixed(const Item *__restrict__ it
 // 16,384 segments at 4 points: 1.97 -> 1.87 ms; a step of 65,536 at 2 points:
 // 15.3 -> 14.6 ms.  Five wavefronts per SIMD leave 44 bytes of scratch in the
 // branch with tests; four were as fast.
+//
+// Where the segments come in no order a wavefront's target points are scattered
+// over the volume, next to no source is safe for all of them, and the branch with
+// tests is slower here than in k_pair_mixed (copies of the sums where its paths
+// meet): 65,536 shuffled segments 19.0 ms, with k_pair_mixed 17.3.  Work items of
+// such targets are left to k_pair_mixed, launched behind this kernel over the same
+// items: 17.5 ms (16,384 at 4 points 1 % more than with k_pair_mixed alone, volumes
+// in order 0.6 % more than without the second launch).  Both loops in one kernel
+// take 18.6, the copies again.
 template <int QN>
 __global__ __launch_bounds__(TILE, 5) void k_pair_mixed_safe(const Item *__restrict__ items,
                                                      const Tile *__restrict__ tiles,
@@ -403,7 +419,14 @@ __global__ __launch_bounds__(TILE, 5) void k_pair_mixed_safe(const Item *__restr
     const float sm = fabsf(sc[0]) + fabsf(sc[1]) + fabsf(sc[2]);
     const bool same_b =
         __builtin_amdgcn_ballot_w64(fb0 == uniform(fb0) && fb1 == uniform(fb1) && fb2 == uniform(fb2)) == ~0ull;
-    __syncthreads();   // the counters are cleared before any wavefront adds to them
+    // worth it?  Of 64 sources across the range, half for one of the wavefronts
+    const int64_t ks64 = it.src_begin + (it.src_end - it.src_begin) * (lane & 63) / 64;
+    const bool ok64 = quad_safe(reinterpret_cast<const f32x4 *>(rf + ks64 * REC32A), sc, sr, sm);
+    const int worth = __builtin_popcountll(__builtin_amdgcn_ballot_w64(ok64)) >= 32;
+    if (!__syncthreads_or(worth)) {   // (and the counters are cleared before any wavefront adds to them)
+        if (lane == 0) leave(partial + it.slot * 3 * TILE);
+        return;
+    }
 
     for (int64_t base = it.src_begin; base < it.src_end; base += TILE) {
         const int n = (int)min(it.src_end - base, (int64_t)TILE);
@@ -487,12 +510,15 @@ static void launch_mixed(const Item *items, const Tile *tiles, const double *rec
                          unsigned long long *counters, int64_t n_items, int64_t range, hipStream_t st)
 {
     const double *ra = rec + (int64_t)REC64 * ns;
-    if (QN && range >= SAFE_MIN_RANGE)
+    if (QN && range >= SAFE_MIN_RANGE) {
         hipLaunchKernelGGL(k_pair_mixed_safe<QN ? QN : 2>, dim3((unsigned)n_items), dim3(TILE), 0, st, items, tiles, rec,
                            ra, rec32, ns, g, kr, nu, k2, cut, partial, counters);
-    else
-        hipLaunchKernelGGL(k_pair_mixed<QN>, dim3((unsigned)n_items), dim3(TILE), 0, st, items, tiles, rec, ra, rec32, ns,
+        hipLaunchKernelGGL((k_pair_mixed<QN ? QN : 2, true>), dim3((unsigned)n_items), dim3(TILE), 0, st, items, tiles, rec,
+                           ra, rec32, ns, g, kr, nu, k2, cut, partial, counters);
+    } else {
+        hipLaunchKernelGGL((k_pair_mixed<QN, false>), dim3((unsigned)n_items), dim3(TILE), 0, st, items, tiles, rec, ra, rec32, ns,
                            g, kr, nu, k2, cut, partial, counters);
+    }
 }
 
 void launch_pair_mixed(const Item *items, const Tile *tiles, const double *rec, const float *rec32, int64_t ns,
