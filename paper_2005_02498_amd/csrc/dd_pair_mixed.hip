@@ -54,8 +54,8 @@ __device__ __forceinline__ bool quad_safe(const f32x4 *s, const float (&c)[3], f
 
 template <int QN>
 __device__ __forceinline__ void quad_acc(float e0, float e1, float e2, float ee, float ym, const float *s, float ra0,
-                                         float tw2, float tb, float cb, float bj0, float bj1, float bj2, float kr, float nu, float three,
-                                         float &f0, float &f1, float &f2, float &fk)
+                                         float tw2, float tb, float cb, float bj0, float bj1, float bj2, float kr,
+                                         float nu, float three, float &f0, float &f1, float &f2, float &fk)
 {
     if (QN == 2)
         quad2_acc_f32(e0, e1, e2, ee, ym, s, ra0, tw2, tb, cb, bj0, bj1, bj2, kr, nu, three, f0, f1, f2, fk);
@@ -63,18 +63,16 @@ __device__ __forceinline__ void quad_acc(float e0, float e1, float e2, float ee,
         quad3_acc_f32(e0, e1, e2, ee, ym, s, ra0, tw2, tb, cb, bj0, bj1, bj2, kr, nu, three, f0, f1, f2, fk);
 }
 
-// A target point and the constants of its pairs.
+// A target point and the constants of its pairs, in FP32.
 struct MixedTarget {
-    double x0, x1, x2, b0, b1, b2, kr, nu;
-    float xh0, xh1, xh2, xl0, xl1, xl2, fb0, fb1, fb2, fkr, fnu, cut2, three, ck2, kap;
-    bool valid;
+    float xh0, xh1, xh2, xl0, xl1, xl2, fb0, fb1, fb2, fkr, fnu, three;
 };
 
 // A source that every target point of the wavefront takes by quadrature: the
-// offsets and the rule, as mixed_pair forms them.
+// offsets and the rule, as k_pair_mixed forms them where it tests.
 template <int QN>
-__device__ __forceinline__ void safe_quad(const MixedTarget &T, const float *r, float ra0, float tw2, float tb, float cb,
-                                          float &f0, float &f1, float &f2, float &fk)
+__device__ __forceinline__ void safe_quad(const MixedTarget &T, const float *r, float ra0, float tw2, float tb,
+                                          float cb, float &f0, float &f1, float &f2, float &fk)
 {
     const float e0 = (T.xh0 - r[R32_XH]) + (T.xl0 - r[R32_XL]);
     const float e1 = (T.xh1 - r[R32_XH + 1]) + (T.xl1 - r[R32_XL + 1]);
@@ -83,64 +81,6 @@ __device__ __forceinline__ void safe_quad(const MixedTarget &T, const float *r, 
     const float ee = fmaf(e2, e2, fmaf(e1, e1, e0 * e0));
     quad_acc<QN>(e0, e1, e2, ee, ym, r, ra0, tw2, tb, cb, T.fb0, T.fb1, T.fb2, T.fkr, T.fnu, T.three, f0, f1, f2, fk);
 }
-
-// One staged source with its tests: quadrature when every lane passes them, else
-// per lane FP64 (near, nearly collinear) or the FP32 closed form; the arithmetic
-// of k_pair_mixed.  d = its FP64 record in memory, k and self = the indices of the
-// source and of the target's own segment in the stage.
-template <int QN>
-__device__ __forceinline__ void mixed_pair(const MixedTarget &T, const f32x4 *lds, const double *d, int k, int self,
-                                           double &a0, double &a1, double &a2, float &f0, float &f1, float &f2, float &fk,
-                                           unsigned &n_near, unsigned &n_quad_src)
-{
-    const Staged<REC32A / 4> v(lds);
-    const float *r = v.f;
-    // offset from the source midpoint, from the split FP32 positions: accurate to
-    // the rounding of its own size
-    const float e0 = (T.xh0 - r[R32_XH]) + (T.xl0 - r[R32_XL]);
-    const float e1 = (T.xh1 - r[R32_XH + 1]) + (T.xl1 - r[R32_XL + 1]);
-    const float e2 = (T.xh2 - r[R32_XH + 2]) + (T.xl2 - r[R32_XL + 2]);
-    // axial coordinate from the midpoint
-    const float ym = fmaf(e2, r[R32_T + 2], fmaf(e1, r[R32_T + 1], e0 * r[R32_T]));
-    const float ym2 = ym * ym;
-    const float ee = fmaf(e2, e2, fmaf(e1, e1, e0 * e0));
-    const uint64_t quad = __builtin_amdgcn_ballot_w64(ee >= r[R32_BAND]) &
-                          __builtin_amdgcn_ballot_w64(ym2 <= fmaf(T.kap, ee, T.kap));
-    if (quad == __builtin_amdgcn_read_exec()) {
-        ++n_quad_src;
-        quad_acc<QN>(e0, e1, e2, ee, ym, r, r[R32_RA0], r[R32_TW], record_tb(r, T.fb0, T.fb1, T.fb2),
-                     record_cb(r, T.fb0, T.fb1, T.fb2), T.fb0, T.fb1, T.fb2, T.fkr, T.fnu, T.three, f0, f1, f2, fk);
-        return;
-    }
-    // axial coordinate from the first node and perpendicular part
-    const float Ls = r[R32_L];
-    const float y = fmaf(0.5f, Ls, ym);
-    const float h0 = fmaf(-ym, r[R32_T], e0), h1 = fmaf(-ym, r[R32_T + 1], e1), h2 = fmaf(-ym, r[R32_T + 2], e2);
-    const float hh = fmaf(h2, h2, fmaf(h1, h1, h0 * h0));
-    const float ya = y - __builtin_amdgcn_fmed3f(y, 0.f, Ls);   // y clamped to [0, L]: one instruction
-    // FP64: near pairs, and nearly collinear ones (rho carries an absolute error
-    // of order |ym| eps32 in FP32)
-    if (hh + ya * ya < T.cut2 || ym2 > fmaf(T.ck2, hh, T.ck2)) {
-        // k through an empty asm: the comparison stays in this branch instead of
-        // becoming a per-lane counter stepped every source
-        int ks = k;
-        asm volatile("" : "+s"(ks));
-        if (ks != self) {
-            n_near += T.valid ? 1u : 0u;
-            pair_acc_isolated_f64(T.x0, T.x1, T.x2, T.b0, T.b1, T.b2, d, T.kr, T.nu, a0, a1, a2);
-        }
-    } else {
-        // the record's b and c carry the quadrature weight
-        pair_acc_f32(y, h0, h1, h2, hh, T.fb0, T.fb1, T.fb2, r[R32_T], r[R32_T + 1], r[R32_T + 2], Ls, r[R32_B],
-                     r[R32_B + 1], r[R32_B + 2], r[R32_C], r[R32_C + 1], r[R32_C + 2], r[R32_IW], T.fkr, T.fnu, f0, f1, f2, fk);
-    }
-}
-
-// A work item that k_pair_mixed_safe leaves to k_pair_mixed: a word in its slot of
-// the partial sums that no sum is (a signaling NaN).
-constexpr long long LEFT_MARK = 0x7ff4c15e77a3b92dll;
-__device__ __forceinline__ bool is_left(const double *slot) { return __double_as_longlong(*slot) == LEFT_MARK; }
-__device__ __forceinline__ void leave(double *slot) { *slot = __longlong_as_double(LEFT_MARK); }
 
 // Mixed precision.  As in the FP64 kernel, every lane of a wavefront works on
 // the same source at the same time.  FP64 records are read with scalar loads.
@@ -165,20 +105,34 @@ __device__ __forceinline__ void leave(double *slot) { *slot = __longlong_as_doub
 // rho alone.  FP32 contributions are summed in FP32 over TILE sources
 // at a time, then added to FP64 sums; all sums are in units of k2 and scaled
 // once at the end.
-template <int QN, bool LEFT>
-__global__ __launch_bounds__(TILE) void k_pair_mixed(const Item *__restrict__ items,
-                                                     const Tile *__restrict__ tiles,
-                                                     const double *__restrict__ rec,
-                                                     const double *__restrict__ ra,
-                                                     const float *__restrict__ rf, int64_t ns,
-                                                     GaussRule g, double kr, double nu, double k2,
-                                                     float cut, double *__restrict__ partial,
-                                                     unsigned long long *near_count)
+//
+// SAFE, for long source ranges.  Bound by FP32 issue and by broadcast reads from
+// LDS (five 16-byte reads a source).  Per 64 sources a wavefront first finds, one
+// source per lane, those that all its target points take by quadrature (quad_safe,
+// 96-98 % of them in sparse volumes in order): a run of these goes through an inner
+// loop without tests or branches, the rest through the loop with the tests.  When
+// its target points share their Burgers vector (a loop of 32 segments at 2 points
+// is one wavefront), t.b_j and c.b_j belong to the source and are formed once, in
+// the same pass, instead of by every lane.  Neither changes a bit of the result.
+// VALU instructions a source in that loop, 2-point rule: 98 with the tests, 94, and
+// 89 with a shared Burgers vector.  The inner loop stands inside the loop with the
+// tests: as two loops or a called function the latter copies the four sums for
+// every source (12-16 v_mov), 5-15 % of a volume whose segments come in no order,
+// where next to no source is safe for a whole wavefront.  Against the loop with the
+// tests alone: 16,384 segments at 4 points 1.97 -> 1.81 ms, a step of 65,536 at 2
+// points 15.2 -> 14.2 ms; at 1 point 643 -> 661 us, 65,536 shuffled segments at 2
+// points 17.8 -> 18.1 ms: 1-4 % for a pass that finds little.  Five wavefronts per
+// SIMD (92 VGPRs, no scratch).
+template <int QN, bool SAFE>
+__global__ __launch_bounds__(TILE, SAFE ? 5 : 1) void k_pair_mixed(
+    const Item *__restrict__ items, const Tile *__restrict__ tiles, const double *__restrict__ rec,
+    const double *__restrict__ ra, const float *__restrict__ rf, int64_t ns, GaussRule g, double kr, double nu,
+    double k2, float cut, double *__restrict__ partial, unsigned long long *near_count)
 {
     __shared__ f32x4 shr[QN ? TILE : 1][REC32A / 4];   // FP32 records of one stage of sources
+    __shared__ f32x4 bsh[SAFE ? TILE : 1];             // per wavefront, of 64 sources: t.b_j, c.b_j, 1 + hq^2, 2 hq
     __shared__ unsigned n_near_block, n_quad_block;
     const Item it = items[blockIdx.x];
-    if (LEFT && !is_left(partial + it.slot * 3 * TILE)) return;
     const Tile tl = tiles[it.tile];
     const int lane = threadIdx.x;
     const bool valid = lane < tl.n_points;
@@ -211,6 +165,30 @@ __global__ __launch_bounds__(TILE) void k_pair_mixed(const Item *__restrict__ it
         n_near_block = 0;
         n_quad_block = 0;
     }
+    // a sphere around the wavefront's target points; do they share a Burgers vector?
+    float sc[3] = {}, sr = 0.f, sm = 0.f;
+    bool same_b = false;
+    if (SAFE) {
+        float lo[3] = {xh0, xh1, xh2}, hi[3] = {xh0, xh1, xh2};
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1)
+#pragma unroll
+            for (int k = 0; k < 3; ++k) {
+                lo[k] = fminf(lo[k], __shfl_xor(lo[k], off));
+                hi[k] = fmaxf(hi[k], __shfl_xor(hi[k], off));
+            }
+#pragma unroll
+        for (int k = 0; k < 3; ++k) sc[k] = uniform(0.5f * lo[k] + 0.5f * hi[k]);
+        const float d0 = xh0 - sc[0], d1 = xh1 - sc[1], d2 = xh2 - sc[2];
+        sr = fmaf(d2, d2, fmaf(d1, d1, d0 * d0));
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) sr = fmaxf(sr, __shfl_xor(sr, off));
+        sr = uniform(sqrtf(sr));
+        sm = fabsf(sc[0]) + fabsf(sc[1]) + fabsf(sc[2]);
+        same_b =
+            __builtin_amdgcn_ballot_w64(fb0 == uniform(fb0) && fb1 == uniform(fb1) && fb2 == uniform(fb2)) == ~0ull;
+    }
+    const MixedTarget T{xh0, xh1, xh2, xl0, xl1, xl2, fb0, fb1, fb2, fkr, fnu, three};
     __syncthreads();   // the counters are cleared before any wavefront adds to them
 
     for (int64_t base = it.src_begin; base < it.src_end; base += TILE) {
@@ -228,257 +206,135 @@ __global__ __launch_bounds__(TILE) void k_pair_mixed(const Item *__restrict__ it
             __syncthreads();
         }
         const float *s = rf + base * REC32A;
-        for (int k = 0; k < n; ++k, s += REC32A) {
-            float r[REC32A];
-            if (QN) {
-                // from LDS (broadcast reads): the FP32 quadrature then runs on
-                // vector-register operands, which issue faster than FP32
-                // instructions with a scalar operand; the fields only the
-                // other pairs use are read below, for those
-#pragma unroll
-                for (int f = 0; f < R32_QUAD_VECS; ++f) {
-                    const f32x4 v = shr[k][f];
-                    r[4 * f] = v[0];
-                    r[4 * f + 1] = v[1];
-                    r[4 * f + 2] = v[2];
-                    r[4 * f + 3] = v[3];
+        uint64_t safe = 0;
+        for (int k64 = 0; k64 < n; k64 += SAFE ? 64 : TILE) {
+            const int kgrp = SAFE ? min(n, k64 + 64) : n;
+            if (SAFE) {
+                // 64 sources at a time: those that every target point of the wavefront
+                // takes by quadrature, tested one per lane
+                const int ks = k64 + (lane & 63);
+                bool ok = false;
+                if (ks < n) {
+                    ok = quad_safe(shr[ks], sc, sr, sm);
+                    if (same_b) {
+                        const Staged<R32_QUAD_VECS> q5(shr[ks]);
+                        bsh[lane] = f32x4{record_tb(q5.f, fb0, fb1, fb2), record_cb(q5.f, fb0, fb1, fb2),
+                                          q5.f[R32_RA0], q5.f[R32_TW]};
+                    }
                 }
-            } else {
-                // straight from memory into scalar registers (two loads, one wait)
-                const f32x16 va = *reinterpret_cast<const f32x16 *>(s);
-                const f32x8 vb = *reinterpret_cast<const f32x8 *>(s + 16);
-#pragma unroll
-                for (int f = 0; f < 16; ++f) r[f] = va[f];
-#pragma unroll
-                for (int f = 0; f < 8; ++f) r[16 + f] = vb[f];
+                __builtin_amdgcn_wave_barrier();
+                safe = __builtin_amdgcn_ballot_w64(ok);
+                __builtin_amdgcn_wave_barrier();
             }
-            // offset from the source midpoint, from the split FP32 positions:
-            // accurate to the rounding of its own size
-            const float e0 = (xh0 - r[R32_XH]) + (xl0 - r[R32_XL]);
-            const float e1 = (xh1 - r[R32_XH + 1]) + (xl1 - r[R32_XL + 1]);
-            const float e2 = (xh2 - r[R32_XH + 2]) + (xl2 - r[R32_XL + 2]);
-            // axial coordinate from the midpoint
-            const float ym = fmaf(e2, r[R32_T + 2], fmaf(e1, r[R32_T + 1], e0 * r[R32_T]));
-            const float ym2 = ym * ym;
-            if (QN) {
-                const float ee = fmaf(e2, e2, fmaf(e1, e1, e0 * e0));
-                // outside the band and not nearly collinear (ym^2 > K^2 (rho^2 + 1)
-                // with rho^2 = ee - ym^2, see COLLINEAR_K2)
-                // every active lane passes both tests: the two comparison masks
-                // against exec, in scalar registers (a ballot of their
-                // conjunction would select and re-compare per lane)
-                const uint64_t quad = __builtin_amdgcn_ballot_w64(ee >= r[R32_BAND]) &
-                                      __builtin_amdgcn_ballot_w64(ym2 <= fmaf(kap, ee, kap));
-                if (quad == __builtin_amdgcn_read_exec()) {
-                    ++n_quad_src;
-                    quad_acc<QN>(e0, e1, e2, ee, ym, r, r[R32_RA0], r[R32_TW], record_tb(r, fb0, fb1, fb2),
-                                 record_cb(r, fb0, fb1, fb2), fb0, fb1, fb2, fkr, fnu, three, f0, f1, f2, fk);
-                    continue;
+            for (int k = k64; k < kgrp; ++k, s += REC32A) {
+                if (SAFE) {
+                    if (safe & 1) {
+                        const int run = ~safe ? __builtin_ctzll(~safe) : 64;
+                        const int kend = k + run;
+                        n_quad_src += (unsigned)run;
+                        s += (run - 1) * REC32A;
+                        safe = run < 64 ? safe >> run : 0;
+                        if (same_b) {
+                            const f32x4 *bw = bsh + (lane & ~63) + (k & 63);
+                            for (; k < kend; ++k, ++bw) {
+                                const Staged<4> q(shr[k]);
+                                const f32x4 w = *bw;
+                                safe_quad<QN ? QN : 2>(T, q.f, w[2], w[3], w[0], w[1], f0, f1, f2, fk);
+                            }
+                        } else {
+                            for (; k < kend; ++k) {
+                                const Staged<R32_QUAD_VECS> q(shr[k]);
+                                safe_quad<QN ? QN : 2>(T, q.f, q.f[R32_RA0], q.f[R32_TW], record_tb(q.f, fb0, fb1, fb2),
+                                                       record_cb(q.f, fb0, fb1, fb2), f0, f1, f2, fk);
+                            }
+                        }
+                        --k;
+                        continue;
+                    }
+                    safe >>= 1;
                 }
-            }
-            if (QN) {
-#pragma unroll
-                for (int f = R32_QUAD_VECS; f < REC32A / 4; ++f) {
-                    const f32x4 v = shr[k][f];
-                    r[4 * f] = v[0];
-                    r[4 * f + 1] = v[1];
-                    r[4 * f + 2] = v[2];
-                    r[4 * f + 3] = v[3];
-                }
-            }
-            // axial coordinate from the first node and perpendicular part
-            const float Ls = r[R32_L];
-            const float y = fmaf(0.5f, Ls, ym);
-            const float h0 = fmaf(-ym, r[R32_T], e0), h1 = fmaf(-ym, r[R32_T + 1], e1), h2 = fmaf(-ym, r[R32_T + 2], e2);
-            const float hh = fmaf(h2, h2, fmaf(h1, h1, h0 * h0));
-            const float ya = y - __builtin_amdgcn_fmed3f(y, 0.f, Ls);   // y clamped to [0, L]: one instruction
-            // FP64: near pairs, and nearly collinear ones (rho carries an absolute
-            // error of order |ym| eps32 in FP32)
-            if (hh + ya * ya < cut2 || ym2 > fmaf(ck2, hh, ck2)) {
-                // k through an empty asm: the comparison stays in this branch
-                // instead of becoming a per-lane counter stepped every source
-                int ks = k;
-                asm volatile("" : "+s"(ks));
-                if (ks != self) {
-                    n_near += valid ? 1u : 0u;
-                    pair_acc_isolated_f64(xq0, xq1, xq2, bj0, bj1, bj2, ra + (base + k) * RECA, kr, nu, a0, a1, a2);
-                }
-            } else {
-                // the record's b and c carry the quadrature weight (1 without a quadrature)
-                pair_acc_f32(y, h0, h1, h2, hh, fb0, fb1, fb2, r[R32_T], r[R32_T + 1], r[R32_T + 2], Ls, r[R32_B],
-                             r[R32_B + 1], r[R32_B + 2], r[R32_C], r[R32_C + 1], r[R32_C + 2], QN ? r[R32_IW] : 1.0f,
-                             fkr, fnu, f0, f1, f2, fk);
-            }
-        }
-        a0 += (double)fmaf(fk, fb0, f0);   // the b_j terms of the stage at once
-        a1 += (double)fmaf(fk, fb1, f1);
-        a2 += (double)fmaf(fk, fb2, f2);
-    }
-    if (valid) {
-        double *o = partial + it.slot * 3 * TILE;
-        o[lane] = k2 * a0;
-        o[TILE + lane] = k2 * a1;
-        o[2 * TILE + lane] = k2 * a2;
-    }
-    const unsigned n_quad = valid ? n_quad_src : 0u;
-    if (n_near) atomicAdd(&n_near_block, n_near);
-    if (n_quad) atomicAdd(&n_quad_block, n_quad);
-    __syncthreads();
-    if (lane == 0 && n_near_block) atomicAdd(near_count, (unsigned long long)n_near_block);
-    if (lane == 0 && n_quad_block) atomicAdd(near_count + 1, (unsigned long long)n_quad_block);
-}
-
-// The same for long source ranges.  Bound by FP32 issue and by broadcast reads
-// from LDS (five 16-byte reads a source).  Per 64 sources a wavefront first
-// finds, one source per lane, those that all its target points take by quadrature
-// (quad_safe, 96-98 % of them in sparse volumes): these run in a loop without
-// tests or branches.  When its target points share their Burgers vector (a loop
-// of 32 segments at 2 points is one wavefront), t.b_j and c.b_j belong to the
-// source and are formed once, in the same pass, instead of by every lane.
-// Neither changes a bit of the result.  VALU instructions a source in that loop,
-// 2-point rule: 98 with the tests, 94, and 89 with a shared Burgers vector.
-// 16,384 segments at 4 points: 1.97 -> 1.87 ms; a step of 65,536 at 2 points:
-// 15.3 -> 14.6 ms.  Five wavefronts per SIMD leave 44 bytes of scratch in the
-// branch with tests; four were as fast.
-//
-// Where the segments come in no order a wavefront's target points are scattered
-// over the volume, next to no source is safe for all of them, and the branch with
-// tests is slower here than in k_pair_mixed (copies of the sums where its paths
-// meet): 65,536 shuffled segments 19.0 ms, with k_pair_mixed 17.3.  Work items of
-// such targets are left to k_pair_mixed, launched behind this kernel over the same
-// items: 17.5 ms (16,384 at 4 points 1 % more than with k_pair_mixed alone, volumes
-// in order 0.6 % more than without the second launch).  Both loops in one kernel
-// take 18.6, the copies again.
-template <int QN>
-__global__ __launch_bounds__(TILE, 5) void k_pair_mixed_safe(const Item *__restrict__ items,
-                                                     const Tile *__restrict__ tiles,
-                                                     const double *__restrict__ rec,
-                                                     const double *__restrict__ ra,
-                                                     const float *__restrict__ rf, int64_t ns,
-                                                     GaussRule g, double kr, double nu, double k2,
-                                                     float cut, double *__restrict__ partial,
-                                                     unsigned long long *near_count)
-{
-    __shared__ f32x4 shr[TILE][REC32A / 4];   // FP32 records of one stage of sources
-    __shared__ f32x4 bsh[TILE];               // per wavefront, of 64 sources: t.b_j, c.b_j, 1 + hq^2, 2 hq
-    __shared__ unsigned n_near_block, n_quad_block;
-    const Item it = items[blockIdx.x];
-    const Tile tl = tiles[it.tile];
-    const int lane = threadIdx.x;
-    const bool valid = lane < tl.n_points;
-    const int64_t p = tl.point_begin + (valid ? lane : 0);
-    const int Q = g.n;
-    const int64_t j = p / Q;
-    const int q = (int)(p - j * Q);
-    double sq = g.s[0];
-    for (int k = 1; k < DD_MAX_GAUSS; ++k)
-        if (k == q) sq = g.s[k];
-    const double L = rec[6 * ns + j];
-    const double xq0 = rec[0 * ns + j] + sq * L * rec[3 * ns + j];
-    const double xq1 = rec[1 * ns + j] + sq * L * rec[4 * ns + j];
-    const double xq2 = rec[2 * ns + j] + sq * L * rec[5 * ns + j];
-    const float xh0 = (float)xq0, xh1 = (float)xq1, xh2 = (float)xq2;
-    const float xl0 = (float)(xq0 - (double)xh0), xl1 = (float)(xq1 - (double)xh1),
-                xl2 = (float)(xq2 - (double)xh2);
-    const double bj0 = rec[7 * ns + j], bj1 = rec[8 * ns + j], bj2 = rec[9 * ns + j];
-    const float fb0 = (float)bj0, fb1 = (float)bj1, fb2 = (float)bj2;
-    const float fkr = (float)kr, fnu = (float)nu, cut2 = cut * cut;
-    // constants of the FP32 arithmetic in vector registers (the empty asm keeps
-    // them there): an FP32 instruction with a literal operand issues at half rate
-    // kap = K^2 / (1 + K^2): the collinear test ym^2 (1 + K^2) <= K^2 (ee + 1)
-    // as ym^2 <= kap (ee + 1), one instruction fewer
-    float three = 3.0f, ck2 = COLLINEAR_K2, kap = COLLINEAR_K2 / (1.0f + COLLINEAR_K2);
-    asm volatile("" : "+v"(three), "+v"(ck2), "+v"(kap));
-    const MixedTarget T{xq0, xq1, xq2, bj0, bj1, bj2, kr, nu, xh0, xh1, xh2, xl0, xl1, xl2, fb0, fb1, fb2, fkr, fnu, cut2,
-                        three, ck2, kap, valid};
-    double a0 = 0.0, a1 = 0.0, a2 = 0.0;
-    unsigned n_near = 0, n_quad_src = 0;
-    if (lane == 0) {
-        n_near_block = 0;
-        n_quad_block = 0;
-    }
-    // a sphere around the wavefront's target points; do they share a Burgers vector?
-    float sc[3], sr;
-    {
-        float lo[3] = {xh0, xh1, xh2}, hi[3] = {xh0, xh1, xh2};
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1)
-#pragma unroll
-            for (int k = 0; k < 3; ++k) {
-                lo[k] = fminf(lo[k], __shfl_xor(lo[k], off));
-                hi[k] = fmaxf(hi[k], __shfl_xor(hi[k], off));
-            }
-#pragma unroll
-        for (int k = 0; k < 3; ++k) sc[k] = uniform(0.5f * lo[k] + 0.5f * hi[k]);
-        const float d0 = xh0 - sc[0], d1 = xh1 - sc[1], d2 = xh2 - sc[2];
-        sr = fmaf(d2, d2, fmaf(d1, d1, d0 * d0));
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) sr = fmaxf(sr, __shfl_xor(sr, off));
-        sr = uniform(sqrtf(sr));
-    }
-    const float sm = fabsf(sc[0]) + fabsf(sc[1]) + fabsf(sc[2]);
-    const bool same_b =
-        __builtin_amdgcn_ballot_w64(fb0 == uniform(fb0) && fb1 == uniform(fb1) && fb2 == uniform(fb2)) == ~0ull;
-    // worth it?  Of 64 sources across the range, half for one of the wavefronts
-    const int64_t ks64 = it.src_begin + (it.src_end - it.src_begin) * (lane & 63) / 64;
-    const bool ok64 = quad_safe(reinterpret_cast<const f32x4 *>(rf + ks64 * REC32A), sc, sr, sm);
-    const int worth = __builtin_popcountll(__builtin_amdgcn_ballot_w64(ok64)) >= 32;
-    if (!__syncthreads_or(worth)) {   // (and the counters are cleared before any wavefront adds to them)
-        if (lane == 0) leave(partial + it.slot * 3 * TILE);
-        return;
-    }
-
-    for (int64_t base = it.src_begin; base < it.src_end; base += TILE) {
-        const int n = (int)min(it.src_end - base, (int64_t)TILE);
-        // the target's own segment as a source index of this stage (-1: not in it)
-        const int self = j >= base && j < base + n ? (int)(j - base) : -1;
-        float f0 = 0.f, f1 = 0.f, f2 = 0.f, fk = 0.f;
-        __syncthreads();
-        if (lane < n) {
-            const f32x4 *g4 = reinterpret_cast<const f32x4 *>(rf + (base + lane) * REC32A);
-#pragma unroll
-            for (int f = 0; f < REC32A / 4; ++f) shr[lane][f] = g4[f];
-        }
-        __syncthreads();
-        // 64 sources at a time: those that every target point of the wavefront
-        // takes by quadrature, tested one per lane
-        for (int k64 = 0; k64 < n; k64 += 64) {
-            const int kend = min(n, k64 + 64), ks = k64 + (lane & 63);
-            bool ok = false;
-            if (ks < n) {
-                ok = quad_safe(shr[ks], sc, sr, sm);
-                if (same_b) {
-                    const Staged<R32_QUAD_VECS> r(shr[ks]);
-                    bsh[lane] = f32x4{record_tb(r.f, fb0, fb1, fb2), record_cb(r.f, fb0, fb1, fb2), r.f[R32_RA0],
-                                      r.f[R32_TW]};
-                }
-            }
-            const uint64_t safe = __builtin_amdgcn_ballot_w64(ok);
-            __builtin_amdgcn_wave_barrier();
-            for (int k = k64; k < kend;) {
-                const int kq = min(kend, k + __builtin_ctzll(~(safe >> (k - k64)) | (1ull << 63)));
-                n_quad_src += (unsigned)(kq - k);
-                if (same_b) {
-                    const f32x4 *bw = bsh + (lane & ~63) + (k - k64);
-                    for (; k < kq; ++k, ++bw) {
-                        const Staged<4> r(shr[k]);
-                        const f32x4 w = *bw;
-                        safe_quad<QN>(T, r.f, w[2], w[3], w[0], w[1], f0, f1, f2, fk);
+                float r[REC32A];
+                if (QN) {
+                    // from LDS (broadcast reads): the FP32 quadrature then runs on
+                    // vector-register operands, which issue faster than FP32
+                    // instructions with a scalar operand; the fields only the
+                    // other pairs use are read below, for those
+    #pragma unroll
+                    for (int f = 0; f < R32_QUAD_VECS; ++f) {
+                        const f32x4 v = shr[k][f];
+                        r[4 * f] = v[0];
+                        r[4 * f + 1] = v[1];
+                        r[4 * f + 2] = v[2];
+                        r[4 * f + 3] = v[3];
                     }
                 } else {
-                    for (; k < kq; ++k) {
-                        const Staged<R32_QUAD_VECS> r(shr[k]);
-                        safe_quad<QN>(T, r.f, r.f[R32_RA0], r.f[R32_TW], record_tb(r.f, fb0, fb1, fb2),
-                                      record_cb(r.f, fb0, fb1, fb2), f0, f1, f2, fk);
+                    // straight from memory into scalar registers (two loads, one wait)
+                    const f32x16 va = *reinterpret_cast<const f32x16 *>(s);
+                    const f32x8 vb = *reinterpret_cast<const f32x8 *>(s + 16);
+    #pragma unroll
+                    for (int f = 0; f < 16; ++f) r[f] = va[f];
+    #pragma unroll
+                    for (int f = 0; f < 8; ++f) r[16 + f] = vb[f];
+                }
+                // offset from the source midpoint, from the split FP32 positions:
+                // accurate to the rounding of its own size
+                const float e0 = (xh0 - r[R32_XH]) + (xl0 - r[R32_XL]);
+                const float e1 = (xh1 - r[R32_XH + 1]) + (xl1 - r[R32_XL + 1]);
+                const float e2 = (xh2 - r[R32_XH + 2]) + (xl2 - r[R32_XL + 2]);
+                // axial coordinate from the midpoint
+                const float ym = fmaf(e2, r[R32_T + 2], fmaf(e1, r[R32_T + 1], e0 * r[R32_T]));
+                const float ym2 = ym * ym;
+                if (QN) {
+                    const float ee = fmaf(e2, e2, fmaf(e1, e1, e0 * e0));
+                    // outside the band and not nearly collinear (ym^2 > K^2 (rho^2 + 1)
+                    // with rho^2 = ee - ym^2, see COLLINEAR_K2)
+                    // every active lane passes both tests: the two comparison masks
+                    // against exec, in scalar registers (a ballot of their
+                    // conjunction would select and re-compare per lane)
+                    const uint64_t quad = __builtin_amdgcn_ballot_w64(ee >= r[R32_BAND]) &
+                                          __builtin_amdgcn_ballot_w64(ym2 <= fmaf(kap, ee, kap));
+                    if (quad == __builtin_amdgcn_read_exec()) {
+                        ++n_quad_src;
+                        quad_acc<QN>(e0, e1, e2, ee, ym, r, r[R32_RA0], r[R32_TW], record_tb(r, fb0, fb1, fb2),
+                                     record_cb(r, fb0, fb1, fb2), fb0, fb1, fb2, fkr, fnu, three, f0, f1, f2, fk);
+                        continue;
                     }
                 }
-                if (k < kend) {
-                    mixed_pair<QN>(T, shr[k], ra + (base + k) * RECA, k, self, a0, a1, a2, f0, f1, f2, fk, n_near,
-                                   n_quad_src);
-                    ++k;
+                if (QN) {
+    #pragma unroll
+                    for (int f = R32_QUAD_VECS; f < REC32A / 4; ++f) {
+                        const f32x4 v = shr[k][f];
+                        r[4 * f] = v[0];
+                        r[4 * f + 1] = v[1];
+                        r[4 * f + 2] = v[2];
+                        r[4 * f + 3] = v[3];
+                    }
+                }
+                // axial coordinate from the first node and perpendicular part
+                const float Ls = r[R32_L];
+                const float y = fmaf(0.5f, Ls, ym);
+                const float h0 = fmaf(-ym, r[R32_T], e0), h1 = fmaf(-ym, r[R32_T + 1], e1),
+                            h2 = fmaf(-ym, r[R32_T + 2], e2);
+                const float hh = fmaf(h2, h2, fmaf(h1, h1, h0 * h0));
+                const float ya = y - __builtin_amdgcn_fmed3f(y, 0.f, Ls);   // y clamped to [0, L]: one instruction
+                // FP64: near pairs, and nearly collinear ones (rho carries an absolute
+                // error of order |ym| eps32 in FP32)
+                if (hh + ya * ya < cut2 || ym2 > fmaf(ck2, hh, ck2)) {
+                    // k through an empty asm: the comparison stays in this branch
+                    // instead of becoming a per-lane counter stepped every source
+                    int ks = k;
+                    asm volatile("" : "+s"(ks));
+                    if (ks != self) {
+                        n_near += valid ? 1u : 0u;
+                        pair_acc_isolated_f64(xq0, xq1, xq2, bj0, bj1, bj2, ra + (base + k) * RECA, kr, nu, a0, a1, a2);
+                    }
+                } else {
+                    // the record's b and c carry the quadrature weight (1 without a quadrature)
+                    pair_acc_f32(y, h0, h1, h2, hh, fb0, fb1, fb2, r[R32_T], r[R32_T + 1], r[R32_T + 2], Ls, r[R32_B],
+                                 r[R32_B + 1], r[R32_B + 2], r[R32_C], r[R32_C + 1], r[R32_C + 2],
+                                 QN ? r[R32_IW] : 1.0f, fkr, fnu, f0, f1, f2, fk);
                 }
             }
-            __builtin_amdgcn_wave_barrier();
         }
         a0 += (double)fmaf(fk, fb0, f0);   // the b_j terms of the stage at once
         a1 += (double)fmaf(fk, fb1, f1);
@@ -498,10 +354,10 @@ __global__ __launch_bounds__(TILE, 5) void k_pair_mixed_safe(const Item *__restr
     if (lane == 0 && n_quad_block) atomicAdd(near_count + 1, (unsigned long long)n_quad_block);
 }
 
-// Source ranges from which k_pair_mixed_safe is used: its set-up costs a
-// wavefront the sphere around its targets and a test per 64 sources.  Ranges of
-// 64 and 128 sources (5,000 segments and fewer) lose up to 10 % with it, 256
-// about as much as they gain; 1024 and 2048 gain 5 %.
+// Source ranges from which the SAFE form is used: its set-up costs a wavefront
+// the sphere around its targets and a test per 64 sources.  Ranges of 64 and 128
+// sources (5,000 segments and fewer) lose up to 10 % with it, 256 about as much
+// as they gain; 1,024 and 2,048 gain 6-8 % in order at 2 and 4 points.
 constexpr int64_t SAFE_MIN_RANGE = 512;
 
 template <int QN>
@@ -510,15 +366,12 @@ static void launch_mixed(const Item *items, const Tile *tiles, const double *rec
                          unsigned long long *counters, int64_t n_items, int64_t range, hipStream_t st)
 {
     const double *ra = rec + (int64_t)REC64 * ns;
-    if (QN && range >= SAFE_MIN_RANGE) {
-        hipLaunchKernelGGL(k_pair_mixed_safe<QN ? QN : 2>, dim3((unsigned)n_items), dim3(TILE), 0, st, items, tiles, rec,
+    if (QN && range >= SAFE_MIN_RANGE)
+        hipLaunchKernelGGL((k_pair_mixed<QN ? QN : 2, true>), dim3((unsigned)n_items), dim3(TILE), 0, st, items,
+                           tiles, rec, ra, rec32, ns, g, kr, nu, k2, cut, partial, counters);
+    else
+        hipLaunchKernelGGL((k_pair_mixed<QN, false>), dim3((unsigned)n_items), dim3(TILE), 0, st, items, tiles, rec,
                            ra, rec32, ns, g, kr, nu, k2, cut, partial, counters);
-        hipLaunchKernelGGL((k_pair_mixed<QN ? QN : 2, true>), dim3((unsigned)n_items), dim3(TILE), 0, st, items, tiles, rec,
-                           ra, rec32, ns, g, kr, nu, k2, cut, partial, counters);
-    } else {
-        hipLaunchKernelGGL((k_pair_mixed<QN, false>), dim3((unsigned)n_items), dim3(TILE), 0, st, items, tiles, rec, ra, rec32, ns,
-                           g, kr, nu, k2, cut, partial, counters);
-    }
 }
 
 void launch_pair_mixed(const Item *items, const Tile *tiles, const double *rec, const float *rec32, int64_t ns,

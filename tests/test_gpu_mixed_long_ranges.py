@@ -1,7 +1,7 @@
 """The mixed all-pairs kernel for long source ranges (512 sources and more),
 which runs sources that every target point of a wavefront takes by quadrature
-in a loop without tests and leaves work items of scattered target points to the
-other kernel, against that kernel for shorter ranges, which tests every source.
+in a loop without tests, against the kernel for shorter ranges, which tests
+every source.
 
 Both flush FP32 sums to FP64 at the same 256 sources where ranges are multiples
 of 256, and take every pair by the same arithmetic, so that the forces differ by
@@ -25,7 +25,7 @@ pytestmark = pytest.mark.gpu
 def _volume(loops, nseg, box, shuffle=False):
     rng = np.random.default_rng(loops + nseg)
     x, seg, bur, nrm, _ = W._loops(rng, loops, box, 100.0, 500.0, nseg=nseg)
-    if shuffle:   # all segments, or the first half: every work item scattered, or some
+    if shuffle:   # all segments, or the first half: targets scattered in every work item, or in some
         m = seg.shape[1] if shuffle == "all" else seg.shape[1] // 2
         p = np.concatenate([rng.permutation(m), np.arange(m, seg.shape[1])])
         seg, bur, nrm = seg[:, p], bur[:, p], nrm[:, p]
@@ -51,7 +51,8 @@ def _forces(vol, Q, chunk, variant):
 # 128, 130, 164 and 47.  The densest volume leaves much to the tests.
 @pytest.mark.parametrize("loops,nseg,box,shuffle,Q", [
     (20, 32, 9000.0, False, 2), (20, 32, 9000.0, False, 4), (33, 27, 9000.0, False, 2), (36, 33, 9000.0, False, 3),
-    (20, 32, 9000.0, "all", 2), (48, 32, 9000.0, "half", 2), (24, 32, 1500.0, False, 2), (49, 16, 9000.0, False, 1), (815, 1, 9000.0, False, 2)])
+    (20, 32, 9000.0, "all", 2), (48, 32, 9000.0, "half", 2), (24, 32, 1500.0, False, 2),
+    (49, 16, 9000.0, False, 1), (815, 1, 9000.0, False, 2)])
 @pytest.mark.parametrize("variant", [0, 2])
 def test_same_as_with_short_ranges(loops, nseg, box, shuffle, Q, variant):
     if nseg == 1:   # separate straight segments, no two with one Burgers vector
