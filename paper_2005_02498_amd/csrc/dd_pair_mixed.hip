@@ -119,10 +119,9 @@ __device__ __forceinline__ void safe_quad(const MixedTarget &T, const float *r, 
 // tests: as two loops or a called function the latter copies the four sums for
 // every source (12-16 v_mov), 5-15 % of a volume whose segments come in no order,
 // where next to no source is safe for a whole wavefront.  Against the loop with the
-// tests alone: 16,384 segments at 4 points 1.97 -> 1.81 ms, a step of 65,536 at 2
-// points 15.2 -> 14.2 ms; at 1 point 643 -> 661 us, 65,536 shuffled segments at 2
-// points 17.8 -> 18.1 ms: 1-4 % for a pass that finds little.  Five wavefronts per
-// SIMD (92 VGPRs, no scratch).
+// tests alone: 16,384 segments at 4 points 1.96 -> 1.84 ms, 65,536 at 2 points 15.1 ->
+// 14.0 ms; 16,384 and 65,536 shuffled segments at 2 points 1.25 -> 1.29 and 17.8 ->
+// 18.1 ms, for a pass that finds little.  Five wavefronts per SIMD (92 VGPRs, no scratch).
 template <int QN, bool SAFE>
 __global__ __launch_bounds__(TILE, SAFE ? 5 : 1) void k_pair_mixed(
     const Item *__restrict__ items, const Tile *__restrict__ tiles, const double *__restrict__ rec,
@@ -357,8 +356,12 @@ __global__ __launch_bounds__(TILE, SAFE ? 5 : 1) void k_pair_mixed(
 // Source ranges from which the SAFE form is used: its set-up costs a wavefront
 // the sphere around its targets and a test per 64 sources.  Ranges of 64 and 128
 // sources (5,000 segments and fewer) lose up to 10 % with it, 256 about as much
-// as they gain; 1,024 and 2,048 gain 6-8 % in order at 2 and 4 points.
+// as they gain; 1,024 and 2,048 gain 6-8 % in order at 2 and 4 points.  With one
+// Gauss point a wavefront holds two loops of 32, which lie apart and share no
+// Burgers vector: 16,384 segments at ranges of 512 and 1,024 641 and 650 us, with the
+// SAFE form 652 and 671, shuffled 734 and 755.
 constexpr int64_t SAFE_MIN_RANGE = 512;
+constexpr int SAFE_MIN_GAUSS = 2;
 
 template <int QN>
 static void launch_mixed(const Item *items, const Tile *tiles, const double *rec, const float *rec32, int64_t ns,
@@ -366,7 +369,7 @@ static void launch_mixed(const Item *items, const Tile *tiles, const double *rec
                          unsigned long long *counters, int64_t n_items, int64_t range, hipStream_t st)
 {
     const double *ra = rec + (int64_t)REC64 * ns;
-    if (QN && range >= SAFE_MIN_RANGE)
+    if (QN && range >= SAFE_MIN_RANGE && g.n >= SAFE_MIN_GAUSS)
         hipLaunchKernelGGL((k_pair_mixed<QN ? QN : 2, true>), dim3((unsigned)n_items), dim3(TILE), 0, st, items,
                            tiles, rec, ra, rec32, ns, g, kr, nu, k2, cut, partial, counters);
     else
