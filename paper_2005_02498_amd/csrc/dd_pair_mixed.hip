@@ -118,10 +118,13 @@ __device__ __forceinline__ void safe_quad(const MixedTarget &T, const float *r, 
 // 89 with a shared Burgers vector.  The inner loop stands inside the loop with the
 // tests: as two loops or a called function the latter copies the four sums for
 // every source (12-16 v_mov), 5-15 % of a volume whose segments come in no order,
-// where next to no source is safe for a whole wavefront.  Against the loop with the
-// tests alone: 16,384 segments at 4 points 1.96 -> 1.84 ms, 65,536 at 2 points 15.1 ->
-// 14.0 ms; 16,384 and 65,536 shuffled segments at 2 points 1.25 -> 1.29 and 17.8 ->
-// 18.1 ms, for a pass that finds little.  Five wavefronts per SIMD (92 VGPRs, no scratch).
+// where next to no source is safe for a whole wavefront.  After two groups of 64 in
+// a row with fewer than 8 safe sources only the first group of a stage is looked at,
+// until one has more: shuffled segments 1 % less.  Against the loop with the tests
+// alone: 16,384 segments at 4 points 1.96 -> 1.84 ms, 65,536 at 2 points 15.1 -> 14.0
+// ms; 16,384 and 65,536 shuffled segments at 2 points 1.25 -> 1.28 and 17.8 -> 17.9
+// ms.  Five wavefronts per SIMD (92 VGPRs, no scratch).  Left out: the index of the next
+// safe source in place of the mask (the copies come back, 14-19 % of shuffled segments).
 template <int QN, bool SAFE>
 __global__ __launch_bounds__(TILE, SAFE ? 5 : 1) void k_pair_mixed(
     const Item *__restrict__ items, const Tile *__restrict__ tiles, const double *__restrict__ rec,
@@ -187,6 +190,7 @@ __global__ __launch_bounds__(TILE, SAFE ? 5 : 1) void k_pair_mixed(
         same_b =
             __builtin_amdgcn_ballot_w64(fb0 == uniform(fb0) && fb1 == uniform(fb1) && fb2 == uniform(fb2)) == ~0ull;
     }
+    int misses = 0;   // groups of 64 sources in a row with next to none of them safe
     const MixedTarget T{xh0, xh1, xh2, xl0, xl1, xl2, fb0, fb1, fb2, fkr, fnu, three};
     __syncthreads();   // the counters are cleared before any wavefront adds to them
 
@@ -205,10 +209,10 @@ __global__ __launch_bounds__(TILE, SAFE ? 5 : 1) void k_pair_mixed(
             __syncthreads();
         }
         const float *s = rf + base * REC32A;
-        uint64_t safe = 0;
         for (int k64 = 0; k64 < n; k64 += SAFE ? 64 : TILE) {
             const int kgrp = SAFE ? min(n, k64 + 64) : n;
-            if (SAFE) {
+            uint64_t safe = 0;
+            if (SAFE && (misses < 2 || k64 == 0)) {
                 // 64 sources at a time: those that every target point of the wavefront
                 // takes by quadrature, tested one per lane
                 const int ks = k64 + (lane & 63);
@@ -224,6 +228,7 @@ __global__ __launch_bounds__(TILE, SAFE ? 5 : 1) void k_pair_mixed(
                 __builtin_amdgcn_wave_barrier();
                 safe = __builtin_amdgcn_ballot_w64(ok);
                 __builtin_amdgcn_wave_barrier();
+                misses = __builtin_popcountll(safe) < 8 ? misses + 1 : 0;
             }
             for (int k = k64; k < kgrp; ++k, s += REC32A) {
                 if (SAFE) {
