@@ -1774,7 +1774,7 @@ __global__ __launch_bounds__(PB_THREADS) void k_small(PBArgs A)
     const int ne = has_node ? s_eptr[own + 1] - s_eptr[own] : 0, e0 = has_node ? s_eptr[own] : 0;
     const int en0 = ne > 0 ? s_ent[e0] : 0, en1 = ne > 1 ? s_ent[e0 + 1] : en0;
     const int n_normals = has_node ? s_cnt[own] : 0;
-    double nr[6] = {0, 0, 0, 0, 0, 0}, sc = 0.0;
+    double nr[6] = {0, 0, 0, 0, 0, 0}, sc = -1.0;   // sc: 1 / (B ell), or negative: the node stays
     if (has_node)
         for (int c = 0; c < 6; ++c) nr[c] = s_nrm[own][c];
     // the point whose sums this thread shares: its segment, sigma_app b, Gauss point and weight
@@ -1964,7 +1964,7 @@ __global__ __launch_bounds__(PB_THREADS) void k_small(PBArgs A)
                 double ell = 0.5 * (s_rec[6][en0 >> 16] * A.a);
                 if (ne > 1) ell += 0.5 * (s_rec[6][en1 >> 16] * A.a);
                 for (int e = 2; e < ne; ++e) ell += 0.5 * (s_rec[6][s_ent[e0 + e] >> 16] * A.a);
-                sc = ell > 0.0 ? A.invB / ell : 0.0;
+                sc = ell > 0.0 ? A.invB / ell : -1.0;
             }
             __syncthreads();
             if (single) break;
@@ -2016,7 +2016,7 @@ __global__ __launch_bounds__(PB_THREADS) void k_small(PBArgs A)
                 A.force[nn + n] = F1;
                 A.force[2 * nn + n] = F2;
             }
-            if (sc != 0.0) {
+            if (sc >= 0.0) {   // (0 for a segment of infinite length, as k_glide takes it)
                 v0 = F0 * sc;
                 v1 = F1 * sc;
                 v2 = F2 * sc;
