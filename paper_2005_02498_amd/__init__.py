@@ -306,7 +306,7 @@ def dd_dissipation_fix(T, alpha=None, Lp=None, V=None, stream=None):
 
 
 def dd_set_plan(chunk_len: int = -1, variant: int = 0):
-    """Fix the work split (chunk_len 0 = heuristic, >= 256; mixed variant 0/1);
+    """Fix the work split (chunk_len 0 = heuristic, else >= 16; mixed variant 0 to 2);
     chunk_len < 0 returns to the automatic choice."""
     _check(lib().dd_set_plan(int(chunk_len), int(variant)))
 
